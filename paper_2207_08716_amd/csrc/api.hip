@@ -1466,18 +1466,13 @@ SweepPtrs<double> mg_ptrs(pt_grid* g, int l) {
 pt_status mg_smooth(pt_grid* g, int l, int n) {
     const bool coarsest = l == g->mg_levels - 1;
     Coef c = mg_coef(g, l, coarsest);
-    // the smoother has no damping: R is neither needed nor stored, and its
-    // input slots take the present V (a cache hit instead of three streams);
-    // the coarsest grid's damped sweeps run the stored-R form on its own R
+    // the smoother has no damping: R is neither read nor stored; the coarsest
+    // grid's damped sweeps run the stored-R form on its own R
     c.rform = 1;
     c.rwrite = coarsest ? 1 : 0;
+    c.undamped = coarsest ? 0 : 1;
     for (int k = 0; k < n; ++k) {
-        SweepPtrs<double> p = mg_ptrs(g, l);
-        if (!coarsest) {
-            p.rx = p.vx;
-            p.ry = p.vy;
-            p.rz = p.vz;
-        }
+        const SweepPtrs<double> p = mg_ptrs(g, l);
         hipError_t e = launch_iteration(g->mg_geom[l], c, p, MD_LINEAR, 0, g->stream);
         if (e != hipSuccess) return hip_fail(g, e, "multigrid sweep");
         if (l == 0) {

@@ -28,6 +28,25 @@
 // The next plane's loads are issued one step ahead.  Stresses and Darcy
 // fluxes never touch HBM; the iterated fields are written once.
 //
+// What bounds it: HBM on large grids (the 24 streams of a thesis sweep, at
+// the rate that many concurrent streams reach), one wave's chain of dependent
+// instructions through a plane step on small ones.  Both suffer from what
+// keeps a step from overlapping the next one's memory traffic and from every
+// instruction that is not arithmetic, so:
+//   - loads and stores go through buffer descriptors whose range check
+//     replaces the edges' branches and selects (see ldp); the number of
+//     memory operations of a step is the same for every wave, so a step waits
+//     for exactly its own plane's loads and never for its predecessor's
+//     stores (before, every step ended with all of them drained);
+//   - two steps per loop round on alternating register sets, so that no loaded
+//     value is copied before it is needed;
+//   - field pointers come from the argument segment at each step, constants
+//     combined on the host, divisions without operand rescaling: 391 vector
+//     instructions per plane step of the linear sweep instead of 640.
+// Measured at 511^3 (before -> after): thesis sweep 6.17 -> 5.59 ms, with
+// norms 8.75 -> 6.73, linear 5.68 -> 5.00, residual 6.47 -> 4.40, FP32
+// correction 2.67 -> 2.52; at 32^3 thesis 27.1 -> 22.3 us.
+//
 // Damped velocity update of the FP64 sweeps (eq (19) with the script's
 // damping): R' = f/rho_i + d R, V' = V + dtau_V R'.  Between checks the
 // sweep does not store R: with dtau_V unchanged since the last iteration,
@@ -44,31 +63,12 @@ namespace ptk {
 
 namespace {
 
-template <typename T, int W, int H>
-struct Lds {
-    T vx[H][W], vy[H][W], vz1[H][W];
-    T pf[H][W], kc[H][W], s[H][W], mu[H][W], mu1[H][W];
-    T ptn[H][W], txx[H][W], tyy[H][W], txy[H][W], w[H][W];
-    T txz[2][H][W], tyz[2][H][W];
-};
-
-// Block width of a sweep variant: the plain sweeps use BX, the variants that
-// also reduce norms BX_NORMS (both give 64-column output tiles).
-template <typename T, int MODE, bool NORMS>
-constexpr int sweep_bx() {
-    return (NORMS || MODE == MD_RESID) ? BX_NORMS : BX;
-}
-// Block height: taller tiles re-read fewer halo rows but need registers for
-// more waves per CU, and the number of tiles sets how full the last round of
-// blocks is; the heights below fit each variant's registers without spilling
-// and were measured fastest at 511^3.
-template <typename T, int MODE, bool NORMS>
-constexpr int sweep_by() {
-    if (NORMS || MODE == MD_RESID) return BY_NORMS;
-    if (MODE == MD_THESIS) return BY;
-    if (MODE == MD_CORR && sizeof(T) == 4) return BY_CORR32;
-    return BY_LINEAR;
-}
+// LDS planes of a block, each W x H values: inputs of plane p (L_VZ1, L_MU1:
+// of plane p + 1), then what the face updates read.  A margin of one row and
+// one value on either side lets every thread read its neighbours' places;
+// what a thread at the rim of the block reads there is never used.
+enum LdsPlane { L_VX, L_VY, L_VZ1, L_PF, L_KC, L_MU, L_MU1, L_PTN, L_TXX, L_TYY, L_TXY, L_TXZ, L_TYZ = L_TXZ + 2,
+                L_CORE = L_TYZ + 2 };   // then, where used: the solid fraction of two planes, tau_zz, the norms' W plane
 
 template <typename T>
 __device__ __forceinline__ T nanmax(T m, T v) {
@@ -76,51 +76,159 @@ __device__ __forceinline__ T nanmax(T m, T v) {
     return (v > m || v != v) ? v : m;
 }
 
-// Constants in the working precision of the sweep.
+// Larger of two values as one instruction (fmax would first quiet both
+// operands, one more instruction each, since it cannot see where they come
+// from; the results are the same).
+__device__ __forceinline__ double max1(double a, double b) {
+    double r;
+    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+__device__ __forceinline__ float max1(float a, float b) {
+    float r;
+    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
+    return r;
+}
+
+// a / b by Newton's iteration on the reciprocal and a corrected quotient,
+// the compiler's division without its rescaling of the operands (which only
+// quotients and divisors near the ends of the exponent range need);
+// infinities, zeros and NaN come out as from the division.
+__device__ __forceinline__ double quot(double a, double b) {
+    double y = __builtin_amdgcn_rcp(b);
+    y = __builtin_fma(__builtin_fma(-b, y, 1.0), y, y);
+    y = __builtin_fma(__builtin_fma(-b, y, 1.0), y, y);
+    const double q = a * y;
+    return __builtin_amdgcn_div_fixup(__builtin_fma(__builtin_fma(-b, q, a), y, q), b, a);
+}
+__device__ __forceinline__ float quot(float a, float b) {
+    float y = __builtin_amdgcn_rcpf(b);
+    y = __builtin_fmaf(__builtin_fmaf(-b, y, 1.0f), y, y);
+    const float q = a * y;
+    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-b, q, a), y, q), b, a);
+}
+
+// A copy in a register of its own: the queue moves out of the registers a
+// plane was loaded into, which then take the loads after next.  (Left to
+// itself the compiler loads into other registers and copies at the end of a
+// round, which waits for loads just issued.)
+__device__ __forceinline__ double fresh(double v) {
+    double r;
+    asm("v_mov_b64 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+__device__ __forceinline__ float fresh(float v) {
+    float r;
+    asm("v_mov_b32 %0, %1" : "=v"(r) : "v"(v));
+    return r;
+}
+
+// Buffer access to a tile's rows in one plane of a field: their address and
+// size are wave-uniform (scalar registers), a lane brings its byte offset in
+// them.  A lane with offset OFF_NONE, or any lane where the size is
+// given as 0, loads 0 and stores nothing, so that neither the rim of a field
+// needs a branch or a select: every step of a wave issues the same number of
+// loads and stores, and the wait for a plane's loads need not cover the
+// stores and loads issued after them.
+using u32 = unsigned int;
+constexpr u32 OFF_NONE = 0x80000000u;   // beyond any tile (the rows of a tile hold less than 2 GiB)
+constexpr int RSRC_FLAGS = 0x00020000;  // raw 32-bit data
+constexpr int NONTEMPORAL = 2;
+
+template <int AUX = 0, typename T>
+__device__ __forceinline__ T ldp(const T* rows, u32 bytes, u32 off) {
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(rows), 0, (int)bytes, RSRC_FLAGS);
+    if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, AUX));
+    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, AUX));
+}
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+template <typename T>
+__device__ __forceinline__ void stp(T* rows, u32 bytes, u32 off, T v) {
+    const auto r = __builtin_amdgcn_make_buffer_rsrc(rows, 0, (int)bytes, RSRC_FLAGS);
+    if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, 0);
+    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(u32, v), r, (int)off, 0, 0);
+}
+
+// Constants in the working precision of the sweep, combined on the host (the
+// scalar unit has no floating point: a product formed in the kernel would
+// occupy vector registers).
 template <typename T>
 struct CT {
-    T dxi, dyi, dzi, dt, dti, beta_d, alpha, beta_phi, rhofg, rhosg, rhobg, buoy, gdts_inv, beta_n,
-        rho_i_inv, dtauv_c, dtaupt_c, dtaupf_c, dampx, dampy, dampz, ab, third, gbg_half;
-    int mech_off, rform, rwrite;
-    __device__ explicit CT(const Coef& c)
-        : dxi(T(c.dxi)), dyi(T(c.dyi)), dzi(T(c.dzi)), dt(T(c.dt)), dti(T(c.dti)), beta_d(T(c.beta_d)),
-          alpha(T(c.alpha)), beta_phi(T(c.beta_phi)), rhofg(T(c.rhofg)), rhosg(T(c.rhosg)),
-          rhobg(T(c.rhobg)), buoy(T(c.buoy)), gdts_inv(T(c.gdts_inv)), beta_n(T(c.beta_n)),
-          rho_i_inv(T(c.rho_i_inv)), dtauv_c(T(c.dtauv_c)), dtaupt_c(T(c.dtaupt_c)),
-          dtaupf_c(T(c.dtaupf_c)), dampx(T(c.dampx)), dampy(T(c.dampy)), dampz(T(c.dampz)),
-          ab(T(c.ab)), third(T(c.third)), gbg_half(T(c.gbg_half)), mech_off(c.mech_off), rform(c.rform),
-          rwrite(c.rwrite) {}
+    T dxi, dyi, dzi, third;
+    T hxx, hyy, buoy;                     // -1/(2 dx^2), -1/(2 dy^2); Darcy buoyancy
+    T dtaupt_c, bdt, alpha, bda;          // beta_d/dt, alpha, alpha beta_d/dt
+    T dtaupf_c, ab, bdab;                 // alpha/B, (alpha/B) beta_d/dt
+    T gdts, gdts4, beta_n;                // 1/(G dtS), a quarter of it
+    T rho_i_inv, dtauv_c, dampx, dampy, dampz;
+    T rhofg, rhosg, rhobg;
+    T hdx, hdy, hdz, bpt, dt;             // 1/(2 dx) ..., beta_phi/dt
+    T gbg_half;
+    explicit CT(const Coef& c)
+        : dxi(T(c.dxi)), dyi(T(c.dyi)), dzi(T(c.dzi)), third(T(c.third)), hxx(T(-0.5 * c.dxi * c.dxi)),
+          hyy(T(-0.5 * c.dyi * c.dyi)), buoy(T(c.buoy)), dtaupt_c(T(c.dtaupt_c)),
+          bdt(T(c.beta_d * c.dti)), alpha(T(c.alpha)), bda(T(c.beta_d * c.alpha * c.dti)), dtaupf_c(T(c.dtaupf_c)),
+          ab(T(c.ab)), bdab(T(c.beta_d * c.ab * c.dti)), gdts(T(c.gdts_inv)), gdts4(T(0.25 * c.gdts_inv)),
+          beta_n(T(c.beta_n)), rho_i_inv(T(c.rho_i_inv)), dtauv_c(T(c.dtauv_c)), dampx(T(c.dampx)),
+          dampy(T(c.dampy)), dampz(T(c.dampz)), rhofg(T(c.rhofg)), rhosg(T(c.rhosg)), rhobg(T(c.rhobg)),
+          hdx(T(0.5 * c.dxi)), hdy(T(0.5 * c.dyi)), hdz(T(0.5 * c.dzi)), bpt(T(c.beta_phi * c.dti)), dt(T(c.dt)),
+          gbg_half(T(c.gbg_half)) {
+        if (c.mech_off) {   // V, R and Pt stay as they are: no pseudo step, R' = R
+            dtaupt_c = dtauv_c = rho_i_inv = T(0);
+            dampx = dampy = dampz = T(1);
+        }
+    }
 };
 
+// Kernel arguments as one block, so that they can be read again from the
+// argument segment where they are used (see the sweep).
+template <typename T>
+struct SweepArgs {
+    Geom g;
+    CT<T> c;
+    SweepPtrs<T> p;
+};
+
+// Damping memory of a sweep variant: the previous velocity iterate (in the
+// rx..rz inputs), the stored damped residual, or none (damping factor 0).
+constexpr int RM_VPREV = 0, RM_STORED = 1, RM_NONE = 2;
+
 // One face's damped velocity update (see the header): returns V', sets the
-// damped residual R' in r.  q: the stored R (rform) or V_prev.
-template <typename T, typename C>
+// damped residual R' in r.  q: the stored R or V_prev.
+template <int RM, typename T, typename C>
 __device__ __forceinline__ T damped_update(const C& c, T v_c, T q, T f, T damp, T dtv, T& r) {
-    if (c.rform) {
+    if constexpr (RM == RM_STORED) {
         r = f * c.rho_i_inv + damp * q;
+        return v_c + dtv * r;
+    } else if constexpr (RM == RM_NONE) {
+        r = f * c.rho_i_inv;
         return v_c + dtv * r;
     }
     const T v = v_c + dtv * (f * c.rho_i_inv) + damp * (v_c - q);
-    r = (v - v_c) / dtv;
+    r = quot(v - v_c, dtv);
     return v;
 }
 
-// HV, if not 0, overrides the variant's block height.  BGS: the background
-// shear of eq (32) is on (a variant of its own: the plain thesis sweep has no
-// register to spare for it).
-template <typename T, int MODE, bool NORMS, int HV = 0, bool BGS = false>
-__global__ __launch_bounds__((sweep_bx<T, MODE, NORMS>() * (HV ? HV : sweep_by<T, MODE, NORMS>()))) void k_sweep(
-    Geom g, Coef cd, SweepPtrs<T> p) {
-    constexpr int W = sweep_bx<T, MODE, NORMS>();
-    constexpr int H = HV ? HV : sweep_by<T, MODE, NORMS>();
+// Waves per SIMD a block of n threads is compiled for: what it has itself,
+// but three for small blocks, of which several share a compute unit.
+constexpr int sweep_waves(int n) { return n > 768 ? 4 : (n > 448 && n <= 512) ? 2 : 3; }
+
+// RM: where the damping memory is; RW: store the damped residual R'.  W x H:
+// the block's threads.  BGS: the background shear of eq (32) is on.
+template <typename T, int MODE, bool NORMS, int RM, bool RW, int W, int H, bool BGS>
+__global__ __launch_bounds__(W * H, sweep_waves(W * H)) void k_sweep(SweepArgs<T> args) {
     static_assert(W * H <= 1024, "a block holds at most 1024 threads");
     constexpr bool UPD_LP = (MODE == MD_THESIS);
     constexpr bool RESID = (MODE == MD_RESID);
     constexpr bool CORR = (MODE == MD_CORR);
     constexpr bool WNORM = NORMS || RESID;
-    __shared__ Lds<T, W, H> sh;
-    const CT<T> c(cd);
-    const T zero = T(0), half = T(0.5), one = T(1), two = T(2), quarter = T(0.25);
+    constexpr bool LATE_C = UPD_LP;
+    constexpr bool RREAD = !RESID && RM != RM_NONE;
+    constexpr int L_S = L_CORE, L_TZZ = L_S + (UPD_LP ? 2 : 0), L_W = L_TZZ + (UPD_LP ? 1 : 0), NPL = L_W + (NORMS ? 1 : 0);
+    constexpr int WH = W * H;
+    __shared__ T lds[NPL * WH + 2 * (W + 1)];
+    const Geom& g = args.g;
+    const CT<T>& c = args.c;
+    const T zero = T(0), one = T(1), two = T(2), quarter = T(0.25);
 
     const int gx = (g.nx + W - 3) / (W - 2);
     const int gy = (g.ny + H - 3) / (H - 2);
@@ -140,129 +248,180 @@ __global__ __launch_bounds__((sweep_bx<T, MODE, NORMS>() * (HV ? HV : sweep_by<T
     const bool ci = (i >= 0) && (i < g.nx);
     const bool cj = (j >= 0) && (j < g.ny);
     const bool cell = ci && cj;
-    const bool vxcol = (i >= 0) && (i <= g.nx) && cj;   // x-faces of this column
-    const bool vycol = ci && (j >= 0) && (j <= g.ny);   // y-faces of this column
     const bool outc = cell && tx >= 1 && tx <= W - 2 && ty >= 1 && ty <= H - 2;
     const bool cellq = cell && tx <= W - 2 && ty <= H - 2;
-    const bool edge = tx >= 1 && ty >= 1;
+    // waves without a row of the tile skip what only tile cells need
+    const bool tile_wave = __builtin_amdgcn_ballot_w64(tx >= 1 && tx <= W - 2 && ty >= 1 && ty <= H - 2) != 0;
+    const bool e_xy = i >= 1 && i < g.nx && j >= 1 && j < g.ny;   // interior edges of this column
+    const bool e_xz = i >= 1 && i < g.nx && cj;
+    const bool e_yz = j >= 1 && j < g.ny && ci;
 
-    // Every load is issued from an address clamped into the padded box
-    // (always inside the allocation); values of positions outside a field's
-    // extent are replaced by zero where they are consumed.  The loads are
-    // branch-free so that a whole plane's worth is in flight at once.
-    const int ic = min(max(i, 0), g.nx), jc = min(max(j, 0), g.ny);
-    const int64_t col = (int64_t)jc * g.P + ic;
-    auto at = [&](int k) -> int64_t { return (int64_t)min(max(k, 0), g.nz) * g.S + col; };
+    // Byte offsets in the tile's rows, OFF_NONE where the column has no such value
+    // or the thread no use for it (halo columns would otherwise fetch
+    // tile-only fields from HBM a second time).  Pf and k take the nearest
+    // cell's value outside the domain: the gradient, so the Darcy flux,
+    // through the wall comes out as zero and the largest neighbouring k is
+    // the same.
+    const u32 sz = (u32)sizeof(T);
+    const int row0 = max(by * (H - 2) - 1, 0), rows = min(by * (H - 2) - 1 + H - 1, g.ny) - row0 + 1;
+    const int64_t tile0 = (int64_t)row0 * g.P;
+    const u32 col = (u32)((j - row0) * (int)g.P + i);
+    const u32 o_near = (u32)((min(max(j, 0), g.ny - 1) - row0) * (int)g.P + min(max(i, 0), g.nx - 1)) * sz;
+    const u32 o_cell = cell ? col * sz : OFF_NONE;
+    const u32 o_vx = ((i >= 0) && (i <= g.nx) && cj) ? col * sz : OFF_NONE;
+    const u32 o_vy = (ci && (j >= 0) && (j <= g.ny)) ? col * sz : OFF_NONE;
+    const u32 o_q = cellq ? col * sz : OFF_NONE;
+    const u32 o_out = outc ? col * sz : OFF_NONE;
+    const u32 so = RESID ? (u32)sizeof(float) : sz;              // stored values
+    const u32 o_sx = (outc && i >= 1) ? col * so : OFF_NONE;
+    const u32 o_sy = (outc && j >= 1) ? col * so : OFF_NONE;
+    const u32 o_sc = outc ? col * so : OFF_NONE;
+    const u32 tile_bytes = (u32)(rows * (int)g.P) * sz;
+    const u32 tile_store = (u32)(rows * (int)g.P) * so;
+
+    // The field pointers are read from the argument segment at every plane
+    // step (scalar loads that hit the scalar cache): kept in registers they
+    // and the constants exceed the scalar file, and the compiler parks them
+    // in vector lanes (measured: 148 of 640 vector instructions per plane
+    // step were lane reads).  The empty asm keeps the loads in the loop.
+    using KPtrs = const __attribute__((address_space(4))) SweepPtrs<T>;
+    KPtrs* const kargs = (KPtrs*)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() +
+                                  offsetof(SweepArgs<T>, p));
+    auto ptrs = [&]() {
+        KPtrs* q = kargs;
+        asm volatile("" : "+s"(q));
+        return q;
+    };
 
     // queue set of a plane (own column): needed at planes p-1..p+1
     struct QSet { T vx, vy, vz, pf, kc, lp, mu; };
-    // cell set of a plane: needed at plane p only
-    struct CSet { T pt, pto, pfo, eta, lpo, rx, ry, rz, fox, foy, foz; };
-    auto load_q = [&](int k, QSet& q) {
-        const int64_t o = at(k);
-        q.vx = p.vx[o]; q.vy = p.vy[o]; q.vz = p.vz[o]; q.pf = p.pf[o];
-        q.kc = p.kc[o]; q.mu = p.mus[o];
-        q.lp = CORR ? zero : p.lp[o];
+    // cell set of a plane: needed for the cell quantities of plane p
+    struct CSet { T pt, pto, pfo, eta; };
+    // face set of a plane: needed when its faces and its porosity are updated
+    struct FSet { T lpo, rx, ry, rz, fox, foy, foz; };
+    auto load_q = [&](KPtrs* p, int k, QSet& q) {
+        const int64_t o = (int64_t)k * g.S + tile0;
+        const u32 nb = (k >= 0 && k < g.nz) ? tile_bytes : 0u;
+        const u32 nbz = (k >= 0 && k <= g.nz) ? tile_bytes : 0u;
+        q.vx = ldp(p->vx + o, nb, o_vx);
+        q.vy = ldp(p->vy + o, nb, o_vy);
+        q.vz = ldp(p->vz + o, nbz, o_cell);
+        q.pf = ldp(p->pf + o, nb, o_near);
+        q.kc = ldp(p->kc + o, nb, o_near);
+        q.mu = ldp(p->mus + o, nb, o_cell);
+        if constexpr (CORR) q.lp = zero;
+        else q.lp = ldp(p->lp + o, nb, o_cell);
     };
-    // The cell set is loaded only by the threads that use it (halo columns
-    // would otherwise fetch tile-only fields from HBM a second time).  The
-    // tile-only fields are read exactly once per launch: in FP64 they are
+    auto load_c = [&](KPtrs* p, int k, CSet& cs) {
+        const int64_t o = (int64_t)k * g.S + tile0;
+        const u32 nb = (k >= 0 && k < g.nz) ? tile_bytes : 0u;
+        cs.pt = ldp(p->pt + o, nb, o_q);
+        cs.pto = ldp(p->pto + o, nb, o_q);
+        cs.pfo = ldp(p->pfo + o, nb, o_q);
+        cs.eta = ldp(p->eta + o, nb, o_q);
+    };
+    // The tile-only fields are read exactly once per launch: in FP64 they are
     // loaded non-temporally, which keeps them from displacing halo data in
     // the caches.  The FP32 sweep keeps ordinary loads: its whole working set
     // fits the last-level cache at 127^3, where non-temporal loads made the
     // mixed solve 8 % slower.
-    auto once = [](const T* ptr) -> T {
-        if constexpr (sizeof(T) == 8) return __builtin_nontemporal_load(ptr);
-        else return *ptr;
-    };
-    auto load_c = [&](int k, CSet& cs) {
-        const int64_t o = at(k);
-        if (cellq) {
-            cs.pt = p.pt[o]; cs.pto = p.pto[o]; cs.pfo = p.pfo[o]; cs.eta = p.eta[o];
+    constexpr int ONCE = sizeof(T) == 8 ? NONTEMPORAL : 0;
+    auto load_f = [&](KPtrs* p, int k, FSet& f) {
+        const int64_t o = (int64_t)k * g.S + tile0;
+        const u32 nb = (k >= kz0 && k < kz1) ? tile_bytes : 0u;
+        if constexpr (UPD_LP) f.lpo = ldp<ONCE>(p->lpo + o, nb, o_out);
+        else f.lpo = zero;
+        if constexpr (RREAD) {
+            f.rx = ldp<ONCE>(p->rx + o, nb, o_out);
+            f.ry = ldp<ONCE>(p->ry + o, nb, o_out);
+            f.rz = ldp<ONCE>(p->rz + o, nb, o_out);
+        } else {
+            f.rx = f.ry = f.rz = zero;
         }
-        if (outc) {
-            cs.lpo = UPD_LP ? once(&p.lpo[o]) : zero;
-            if (!RESID) {
-                cs.rx = once(&p.rx[o]);
-                cs.ry = once(&p.ry[o]);
-                cs.rz = once(&p.rz[o]);
+        f.fox = ldp<ONCE>(p->fox + o, nb, o_out);
+        f.foy = ldp<ONCE>(p->foy + o, nb, o_out);
+        f.foz = ldp<ONCE>(p->foz + o, nb, o_out);
+    };
+    // outputs of a plane
+    struct OSet { T vx, vy, vz, rx, ry, rz, pt, pf, lp; };
+    auto store = [&](KPtrs* p, int k, bool live, const OSet& s) {
+        const int64_t o = (int64_t)k * g.S + tile0;
+        const u32 nb = live ? tile_store : 0u;
+        const u32 nbz = (live && k >= 1) ? tile_store : 0u;
+        if constexpr (RESID) {
+            stp(p->res_fx + o, nb, o_sx, float(s.vx));
+            stp(p->res_fy + o, nb, o_sy, float(s.vy));
+            stp(p->res_fz + o, nbz, o_sc, float(s.vz));
+            stp(p->res_rpt + o, nb, o_sc, float(s.pt));
+            stp(p->res_rpf + o, nb, o_sc, float(s.pf));
+        } else {
+            stp(p->vx_o + o, nb, o_sx, s.vx);
+            stp(p->vy_o + o, nb, o_sy, s.vy);
+            stp(p->vz_o + o, nbz, o_sc, s.vz);
+            if constexpr (RW) {
+                stp(p->rx_o + o, nb, o_sx, s.rx);
+                stp(p->ry_o + o, nb, o_sy, s.ry);
+                stp(p->rz_o + o, nbz, o_sc, s.rz);
             }
-            cs.fox = once(&p.fox[o]);
-            cs.foy = once(&p.foy[o]);
-            cs.foz = once(&p.foz[o]);
+            stp(p->pt_o + o, nb, o_sc, s.pt);
+            stp(p->pf_o + o, nb, o_sc, s.pf);
+            if constexpr (UPD_LP) stp(p->lp_o + o, nb, o_sc, s.lp);
         }
     };
-    auto mask_q = [&](int k, QSet& q) {
-        const bool pk = (k >= 0) && (k < g.nz);
-        q.vx = (vxcol && pk) ? q.vx : zero;
-        q.vy = (vycol && pk) ? q.vy : zero;
-        q.vz = (cell && k >= 0 && k <= g.nz) ? q.vz : zero;
-        q.pf = (cell && pk) ? q.pf : zero;
-        q.kc = (cell && pk) ? q.kc : zero;
-        q.lp = (cell && pk) ? q.lp : zero;
-        q.mu = (cell && pk) ? q.mu : zero;
-    };
-    auto solid = [&](bool ok, T lp) -> T { return CORR ? one : (ok ? T(exp(lp)) : zero); };
+    auto weight = [&](T s) -> T { return c.rhofg * (one - s) + c.rhosg * s; };
+    auto solid = [&](T lp) -> T { return CORR ? one : T(exp(lp)); };
+
+    T* const me = lds + (W + 1) + ty * W + tx;   // own place in a plane
+    auto sh = [&](int pl, int dx, int dy) -> T& { return me[pl * WH + dy * W + dx]; };
 
     // register queue (own column): _p = plane p-1, _c = plane p, _n = plane p+1
-    T vx_c, vy_c, vz_c, pf_p = zero, pf_c, kc_p = zero, kc_c, s_p = zero, s_c, mu_p = zero, mu_c, lp_c;
-    T ptn_p = zero, tzz_p = zero, rg_p = zero, w_p = zero, txz_c = zero, tyz_c = zero;
+    T vx_c, vy_c, vz_c, pf_c, kc_c, s_c, mu_p = zero, mu_c, lp_c;
+    T tzz_r = zero, rg_p = zero, w_p = zero, txz_c = zero, tyz_c = zero;
+    // of the level below plane p: Darcy flux, larger k and advection of the two cells
+    T qz_c = zero, kz_c = zero, az_c = zero;
     T nm[NNORM];
 #pragma unroll
     for (int q = 0; q < NNORM; ++q) nm[q] = zero;
 
-    QSet qn;     // plane p+1 (prefetched one step ahead)
-    CSet cc{};   // cell set of plane p (prefetched one step ahead)
-    {
-        const int p0 = kz0 - 1;
-        QSet q0;
-        load_q(p0, q0);
-        load_q(p0 + 1, qn);
-        load_c(p0, cc);
-        mask_q(p0, q0);
-        vx_c = q0.vx; vy_c = q0.vy; vz_c = q0.vz; pf_c = q0.pf; kc_c = q0.kc; lp_c = q0.lp; mu_c = q0.mu;
-        s_c = solid(cell && p0 >= 0, lp_c);
-    }
+    FSet ff;   // face set of plane p, loaded at the end of the step before
 
-    for (int pz = kz0 - 1; pz < kz1; ++pz) {
+    // One plane step: the loads of the next step go to qnn and cn, plane
+    // pz + 1 of the queue is in qn, the cell set of plane pz in cc (both
+    // loaded one step ahead).
+    auto step = [&](int pz, const QSet& qn, QSet& qnn, CSet& cc, CSet& cn) __attribute__((always_inline)) {
         const bool plc = pz >= 0;                // plane pz is a real plane
         const bool pln = pz + 1 < g.nz;          // plane pz+1 is a real plane
         const bool live = pz >= kz0;             // outputs of this plane belong to the block
+        const int bn = (pz + 1) & 1, bc = pz & 1;
+        KPtrs* const p = ptrs();
 
         // prefetch what the next step needs
-        QSet qnn;
-        CSet cn = cc;
-        load_q(pz + 2, qnn);
-        load_c(pz + 1, cn);
+        load_q(p, pz + 2, qnn);
+        if constexpr (!LATE_C) load_c(p, pz + 1, cn);
 
-        // plane pz+1 for the queue (arrived during the previous step)
-        mask_q(pz + 1, qn);
         const T vx_n = qn.vx, vy_n = qn.vy, vz_n = qn.vz, pf_n = qn.pf, kc_n = qn.kc;
         const T lp_n = qn.lp, mu_n = qn.mu;
-        const T s_n = solid(cell && pln, lp_n);
+        const T s_n = solid(lp_n);
+        const T pt = cc.pt, pto = cc.pto, pfo = cc.pfo, eta = cc.eta;
 
-        // plane pz values needed for the cell quantities
-        const bool cq = cellq && plc;
-        const bool oc = outc && plc && live;
-        const T pt = cc.pt, pto = cc.pto, pfo = cc.pfo, eta = cc.eta, lpo = cc.lpo;
-        const T rx = cc.rx, ry = cc.ry, rz = cc.rz, fox = cc.fox, foy = cc.foy, foz = cc.foz;
-
-        sh.vx[ty][tx] = vx_c;
-        sh.vy[ty][tx] = vy_c;
-        sh.vz1[ty][tx] = vz_n;
-        sh.pf[ty][tx] = pf_c;
-        sh.kc[ty][tx] = kc_c;
-        sh.s[ty][tx] = s_c;
-        sh.mu[ty][tx] = mu_c;
-        sh.mu1[ty][tx] = mu_n;
+        sh(L_VX, 0, 0) = vx_c;
+        sh(L_VY, 0, 0) = vy_c;
+        sh(L_VZ1, 0, 0) = vz_n;
+        sh(L_PF, 0, 0) = pf_c;
+        sh(L_KC, 0, 0) = kc_c;
+        if constexpr (UPD_LP) sh(L_S + bc, 0, 0) = s_c;
+        sh(L_MU, 0, 0) = mu_c;
+        sh(L_MU1, 0, 0) = mu_n;
         __syncthreads();
 
+        // Cells outside the domain compute values from zeros that nothing
+        // reads but the faces on the walls, which are not stored.
         // ---- cell quantities: div V, Pt' (eq (17)), stresses (eq (21)) ----
-        T ptn = zero, txx = zero, tyy = zero, tzz = zero, rg = zero, w = zero, chi = zero;
-        T rpt_k = zero;
-        if (cq) {
-            const T dxv = (sh.vx[ty][tx + 1] - vx_c) * c.dxi;
-            const T dyv = (sh.vy[ty + 1][tx] - vy_c) * c.dyi;
+        T ptn, txx, tyy, tzz, rg = zero, w = zero, chi, rpt_k, txy, txz_n, tyz_n, mu_w, mu_s;
+        T pfn = zero, lpn = zero, rpf_k = zero;
+        auto cell_part = [&]() __attribute__((always_inline)) {
+            const T dxv = (sh(L_VX, 1, 0) - vx_c) * c.dxi;
+            const T dyv = (sh(L_VY, 0, 1) - vy_c) * c.dyi;
             const T dzv = (vz_n - vz_c) * c.dzi;
             const T divv = dxv + dyv + dzv;
             const T dtp = c.dtaupt_c * mu_c;
@@ -272,235 +431,258 @@ __global__ __launch_bounds__((sweep_bx<T, MODE, NORMS>() * (HV ? HV : sweep_by<T
                 // d Pt' = [d Pt - dtau (div dV + r_Pt(x) - beta_d alpha dPf/dt - dPf chi)]
                 //         / (1 + dtau (beta_d/dt + chi)); chi is a stored field here
                 chi = eta;
-                ptn = (pt - dtp * (divv + pto - c.beta_d * c.alpha * pf_c * c.dti - pf_c * chi)) /
-                      (one + dtp * (c.beta_d * c.dti + chi));
-                rpt_k = pto + divv + c.beta_d * (pt - c.alpha * pf_c) * c.dti + (pt - pf_c) * chi;
+                ptn = quot(pt - dtp * (divv + pto - c.bda * pf_c - pf_c * chi), one + dtp * (c.bdt + chi));
+                rpt_k = pto + divv + c.bdt * (pt - c.alpha * pf_c) + (pt - pf_c) * chi;
             } else {
-                chi = one / (eta * s_c);
-                if (RESID || c.mech_off) {
+                chi = quot(one, eta * s_c);
+                if constexpr (RESID)
                     ptn = pt;
-                } else {
-                    ptn = (pt - dtp * (divv + c.beta_d * (-pto - c.alpha * (pf_c - pfo)) * c.dti - pf_c * chi)) /
-                          (one + dtp * (c.beta_d * c.dti + chi));
-                }
-                rpt_k = divv + c.beta_d * ((pt - pto) - c.alpha * (pf_c - pfo)) * c.dti + (pt - pf_c) * chi;
-                rg = c.rhofg * (one - s_c) + c.rhosg * s_c;
+                else
+                    ptn = quot(pt - dtp * (divv - c.bdt * (pto + c.alpha * (pf_c - pfo)) - pf_c * chi),
+                               one + dtp * (c.bdt + chi));
+                rpt_k = divv + c.bdt * ((pt - pto) - c.alpha * (pf_c - pfo)) + (pt - pf_c) * chi;
+                if constexpr (!UPD_LP) rg = weight(s_c);
             }
-            const T xi = mu_c * c.gdts_inv;
-            const T b = two * mu_c / (one + xi);
+            const T b = quot(two * mu_c, one + mu_c * c.gdts);
             const T d3 = divv * c.third;
             const T comp = RESID ? zero : c.beta_n * rpt_k;
             txx = b * ((dxv - d3) + comp);
             tyy = b * ((dyv - d3) + comp);
             tzz = b * ((dzv - d3) + comp);
             if (NORMS) w = b * comp - ptn + pt;
-        }
+        };
 
         // ---- Darcy flux and fluid pressure (eqs (18), (20)); porosity (eq (22)) ----
-        T pfn = zero, lpn = zero, rpf_k = zero;
-        if (oc) {
-            const T buoy = CORR ? zero : c.buoy;
-            const T kw = sh.kc[ty][tx - 1], ke = sh.kc[ty][tx + 1];
-            const T ks = sh.kc[ty - 1][tx], kn = sh.kc[ty + 1][tx];
-            const T qxl = (i >= 1) ? -half * (kw + kc_c) * (pf_c - sh.pf[ty][tx - 1]) * c.dxi : zero;
-            const T qxh = (i + 1 < g.nx) ? -half * (kc_c + ke) * (sh.pf[ty][tx + 1] - pf_c) * c.dxi : zero;
-            const T qyl = (j >= 1) ? -half * (ks + kc_c) * (pf_c - sh.pf[ty - 1][tx]) * c.dyi : zero;
-            const T qyh = (j + 1 < g.ny) ? -half * (kc_c + kn) * (sh.pf[ty + 1][tx] - pf_c) * c.dyi : zero;
-            const T qzl = (pz >= 1) ? -half * (kc_p + kc_c) * ((pf_c - pf_p) * c.dzi + buoy) : zero;
-            const T qzh = pln ? -half * (kc_c + kc_n) * ((pf_n - pf_c) * c.dzi + buoy) : zero;
-            const T divq = (qxh - qxl) * c.dxi + (qyh - qyl) * c.dyi + (qzh - qzl) * c.dzi;
-            T kl = kc_c;
-            if (i >= 1) kl = fmax(kl, kw);
-            if (i + 1 < g.nx) kl = fmax(kl, ke);
-            if (j >= 1) kl = fmax(kl, ks);
-            if (j + 1 < g.ny) kl = fmax(kl, kn);
-            if (pz >= 1) kl = fmax(kl, kc_p);
-            if (pln) kl = fmax(kl, kc_n);
-            const T dtf = c.dtaupf_c / kl;
+        T qz_n = zero, kz_n = zero, az_n = zero;
+        auto fluid_part = [&]() __attribute__((always_inline)) {
+            const T kw = sh(L_KC, -1, 0), ke = sh(L_KC, 1, 0);
+            const T ks = sh(L_KC, 0, -1), kn = sh(L_KC, 0, 1);
+            // (fluxes of the x and y faces without their factors -1/(2 dx), -1/(2 dy);
+            // products rounded before they are subtracted, so that equal
+            // fluxes cancel exactly: the sign of Pf - Pt in a quiet medium
+            // switches the bulk viscosity)
+            T qx, qy;
+            {
+#pragma clang fp contract(off)
+                qx = (kc_c + ke) * (sh(L_PF, 1, 0) - pf_c) - (kw + kc_c) * (pf_c - sh(L_PF, -1, 0));
+                qy = (kc_c + kn) * (sh(L_PF, 0, 1) - pf_c) - (ks + kc_c) * (pf_c - sh(L_PF, 0, -1));
+                // the flux through the level above, zero through the walls
+                const T hz = (plc && pln) ? T(-0.5) : zero;
+                qz_n = hz * (kc_c + kc_n) * ((pf_n - pf_c) * c.dzi + (CORR ? zero : c.buoy));
+            }
+            const T divq = c.hxx * qx + c.hyy * qy + (qz_n - qz_c) * c.dzi;
+            // largest permeability of the cell and its face neighbours
+            kz_n = max1(kc_c, kc_n);
+            const T kl = max1(max1(max1(kw, ke), max1(ks, kn)), max1(kz_c, kz_n));
+            const T dtf = quot(c.dtaupf_c, kl);
             if constexpr (CORR) {
-                pfn = (pf_c - dtf * (divq + pfo - c.beta_d * c.alpha * pt * c.dti - pt * chi)) /
-                      (one + dtf * (c.beta_d * c.ab * c.dti + chi));
-                if (WNORM) rpf_k = pfo + divq + c.beta_d * (c.ab * pf_c - c.alpha * pt) * c.dti + (pf_c - pt) * chi;
+                pfn = quot(pf_c - dtf * (divq + pfo - c.bda * pt - pt * chi), one + dtf * (c.bdab + chi));
+                if (WNORM) rpf_k = pfo + divq + c.bdt * (c.ab * pf_c - c.alpha * pt) + (pf_c - pt) * chi;
             } else if constexpr (RESID) {
                 pfn = pf_c;
-                rpf_k = divq + c.beta_d * (c.ab * (pf_c - pfo) - c.alpha * (pt - pto)) * c.dti + (pf_c - pt) * chi;
+                rpf_k = divq + c.bdt * (c.ab * (pf_c - pfo) - c.alpha * (pt - pto)) + (pf_c - pt) * chi;
             } else {
-                pfn = (pf_c - dtf * (divq + c.beta_d * (-c.ab * pfo - c.alpha * (pt - pto)) * c.dti - pt * chi)) /
-                      (one + dtf * (c.beta_d * c.ab * c.dti + chi));
-                if (WNORM)
-                    rpf_k = divq + c.beta_d * (c.ab * (pf_c - pfo) - c.alpha * (pt - pto)) * c.dti + (pf_c - pt) * chi;
+                pfn = quot(pf_c - dtf * (divq - c.bdt * (c.ab * pfo + c.alpha * (pt - pto)) - pt * chi),
+                           one + dtf * (c.bdab + chi));
+                if (WNORM) rpf_k = divq + c.bdt * (c.ab * (pf_c - pfo) - c.alpha * (pt - pto)) + (pf_c - pt) * chi;
             }
             if constexpr (UPD_LP) {
-                T adv = half * vx_c * (s_c - sh.s[ty][tx - 1]) * c.dxi;
-                adv += half * sh.vx[ty][tx + 1] * (sh.s[ty][tx + 1] - s_c) * c.dxi;
-                adv += half * vy_c * (s_c - sh.s[ty - 1][tx]) * c.dyi;
-                adv += half * sh.vy[ty + 1][tx] * (sh.s[ty + 1][tx] - s_c) * c.dyi;
-                adv += half * vz_c * (s_c - s_p) * c.dzi;
-                adv += half * vz_n * (s_n - s_c) * c.dzi;
-                const T dphidt = c.beta_phi * ((pfn - pfo) - (ptn - pto)) * c.dti + (pfn - ptn) / eta + adv;
-                lpn = lpo - c.dt * dphidt;
+                az_n = vz_n * (s_n - s_c);
+                const T adv = c.hdx * (vx_c * (s_c - sh(L_S + bc, -1, 0)) + sh(L_VX, 1, 0) * (sh(L_S + bc, 1, 0) - s_c)) +
+                              c.hdy * (vy_c * (s_c - sh(L_S + bc, 0, -1)) + sh(L_VY, 0, 1) * (sh(L_S + bc, 0, 1) - s_c)) +
+                              c.hdz * (az_c + az_n);
+                const T dphidt = c.bpt * ((pfn - pfo) - (ptn - pto)) + quot(pfn - ptn, eta) + adv;
+                lpn = ff.lpo - c.dt * dphidt;
             }
-        }
+        };
 
         // ---- shear stresses on the xy-edges of plane pz and the xz/yz-edges of level pz+1 ----
-        T txz_n = zero, tyz_n = zero, txy = zero;
-        if (edge) {
-            if (plc && i >= 1 && i < g.nx && j >= 1 && j < g.ny) {
-                const T mue = quarter * (sh.mu[ty - 1][tx - 1] + sh.mu[ty - 1][tx] + sh.mu[ty][tx - 1] + mu_c);
-                const T xie = mue * c.gdts_inv;
-                const T be = two * mue / (one + xie);
-                T exy = half * ((vx_c - sh.vx[ty - 1][tx]) * c.dyi + (vy_c - sh.vy[ty][tx - 1]) * c.dxi);
-                if constexpr (BGS) exy += c.gbg_half;   // background shear (eq (32))
-                txy = be * exy;
-            } else if (BGS && plc && i >= 0 && i <= g.nx && j >= 0 && j <= g.ny) {
-                // boundary edge: the perturbation slips freely, the background
-                // strain rate remains; viscosity averaged over the cells inside
-                // (the staged values outside the domain are zero)
-                const T cnt = T(((i >= 1) + (i < g.nx)) * ((j >= 1) + (j < g.ny)));
-                const T mue = (sh.mu[ty - 1][tx - 1] + sh.mu[ty - 1][tx] + sh.mu[ty][tx - 1] + mu_c) / cnt;
-                const T xie = mue * c.gdts_inv;
-                const T be = two * mue / (one + xie);
-                txy = be * c.gbg_half;
+        // (half the Maxwell coefficient 2 mu/(1 + xi) on an edge, from the sum
+        // of its four cells' viscosities; the strain rates without their 1/2)
+        auto edge_mu = [&](T sum) -> T { return quot(quarter * sum, one + sum * c.gdts4); };
+        auto edge_part = [&]() __attribute__((always_inline)) {
+            // (the neighbour viscosities also serve the velocity pseudo-steps
+            // below, after the input planes have been overwritten)
+            mu_w = sh(L_MU, -1, 0);
+            mu_s = sh(L_MU, 0, -1);
+            const T sxy = sh(L_MU, -1, -1) + mu_s + mu_w + mu_c;
+            T exy = (vx_c - sh(L_VX, 0, -1)) * c.dyi + (vy_c - sh(L_VY, -1, 0)) * c.dxi;
+            if constexpr (BGS) exy += two * c.gbg_half;   // background shear (eq (32))
+            txy = edge_mu(sxy) * exy;
+            txy = (e_xy && plc) ? txy : zero;
+            if constexpr (BGS) {
+                if (!e_xy && plc && i >= 0 && i <= g.nx && j >= 0 && j <= g.ny) {
+                    // boundary edge: the perturbation slips freely, the background
+                    // strain rate remains; viscosity averaged over the cells inside
+                    // (the staged values outside the domain are zero)
+                    const T cnt = T(((i >= 1) + (i < g.nx)) * ((j >= 1) + (j < g.ny)));
+                    const T mue = quot(sxy, cnt);
+                    txy = quot(two * mue, one + mue * c.gdts) * c.gbg_half;
+                }
             }
-            const bool lev = (pz + 1 >= 1) && (pz + 1 < g.nz);
-            if (lev && i >= 1 && i < g.nx && cj) {
-                const T mue = quarter * (sh.mu[ty][tx - 1] + mu_c + sh.mu1[ty][tx - 1] + mu_n);
-                const T xie = mue * c.gdts_inv;
-                const T be = two * mue / (one + xie);
-                const T exz = half * ((vx_n - vx_c) * c.dzi + (vz_n - sh.vz1[ty][tx - 1]) * c.dxi);
-                txz_n = be * exz;
+            const bool lev = plc && pln;
+            const T exz = (vx_n - vx_c) * c.dzi + (vz_n - sh(L_VZ1, -1, 0)) * c.dxi;
+            txz_n = edge_mu(mu_w + mu_c + sh(L_MU1, -1, 0) + mu_n) * exz;
+            txz_n = (e_xz && lev) ? txz_n : zero;
+            const T eyz = (vy_n - vy_c) * c.dzi + (vz_n - sh(L_VZ1, 0, -1)) * c.dyi;
+            tyz_n = edge_mu(mu_s + mu_c + sh(L_MU1, 0, -1) + mu_n) * eyz;
+            tyz_n = (e_yz && lev) ? tyz_n : zero;
+        };
+        if (tile_wave) {
+            // In the thesis sweeps the scheduler keeps the parts apart:
+            // interleaved, they need more registers than eleven waves have
+            // (the order is the one whose live values fit).
+            cell_part();
+            if constexpr (UPD_LP && BGS) {
+                __builtin_amdgcn_sched_barrier(0);
+                edge_part();
+                __builtin_amdgcn_sched_barrier(0);
+                fluid_part();
+            } else {
+                if constexpr (UPD_LP) __builtin_amdgcn_sched_barrier(0);
+                fluid_part();
+                if constexpr (UPD_LP) __builtin_amdgcn_sched_barrier(0);
+                edge_part();
             }
-            if (lev && j >= 1 && j < g.ny && ci) {
-                const T mue = quarter * (sh.mu[ty - 1][tx] + mu_c + sh.mu1[ty - 1][tx] + mu_n);
-                const T xie = mue * c.gdts_inv;
-                const T be = two * mue / (one + xie);
-                const T eyz = half * ((vy_n - vy_c) * c.dzi + (vz_n - sh.vz1[ty - 1][tx]) * c.dyi);
-                tyz_n = be * eyz;
-            }
+        } else {
+            cell_part();
+            edge_part();
         }
-        // Neighbour viscosities for the velocity pseudo-steps are taken into
-        // registers now: the input planes in LDS are overwritten by the next
-        // step's staging, which faster waves may reach while the face updates
-        // below are still running.
-        const T mu_w = (tx >= 1) ? sh.mu[ty][tx - 1] : zero;
-        const T mu_s = (ty >= 1) ? sh.mu[ty - 1][tx] : zero;
-        const int bn = (pz + 1) & 1, bc = pz & 1;
-        sh.ptn[ty][tx] = ptn;
-        sh.txx[ty][tx] = txx;
-        sh.tyy[ty][tx] = tyy;
-        sh.txy[ty][tx] = txy;
-        if (NORMS) sh.w[ty][tx] = w;
-        sh.txz[bn][ty][tx] = txz_n;
-        sh.tyz[bn][ty][tx] = tyz_n;
+        const T ptn_p = sh(L_PTN, 0, 0);   // plane p-1 (not used on the lowest plane)
+        T tzz_p = tzz_r;
+        if constexpr (UPD_LP) {
+            tzz_p = sh(L_TZZ, 0, 0);
+            sh(L_TZZ, 0, 0) = tzz;
+        }
+        sh(L_PTN, 0, 0) = ptn;
+        sh(L_TXX, 0, 0) = txx;
+        sh(L_TYY, 0, 0) = tyy;
+        sh(L_TXY, 0, 0) = txy;
+        if constexpr (NORMS) sh(L_W, 0, 0) = w;
+        sh(L_TXZ + bn, 0, 0) = txz_n;
+        sh(L_TYZ + bn, 0, 0) = tyz_n;
+        if constexpr (LATE_C) load_c(ptrs(), pz + 1, cc);
         __syncthreads();
 
         // ---- momentum (eq (19)) and damped velocity update on the tile ----
-        if (oc) {
-            const int64_t o = (int64_t)pz * g.S + col;
-            if (i >= 1) {
-                const T f = (txx - sh.txx[ty][tx - 1]) * c.dxi + (sh.txy[ty + 1][tx] - txy) * c.dyi +
-                            (txz_n - txz_c) * c.dzi - (ptn - sh.ptn[ty][tx - 1]) * c.dxi + fox;
-                if constexpr (RESID) {
-                    p.res_fx[o] = float(f);
-                    nm[0] = nanmax(nm[0], T(fabs(f)));
-                } else {
-                    T r;
-                    T v = damped_update<T>(c, vx_c, rx, f, T(c.dampx), T(c.dtauv_c / fmax(mu_c, mu_w)), r);
-                    if (c.mech_off) { r = rx; v = vx_c; }
-                    if (c.rwrite) p.rx_o[o] = r;
-                    p.vx_o[o] = v;
-                    if (NORMS) {
-                        nm[0] = nanmax(nm[0], T(fabs(f - (w - sh.w[ty][tx - 1]) * c.dxi)));
-                        nm[7] = nanmax(nm[7], T(fabs(v - vx_c)));
-                    }
-                }
-            }
-            if (j >= 1) {
-                const T f = (sh.txy[ty][tx + 1] - txy) * c.dxi + (tyy - sh.tyy[ty - 1][tx]) * c.dyi +
-                            (tyz_n - tyz_c) * c.dzi - (ptn - sh.ptn[ty - 1][tx]) * c.dyi + foy;
-                if constexpr (RESID) {
-                    p.res_fy[o] = float(f);
-                    nm[0] = nanmax(nm[0], T(fabs(f)));
-                } else {
-                    T r;
-                    T v = damped_update<T>(c, vy_c, ry, f, T(c.dampy), T(c.dtauv_c / fmax(mu_c, mu_s)), r);
-                    if (c.mech_off) { r = ry; v = vy_c; }
-                    if (c.rwrite) p.ry_o[o] = r;
-                    p.vy_o[o] = v;
-                    if (NORMS) {
-                        nm[0] = nanmax(nm[0], T(fabs(f - (w - sh.w[ty - 1][tx]) * c.dyi)));
-                        nm[7] = nanmax(nm[7], T(fabs(v - vy_c)));
-                    }
-                }
-            }
-            if (pz >= 1) {
-                const T fs = (sh.txz[bc][ty][tx + 1] - txz_c) * c.dxi + (sh.tyz[bc][ty + 1][tx] - tyz_c) * c.dyi +
-                             (tzz - tzz_p) * c.dzi - (ptn - ptn_p) * c.dzi;
-                T f;
-                if constexpr (CORR) {
-                    f = fs + foz;
-                } else {
-                    f = fs - (half * (rg_p + rg) - c.rhobg) + foz;
-                }
-                if constexpr (RESID) {
-                    p.res_fz[o] = float(f);
-                    nm[0] = nanmax(nm[0], T(fabs(f)));
-                } else {
-                    T r;
-                    T v = damped_update<T>(c, vz_c, rz, f, T(c.dampz), T(c.dtauv_c / fmax(mu_c, mu_p)), r);
-                    if (c.mech_off) { r = rz; v = vz_c; }
-                    if (c.rwrite) p.rz_o[o] = r;
-                    p.vz_o[o] = v;
-                    if (NORMS) {
-                        nm[0] = nanmax(nm[0], T(fabs(f - (w - w_p) * c.dzi)));
-                        nm[6] = nanmax(nm[6], T(fabs(v - vz_c)));
-                        nm[7] = nanmax(nm[7], T(fabs(v - vz_c)));
-                    }
-                }
+        OSet out{};
+        if (tile_wave) {
+            const T rx = ff.rx, ry = ff.ry, rz = ff.rz;
+            const T fx = (txx - sh(L_TXX, -1, 0)) * c.dxi + (sh(L_TXY, 0, 1) - txy) * c.dyi +
+                         (txz_n - txz_c) * c.dzi - (ptn - sh(L_PTN, -1, 0)) * c.dxi + ff.fox;
+            const T fy = (sh(L_TXY, 1, 0) - txy) * c.dxi + (tyy - sh(L_TYY, 0, -1)) * c.dyi +
+                         (tyz_n - tyz_c) * c.dzi - (ptn - sh(L_PTN, 0, -1)) * c.dyi + ff.foy;
+            const T fs = (sh(L_TXZ + bc, 1, 0) - txz_c) * c.dxi + (sh(L_TYZ + bc, 0, 1) - tyz_c) * c.dyi +
+                         (tzz - tzz_p) * c.dzi - (ptn - ptn_p) * c.dzi;
+            T fz;
+            if constexpr (CORR) {
+                fz = fs + ff.foz;
+            } else {
+                // (the thesis sweep keeps plane p-1's solid fraction and tau_zz
+                // in LDS: it has no register to spare for them)
+                if constexpr (UPD_LP) fz = fs - (T(0.5) * (weight(sh(L_S + bn, 0, 0)) + weight(s_c)) - c.rhobg) + ff.foz;
+                else fz = fs - (T(0.5) * (rg_p + rg) - c.rhobg) + ff.foz;
             }
             if constexpr (RESID) {
-                p.res_rpt[o] = float(rpt_k);
-                p.res_rpf[o] = float(rpf_k);
+                out.vx = fx;
+                out.vy = fy;
+                out.vz = fz;
+                out.pt = rpt_k;
+                out.pf = rpf_k;
             } else {
-                p.pt_o[o] = ptn;
-                p.pf_o[o] = pfn;
-                if constexpr (UPD_LP) {
-                    p.lp_o[o] = lpn;
+                out.vx = damped_update<RM>(c, vx_c, rx, fx, c.dampx, quot(c.dtauv_c, max1(mu_c, mu_w)), out.rx);
+                out.vy = damped_update<RM>(c, vy_c, ry, fy, c.dampy, quot(c.dtauv_c, max1(mu_c, mu_s)), out.ry);
+                out.vz = damped_update<RM>(c, vz_c, rz, fz, c.dampz, quot(c.dtauv_c, max1(mu_c, mu_p)), out.rz);
+                out.pt = ptn;
+                out.pf = pfn;
+                out.lp = lpn;
+            }
+            if constexpr (WNORM) {
+                if (outc && live) {
+                    const bool inx = i >= 1, iny = j >= 1, inz = pz >= 1;
+                    if constexpr (RESID) {
+                        if (inx) nm[0] = nanmax(nm[0], T(fabs(fx)));
+                        if (iny) nm[0] = nanmax(nm[0], T(fabs(fy)));
+                        if (inz) nm[0] = nanmax(nm[0], T(fabs(fz)));
+                    } else {
+                        if (inx) {
+                            nm[0] = nanmax(nm[0], T(fabs(fx - (w - sh(L_W, -1, 0)) * c.dxi)));
+                            nm[7] = nanmax(nm[7], T(fabs(out.vx - vx_c)));
+                        }
+                        if (iny) {
+                            nm[0] = nanmax(nm[0], T(fabs(fy - (w - sh(L_W, 0, -1)) * c.dyi)));
+                            nm[7] = nanmax(nm[7], T(fabs(out.vy - vy_c)));
+                        }
+                        if (inz) {
+                            nm[0] = nanmax(nm[0], T(fabs(fz - (w - w_p) * c.dzi)));
+                            nm[6] = nanmax(nm[6], T(fabs(out.vz - vz_c)));
+                            nm[7] = nanmax(nm[7], T(fabs(out.vz - vz_c)));
+                        }
+                    }
                     // phi' outside (0, 1): ln(1-phi)' not in (-inf, 0); checked
-                    // with the norms (the plain sweep has no register to spare)
-                    if (NORMS && !(lpn < zero && lpn > T(-1.0e300))) *p.domain = 1.0;
+                    // with the norms
+                    if (UPD_LP && !(lpn < zero && lpn > T(-1.0e300))) *p->domain = 1.0;
+                    nm[1] = nanmax(nm[1], T(fabs(rpt_k)));
+                    nm[2] = nanmax(nm[2], T(fabs(rpf_k)));
+                    if (UPD_LP) nm[3] = nanmax(nm[3], T(fabs(lpn - lp_c)));
+                    nm[4] = nanmax(nm[4], T(fabs(ptn - pt)));
+                    nm[5] = nanmax(nm[5], T(fabs(pfn - pf_c)));
                 }
             }
-            if (WNORM) {
-                nm[1] = nanmax(nm[1], T(fabs(rpt_k)));
-                nm[2] = nanmax(nm[2], T(fabs(rpf_k)));
-                if (UPD_LP) nm[3] = nanmax(nm[3], T(fabs(lpn - lp_c)));
-                nm[4] = nanmax(nm[4], T(fabs(ptn - pt)));
-                nm[5] = nanmax(nm[5], T(fabs(pfn - pf_c)));
-            }
         }
+        KPtrs* const pe = ptrs();
+        store(pe, pz, live, out);
+        load_f(pe, pz + 1, ff);
 
         // advance the register queue
-        vx_c = vx_n; vy_c = vy_n; vz_c = vz_n;
-        pf_p = pf_c; pf_c = pf_n;
-        kc_p = kc_c; kc_c = kc_n;
-        s_p = s_c; s_c = s_n;
-        mu_p = mu_c; mu_c = mu_n;
-        lp_c = lp_n;
-        ptn_p = ptn; tzz_p = tzz; rg_p = rg; w_p = w;
+        vx_c = fresh(vx_n); vy_c = fresh(vy_n); vz_c = fresh(vz_n);
+        pf_c = fresh(pf_n);
+        kc_c = fresh(kc_n);
+        s_c = s_n;
+        if constexpr (!UPD_LP) rg_p = rg;
+        mu_p = mu_c; mu_c = fresh(mu_n);
+        if constexpr (NORMS && UPD_LP) lp_c = fresh(lp_n);
+        if constexpr (!UPD_LP) tzz_r = tzz;
+        w_p = w;
         txz_c = txz_n; tyz_c = tyz_n;
-        qn = qnn;
-        cc = cn;
+        qz_c = qz_n; kz_c = kz_n; az_c = az_n;
+    };
+
+    // Two steps per round, the sets loaded ahead alternating between two
+    // register sets: no copy of a set still being loaded makes the wave wait
+    // for it at the end of a step.
+    QSet qa, qb;
+    CSet ca, cb;
+    {
+        const int p0 = kz0 - 1;
+        KPtrs* const p = ptrs();
+        load_q(p, p0, qb);
+        load_q(p, p0 + 1, qa);
+        load_c(p, p0, ca);
+        // as many (empty) stores as a step ends with, so that the first
+        // step waits for its loads as every other does
+        store(p, p0, false, OSet{});
+        load_f(p, p0, ff);
+        vx_c = qb.vx; vy_c = qb.vy; vz_c = qb.vz; pf_c = qb.pf; kc_c = qb.kc; lp_c = qb.lp; mu_c = qb.mu;
+        s_c = solid(lp_c);
+    }
+    for (int pz = kz0 - 1; pz < kz1; pz += 2) {
+        step(pz, qa, qb, ca, cb);
+        if (pz + 1 >= kz1) break;
+        if constexpr (LATE_C) step(pz + 1, qb, qa, ca, ca);
+        else step(pz + 1, qb, qa, cb, ca);
     }
 
     if constexpr (WNORM) {
-        // Block maximum: wave64 butterfly in each of the H row waves (the
-        // 66-wide layout's halo wave holds no tile cell and contributes
-        // nothing), then across the row waves through LDS.
-        __shared__ double red[H][NNORM];
+        // Block maximum: wave64 butterfly in each of the waves of whole tile
+        // rows (the halo wave holds no tile cell and contributes nothing),
+        // then across these waves through LDS.
+        constexpr int NW = (W - 2) * H / 64;
+        static_assert((W - 2) * H % 64 == 0, "whole waves of tile columns");
+        __shared__ double red[NW][NNORM];
         const int L = threadIdx.x;
         const int wave = L >> 6, lane = L & 63;
-        if (wave < H) {
+        if (wave < NW) {
 #pragma unroll
             for (int q = 0; q < NNORM; ++q) {
                 T v = nm[q];
@@ -515,8 +697,8 @@ __global__ __launch_bounds__((sweep_bx<T, MODE, NORMS>() * (HV ? HV : sweep_by<T
         __syncthreads();
         if (L < NNORM) {
             double v = 0.0;
-            for (int wv = 0; wv < H; ++wv) v = nanmax(v, red[wv][L]);
-            p.partials[(int64_t)blockIdx.x * NNORM + L] = v;
+            for (int wv = 0; wv < NW; ++wv) v = nanmax(v, red[wv][L]);
+            args.p.partials[(int64_t)blockIdx.x * NNORM + L] = v;
         }
     }
 }
@@ -552,51 +734,56 @@ __global__ __launch_bounds__(256) void k_reduce_max(const double* __restrict__ p
 
 }  // namespace
 
-template <typename T, int MODE, bool NORMS, int HV = 0>
-void launch_sweep(const Geom& g, const Coef& c, const SweepPtrs<T>& p, hipStream_t s) {
-    constexpr int W = sweep_bx<T, MODE, NORMS>(), H = HV ? HV : sweep_by<T, MODE, NORMS>();
-    const Geom v = sweep_geom(g, W, H);
+template <typename T, int MODE, bool NORMS, int RM, bool RW, int H>
+hipError_t launch_sweep(const Geom& g, const Coef& c, const SweepPtrs<T>& p, hipStream_t s) {
+    if (g.P > (int64_t)(0x7fffffff / (H * sizeof(T)))) return hipErrorInvalidValue;   // a tile's rows: below 2 GiB
+    const SweepArgs<T> a{sweep_geom(g, BX, H), CT<T>(c), p};
+    const dim3 grid((unsigned)iter_grid_blocks(g, BX, H)), block(BX * H);
     // the correction system has no background term (it is in its right-hand side)
     if (MODE != MD_CORR && c.gbg_half != 0.0)
-        hipLaunchKernelGGL((k_sweep<T, MODE, NORMS, HV, MODE != MD_CORR>), dim3((unsigned)iter_grid_blocks(g, W, H)),
-                           dim3(W * H, 1, 1), 0, s, v, c, p);
+        hipLaunchKernelGGL((k_sweep<T, MODE, NORMS, RM, RW, BX, H, MODE != MD_CORR>), grid, block, 0, s, a);
     else
-        hipLaunchKernelGGL((k_sweep<T, MODE, NORMS, HV, false>), dim3((unsigned)iter_grid_blocks(g, W, H)),
-                           dim3(W * H, 1, 1), 0, s, v, c, p);
+        hipLaunchKernelGGL((k_sweep<T, MODE, NORMS, RM, RW, BX, H, false>), grid, block, 0, s, a);
+    return hipGetLastError();
+}
+
+// The sweeps of one mode, by where the damping memory is and whether R' is
+// stored (the combinations the drivers use: R' is always stored with norms).
+template <typename T, int MODE, int H>
+hipError_t launch_mode(const Geom& g, const Coef& c, const SweepPtrs<T>& p, int norms, hipStream_t s) {
+    if (norms) {
+        if (c.rform) return launch_sweep<T, MODE, true, RM_STORED, true, BY_NORMS>(g, c, p, s);
+        return launch_sweep<T, MODE, true, RM_VPREV, true, BY_NORMS>(g, c, p, s);
+    } else if (c.rwrite) {
+        if (c.rform) return launch_sweep<T, MODE, false, RM_STORED, true, H>(g, c, p, s);
+        return launch_sweep<T, MODE, false, RM_VPREV, true, H>(g, c, p, s);
+    } else {
+        if (c.rform) return launch_sweep<T, MODE, false, RM_STORED, false, H>(g, c, p, s);
+        return launch_sweep<T, MODE, false, RM_VPREV, false, H>(g, c, p, s);
+    }
 }
 
 hipError_t launch_iteration(const Geom& g, const Coef& c, const SweepPtrs<double>& p, int mode, int norms,
                             hipStream_t s) {
     switch (mode) {
-        case MD_THESIS:
-            if (norms) launch_sweep<double, MD_THESIS, true>(g, c, p, s);
-            else launch_sweep<double, MD_THESIS, false>(g, c, p, s);
-            break;
+        case MD_THESIS: return launch_mode<double, MD_THESIS, BY>(g, c, p, norms, s);
         case MD_LINEAR:
-            if (norms) launch_sweep<double, MD_LINEAR, true>(g, c, p, s);
-            else launch_sweep<double, MD_LINEAR, false>(g, c, p, s);
-            break;
-        case MD_RESID:
-            launch_sweep<double, MD_RESID, false>(g, c, p, s);
-            break;
-        default:
-            return hipErrorInvalidValue;
+            if (c.undamped) return launch_sweep<double, MD_LINEAR, false, RM_NONE, false, BY_LINEAR>(g, c, p, s);
+            return launch_mode<double, MD_LINEAR, BY_LINEAR>(g, c, p, norms, s);
+        case MD_RESID: return launch_sweep<double, MD_RESID, false, RM_NONE, false, BY_NORMS>(g, c, p, s);
     }
-    return hipGetLastError();
+    return hipErrorInvalidValue;
 }
 
 hipError_t launch_correction(const Geom& g, const Coef& c, const SweepPtrs<float>& p, int norms, hipStream_t s) {
-    if (norms) launch_sweep<float, MD_CORR, true>(g, c, p, s);
-    else if (corr32_short(g)) launch_sweep<float, MD_CORR, false, BY_CORR32_SHORT>(g, c, p, s);
-    else launch_sweep<float, MD_CORR, false>(g, c, p, s);
-    return hipGetLastError();
+    if (corr32_short(g)) return launch_mode<float, MD_CORR, BY_CORR32_SHORT>(g, c, p, norms, s);
+    return launch_mode<float, MD_CORR, BY_CORR32>(g, c, p, norms, s);
 }
 
 hipError_t launch_correction64(const Geom& g, const Coef& c, const SweepPtrs<double>& p, int norms,
                                hipStream_t s) {
-    if (norms) launch_sweep<double, MD_CORR, true>(g, c, p, s);
-    else launch_sweep<double, MD_CORR, false>(g, c, p, s);
-    return hipGetLastError();
+    if (norms) return launch_sweep<double, MD_CORR, true, RM_STORED, true, BY_NORMS>(g, c, p, s);
+    return launch_sweep<double, MD_CORR, false, RM_STORED, true, BY_LINEAR>(g, c, p, s);
 }
 
 hipError_t launch_reduce_max(const double* partials, int64_t nblocks, double* out8, hipStream_t s) {

@@ -47,6 +47,7 @@ struct Coef {
     // sweep's header).  The correction sweeps always read and store R.
     int rform = 1;
     int rwrite = 1;
+    int undamped = 0;              // linear sweep without damping (the multigrid smoother): no R at all
 };
 
 // Sweep modes (see iter_kernel.hip).
@@ -158,26 +159,22 @@ __device__ __forceinline__ int64_t xcd_tile(int64_t L, int64_t total) {
 }
 
 // Thread layout of a W x H tile block (one-dimensional launch of W*H
-// threads).  In 66-wide blocks wave r (r < H) takes the 64 interior columns
-// of row r, so that every load and store of a row is one whole, aligned
-// 512-byte segment, and the last wave takes the two side halo columns of all
-// rows.  64-wide blocks map lanes to columns directly.
+// threads): first the W-2 interior columns of every row, row after row, then
+// the two side halo columns of all rows.  In 66-wide blocks wave r (r < H) so
+// takes the 64 interior columns of row r: every load and store of a row is
+// one whole, aligned 512-byte segment.
 template <int W, int H>
 __device__ __forceinline__ void tile_thread(int& tx, int& ty) {
-    if constexpr (W == 64) {
-        tx = (int)threadIdx.x & 63;
-        ty = (int)threadIdx.x >> 6;
+    static_assert(W == 66 || W == 34, "tiles are 64 or 32 columns wide");
+    constexpr int C = W - 2;
+    const int L = threadIdx.x;
+    if (L < C * H) {
+        tx = 1 + L % C;
+        ty = L / C;
     } else {
-        static_assert(W == 66, "tile blocks are 64 or 66 wide");
-        const int L = threadIdx.x;
-        if (L < 64 * H) {
-            tx = 1 + (L & 63);
-            ty = L >> 6;
-        } else {
-            const int r = L - 64 * H;
-            tx = (r < H) ? 0 : W - 1;
-            ty = (r < H) ? r : r - H;
-        }
+        const int r = L - C * H;
+        tx = (r < H) ? 0 : W - 1;
+        ty = (r < H) ? r : r - H;
     }
 }
 
