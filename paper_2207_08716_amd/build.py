@@ -3,6 +3,8 @@ from __future__ import annotations
 
 import os
 import subprocess
+import tempfile
+from concurrent.futures import ThreadPoolExecutor
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
@@ -12,7 +14,7 @@ SOURCES = ["api.hip", "iter_kernel.hip", "refresh_kernel.hip", "aux_kernels.hip"
            "mg_kernels.hip", "krylov_kernels.hip"]
 
 FLAGS = [
-    "-O3", "-std=c++17", "-fPIC", "-shared", "--offload-arch=gfx950",
+    "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-function",
 ]
@@ -22,11 +24,23 @@ def build(verbose: bool = False, extra=None) -> str:
     """Compile every source into libptporo.so (always recompiles)."""
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
     tmp = LIB + ".tmp"
-    cmd = [hipcc, *FLAGS, *(extra or []), "-I", os.path.join(ROOT, "include"), "-I", CSRC,
-           *[os.path.join(CSRC, s) for s in SOURCES], "-o", tmp]
-    if verbose:
-        print(" ".join(cmd))
-    subprocess.run(cmd, check=True)
+    inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
+    with tempfile.TemporaryDirectory() as objs:
+        # one compiler per source, side by side
+        def compile_one(src):
+            obj = os.path.join(objs, src + ".o")
+            cmd = [hipcc, *FLAGS, *(extra or []), *inc, "-c", os.path.join(CSRC, src), "-o", obj]
+            if verbose:
+                print(" ".join(cmd))
+            subprocess.run(cmd, check=True)
+            return obj
+
+        with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as pool:
+            built = list(pool.map(compile_one, SOURCES))
+        link = [hipcc, "-shared", "--offload-arch=gfx950", *built, "-o", tmp]
+        if verbose:
+            print(" ".join(link))
+        subprocess.run(link, check=True)
     os.replace(tmp, LIB)
     return LIB
 

@@ -14,6 +14,7 @@ using namespace ptk;
 
 struct pt_grid {
     Geom geom;
+    Tiling tiling;             // the sweeps' tiles on this grid
     pt_params prm;
     Coef coef;
     double* f[PT_NFIELDS][2];
@@ -51,6 +52,10 @@ struct pt_grid {
     pt_mg_params mgp{};        // multigrid parameters of the bound workspace
     int mg_levels = 0;         // grids of the hierarchy, the fine one included
     Geom mg_geom[PT_MG_MAX_LEVELS];
+    Tiling mg_tiling[PT_MG_MAX_LEVELS];
+    int64_t mg_parts = 0;      // blocks of the coarse grids' partial maxima
+    int64_t mg_off[PT_MG_MAX_LEVELS] = {};   // doubles before each coarse grid's boxes
+    int64_t mg_tail = 0;       // doubles before the restriction's scratch
     int mg_cur[PT_MG_MAX_LEVELS] = {};   // present copy of the coarse grids' iterated fields
     std::string err;
 };
@@ -122,7 +127,11 @@ void make_coef(pt_grid* g) {
     c.ab = p.alpha / p.B;
     c.third = 1.0 / 3.0;
     c.mech_off = (p.flags & PT_F_MECHOFF) ? 1 : 0;
-    g->geom.tall32 = (p.flags & PT_F_FP32_TALL) ? 1 : 0;
+    const int tall = (p.flags & PT_F_FP32_TALL) ? 1 : 0;
+    if (tall != g->geom.tall32 || g->tiling.most == 0) {
+        g->geom.tall32 = tall;
+        g->tiling = make_tiling(g->geom);
+    }
 }
 
 RefreshCoef make_refresh(const pt_grid* g, double r_eta, double r_mu) {
@@ -221,13 +230,13 @@ pt_status check_ready(pt_grid* g) {
 // flag: 1], padded to a multiple of 256 bytes.  The flag is set (to 1) by the
 // kernels that write ln(1-phi) where phi leaves (0, 1).
 size_t ws_needed(const pt_grid* g) {
-    const int64_t head = norm_blocks(g->geom) * NNORM + NNORM + 1;
+    const int64_t head = g->tiling.most * NNORM + NNORM + 1;
     return (size_t)((head + 31) / 32 * 32) * sizeof(double);
 }
 
 double* domain_flag(pt_grid* g) {
     double* a = norm_area(g);
-    return a ? a + norm_blocks(g->geom) * NNORM + NNORM : nullptr;
+    return a ? a + g->tiling.most * NNORM + NNORM : nullptr;
 }
 
 pt_status clear_domain(pt_grid* g) {
@@ -269,9 +278,9 @@ SweepPtrs<double> sweep_ptrs(pt_grid* g) {
     return p;
 }
 
-pt_status reduce_norms(pt_grid* g) {
-    const int64_t nb = norm_blocks(g->geom);
-    double* out = norm_area(g) + nb * NNORM;
+// The norms from the partial maxima of nb blocks.
+pt_status reduce_norms(pt_grid* g, int64_t nb) {
+    double* out = norm_area(g) + g->tiling.most * NNORM;
     hipError_t e = launch_reduce_max(norm_area(g), nb, out, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "reduce");
     g->norms_pending = true;
@@ -296,10 +305,10 @@ pt_status iteration_impl(pt_grid* g, int update_lp, int norms, bool keep_r = fal
     }
     c.rform = vp ? 0 : 1;
     c.rwrite = (norms || c.mech_off || keep_r) ? 1 : 0;
-    hipError_t e = launch_iteration(g->geom, c, p, update_lp ? MD_THESIS : MD_LINEAR, norms, g->stream);
+    hipError_t e = launch_iteration(g->geom, g->tiling, c, p, update_lp ? MD_THESIS : MD_LINEAR, norms, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "iteration");
     if (norms) {
-        pt_status st = reduce_norms(g);
+        pt_status st = reduce_norms(g, g->tiling.norms64);
         if (st != PT_OK) return st;
     }
     for (int f = 0; f < PT_NPING; ++f) {
@@ -344,7 +353,7 @@ float* mx(pt_grid* g, int b) { return g->mws + (int64_t)b * mx_stride(g); }
 // The eight reduced norms and the domain flag (copied together).
 pt_status read_norms(pt_grid* g, pt_norms* out) {
     double host[NNORM + 1];
-    hipError_t e = hipMemcpyAsync(host, norm_area(g) + norm_blocks(g->geom) * NNORM, sizeof(host),
+    hipError_t e = hipMemcpyAsync(host, norm_area(g) + g->tiling.most * NNORM, sizeof(host),
                                   hipMemcpyDeviceToHost, g->stream);
     const hipError_t es = hipStreamSynchronize(g->stream);   // also on a failed copy: host is local
     if (e == hipSuccess) e = es;
@@ -360,7 +369,7 @@ pt_status read_norms(pt_grid* g, pt_norms* out) {
 // Largest value of a cell field (synchronises; uses the norm area, so the
 // last norms are no longer readable).
 pt_status cells_max(pt_grid* g, const double* f, double* out) {
-    const int64_t nb = norm_blocks(g->geom);
+    const int64_t nb = g->tiling.most;
     double* area = norm_area(g);
     hipError_t e = launch_cell_max(g->geom, f, area, nb, g->stream);
     if (e == hipSuccess) e = launch_reduce_max(area, nb, area + nb * NNORM, g->stream);
@@ -683,8 +692,10 @@ pt_status pt_solve_linear(pt_grid* g, double rtol, int64_t max_iter, int64_t* it
 
 pt_status pt_solve_linear_static(pt_grid* g, double rtol, int64_t max_iter, int64_t* iters, double* rho) {
     if (!g || !(rtol > 0.0) || max_iter < 1) return PT_EINVAL;
-    const int64_t need = norm_blocks(g->geom) * NNORM + NNORM + 1;
-    if (need > STATIC_SCRATCH_DOUBLES)
+    // the limit is on the blocks of 66 x 7 threads that the sweep with norms
+    // takes at most on a large grid
+    const int64_t most = std::max(iter_grid_blocks(g->geom, BX, 7), g->tiling.most);
+    if (most * NNORM + NNORM + 1 > STATIC_SCRATCH_DOUBLES)
         return fail(g, PT_EINVAL, "grid too large for the static scratch of pt_solve_linear_static "
                                   "(more than 16382 norm blocks); use pt_solve_linear with a bound workspace");
     double* sp = nullptr;
@@ -849,9 +860,9 @@ pt_status pt_residual(pt_grid* g) {
     p.res_fz = mx(g, MX_RES + 2);
     p.res_rpt = mx(g, MX_RES + 3);
     p.res_rpf = mx(g, MX_RES + 4);
-    hipError_t e = launch_iteration(g->geom, g->coef, p, MD_RESID, 1, g->stream);
+    hipError_t e = launch_iteration(g->geom, g->tiling, g->coef, p, MD_RESID, 1, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "residual");
-    return reduce_norms(g);
+    return reduce_norms(g, g->tiling.resid);
 }
 
 namespace {
@@ -883,9 +894,9 @@ pt_status correction_sweep(pt_grid* g, int cp, int cr, int norms, bool rform, bo
     Coef c = g->coef;
     c.rform = rform ? 1 : 0;
     c.rwrite = rwrite ? 1 : 0;
-    hipError_t e = launch_correction(g->geom, c, p, norms, g->stream);
+    hipError_t e = launch_correction(g->geom, g->tiling, c, p, norms, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "correction sweep");
-    if (norms) return reduce_norms(g);
+    if (norms) return reduce_norms(g, g->tiling.norms32);
     return PT_OK;
 }
 
@@ -959,9 +970,9 @@ pt_status mixed_core(pt_grid* g, const MixedTarget& t, double rtol, double eta_i
     int32_t outer = 0;
     pt_status st;
     for (;;) {
-        e = launch_iteration(g->geom, t.coef, rp, MD_RESID, 1, g->stream);
+        e = launch_iteration(g->geom, g->tiling, t.coef, rp, MD_RESID, 1, g->stream);
         if (e != hipSuccess) return hip_fail(g, e, "residual");
-        st = reduce_norms(g);
+        st = reduce_norms(g, g->tiling.resid);
         if (st != PT_OK) return st;
         pt_norms nm;
         st = read_norms(g, &nm);
@@ -1141,11 +1152,11 @@ pt_status transposed_solve(pt_grid* g, const double* kc, const double* mus, doub
     const int64_t box_bytes = ad_stride(g) * (int64_t)sizeof(double);
     hipError_t e = hipMemsetAsync(ad(g, 0), 0, 16 * box_bytes, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "adjoint clear");
-    const int64_t nb = norm_blocks(g->geom);
+    const int64_t nb = g->tiling.most;
     const double* rhs[5] = {ad(g, AD_RHS), ad(g, AD_RHS + 1), ad(g, AD_RHS + 2), ad(g, AD_RHS + 3), ad(g, AD_RHS + 4)};
     e = launch_absmax5(g->geom, rhs, norm_area(g), nb, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "rhs norm");
-    pt_status st = reduce_norms(g);
+    pt_status st = reduce_norms(g, nb);
     if (st != PT_OK) return st;
     pt_norms n0;
     st = read_norms(g, &n0);
@@ -1172,11 +1183,11 @@ pt_status transposed_solve(pt_grid* g, const double* kc, const double* mus, doub
             p.pto = ad(g, AD_RHS + 3); p.pfo = ad(g, AD_RHS + 4);
             p.eta = ad(g, AD_CHI); p.kc = kc; p.mus = mus;
             p.partials = norm_area(g);
-            e = launch_correction64(g->geom, g->coef, p, chk ? 1 : 0, g->stream);
+            e = launch_correction64(g->geom, g->tiling, g->coef, p, chk ? 1 : 0, g->stream);
             if (e != hipSuccess) return hip_fail(g, e, "adjoint sweep");
             cp ^= 1;
             if (chk) {
-                st = reduce_norms(g);
+                st = reduce_norms(g, g->tiling.norms64);
                 if (st != PT_OK) return st;
                 pt_norms nm;
                 st = read_norms(g, &nm);
@@ -1303,14 +1314,14 @@ int mg_plan(const pt_grid* g, const pt_mg_params& m, Geom* out) {
 // of any coarse grid (the chunking can give a smaller grid more blocks).
 int64_t mg_part_blocks(const Geom* geo, int L) {
     int64_t nb = 0;
-    for (int l = 1; l < L; ++l) nb = std::max(nb, norm_blocks(geo[l]));
+    for (int l = 1; l < L; ++l) nb = std::max(nb, sweep_blocks(geo[l], sweep_shape(geo[l], SK_F64)));
     return nb;
 }
-int64_t mg_part_doubles(const Geom* geo, int L) { return (mg_part_blocks(geo, L) * NNORM + NNORM + 1 + 31) / 32 * 32; }
+int64_t mg_part_doubles(int64_t blocks) { return (blocks * NNORM + NNORM + 1 + 31) / 32 * 32; }
 
 // Doubles of the grids' pieces.
 int64_t mg_levels_doubles(const Geom* geo, int L) {
-    int64_t n = mg_res_doubles(geo[0]) + mg_part_doubles(geo, L);
+    int64_t n = mg_res_doubles(geo[0]) + mg_part_doubles(mg_part_blocks(geo, L));
     for (int l = 1; l < L; ++l) {
         n += MG_NB * mg_stride(geo[l]);
         if (l < L - 1) n += mg_res_doubles(geo[l]);
@@ -1357,17 +1368,12 @@ size_t mg_needed(const pt_grid* g, const pt_mg_params& m) {
 
 // Workspace pieces.
 float* mg_res(pt_grid* g, int l, int q) {
-    double* base = g->gws;
-    if (l > 0) {
-        base += mg_res_doubles(g->mg_geom[0]) + mg_part_doubles(g->mg_geom, g->mg_levels);
-        for (int k = 1; k < l; ++k) base += MG_NB * mg_stride(g->mg_geom[k]) + mg_res_doubles(g->mg_geom[k]);
-        base += MG_NB * mg_stride(g->mg_geom[l]);
-    }
+    double* base = l > 0 ? g->gws + g->mg_off[l] + MG_NB * mg_stride(g->mg_geom[l]) : g->gws;
     return reinterpret_cast<float*>(base) + (int64_t)q * (box_of(g->mg_geom[l]) + 64);
 }
 double* mg_partials(pt_grid* g) { return g->gws + mg_res_doubles(g->mg_geom[0]); }
 double* mg_scr(pt_grid* g, int b) {
-    double* base = g->gws + mg_levels_doubles(g->mg_geom, g->mg_levels);
+    double* base = g->gws + g->mg_tail;
     return b == 0 ? base : base + mg_scr_a(g->mg_geom);
 }
 // Rows of the transfer from grid l to l + 1 along `axis` (face: for faces
@@ -1379,7 +1385,9 @@ double* mg_tab(pt_grid* g, int l, int axis, int face) {
     for (int a = 0; a < axis; ++a) p += 2 * mg_tab_rows(g->mg_geom[l + 1], a) * MG_TAB;
     return p + (face ? mg_tab_rows(g->mg_geom[l + 1], axis) * MG_TAB : 0);
 }
-double* kry_base(pt_grid* g) { return g->gws + mg_core_doubles(g->mg_geom, g->mg_levels); }
+double* kry_base(pt_grid* g) {
+    return mg_scr(g, 1) + mg_scr_b(g->mg_geom) + mg_tab_doubles(g->mg_geom, g->mg_levels);
+}
 double* kry_x(pt_grid* g, int q) { return kry_base(g) + (int64_t)q * mg_stride(g->mg_geom[0]); }
 double* kry_p(pt_grid* g, int s, int q) { return kry_base(g) + (5 + 5 * (int64_t)s + q) * mg_stride(g->mg_geom[0]); }
 // v = 0: residual of the cycle's result; 1 + s: A p_s.
@@ -1394,9 +1402,7 @@ double* kry_part(pt_grid* g) {
     return kry_base(g) + 5 * (1 + m) * mg_stride(f) + (1 + m) * mg_res_doubles(f);
 }
 double* mg_box(pt_grid* g, int l, int b) {
-    double* base = g->gws + mg_res_doubles(g->mg_geom[0]) + mg_part_doubles(g->mg_geom, g->mg_levels);
-    for (int k = 1; k < l; ++k) base += MG_NB * mg_stride(g->mg_geom[k]) + mg_res_doubles(g->mg_geom[k]);
-    return base + (int64_t)b * mg_stride(g->mg_geom[l]);
+    return g->gws + g->mg_off[l] + (int64_t)b * mg_stride(g->mg_geom[l]);
 }
 
 // Sweep constants of grid l: the smoother's (or, for the coarsest grid, the
@@ -1454,7 +1460,7 @@ SweepPtrs<double> mg_ptrs(pt_grid* g, int l) {
     p.pto = mg_box(g, l, MG_PTO); p.pfo = mg_box(g, l, MG_PFO);
     p.kc = mg_box(g, l, MG_KC); p.eta = mg_box(g, l, MG_ETA); p.mus = mg_box(g, l, MG_MUS);
     p.partials = mg_partials(g);
-    p.domain = mg_partials(g) + mg_part_blocks(g->mg_geom, g->mg_levels) * NNORM + NNORM;
+    p.domain = mg_partials(g) + g->mg_parts * NNORM + NNORM;
     if (l < g->mg_levels - 1) {
         p.res_fx = mg_res(g, l, 0); p.res_fy = mg_res(g, l, 1); p.res_fz = mg_res(g, l, 2);
         p.res_rpt = mg_res(g, l, 3); p.res_rpf = mg_res(g, l, 4);
@@ -1473,7 +1479,7 @@ pt_status mg_smooth(pt_grid* g, int l, int n) {
     c.undamped = coarsest ? 0 : 1;
     for (int k = 0; k < n; ++k) {
         const SweepPtrs<double> p = mg_ptrs(g, l);
-        hipError_t e = launch_iteration(g->mg_geom[l], c, p, MD_LINEAR, 0, g->stream);
+        hipError_t e = launch_iteration(g->mg_geom[l], g->mg_tiling[l], c, p, MD_LINEAR, 0, g->stream);
         if (e != hipSuccess) return hip_fail(g, e, "multigrid sweep");
         if (l == 0) {
             for (int f = 0; f < PT_NPING; ++f)
@@ -1490,9 +1496,9 @@ pt_status mg_smooth(pt_grid* g, int l, int n) {
 pt_status mg_residual(pt_grid* g, int l) {
     const SweepPtrs<double> p = mg_ptrs(g, l);
     const Coef c = l == 0 ? g->coef : mg_coef(g, l, false);
-    hipError_t e = launch_iteration(g->mg_geom[l], c, p, MD_RESID, 1, g->stream);
+    hipError_t e = launch_iteration(g->mg_geom[l], g->mg_tiling[l], c, p, MD_RESID, 1, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "multigrid residual");
-    return l == 0 ? reduce_norms(g) : PT_OK;
+    return l == 0 ? reduce_norms(g, g->mg_tiling[0].resid) : PT_OK;
 }
 
 // Coarse-grid correction of grid l (its residual is in its FP32 boxes).
@@ -1656,10 +1662,10 @@ pt_status solve_mg_krylov(pt_grid* g, double rtol, int64_t max_cycles, int64_t* 
             SweepPtrs<double> p = mg_ptrs(g, 0);
             p.res_fx = kry_vec(g, 0, 0); p.res_fy = kry_vec(g, 0, 1); p.res_fz = kry_vec(g, 0, 2);
             p.res_rpt = kry_vec(g, 0, 3); p.res_rpf = kry_vec(g, 0, 4);
-            e = launch_iteration(f, g->coef, p, MD_RESID, 1, g->stream);
+            e = launch_iteration(f, g->mg_tiling[0], g->coef, p, MD_RESID, 1, g->stream);
             if (e != hipSuccess) return hip_fail(g, e, "multigrid residual");
         }
-        st = reduce_norms(g);
+        st = reduce_norms(g, g->mg_tiling[0].resid);
         double ry = INFINITY;
         if (st == PT_OK) st = mg_rho(g, &ry);
         if (st != PT_OK) break;
@@ -1777,6 +1783,14 @@ pt_status pt_bind_mg_workspace(pt_grid* g, const pt_mg_params* mg, void* dev_ptr
         return fail(g, PT_EINVAL, "multigrid workspace missing, unaligned or too small");
     g->mgp = *mg;
     g->mg_levels = mg_plan(g, *mg, g->mg_geom);
+    for (int l = 0; l < g->mg_levels; ++l) g->mg_tiling[l] = make_tiling(g->mg_geom[l]);
+    g->mg_parts = 0;
+    for (int l = 1; l < g->mg_levels; ++l) g->mg_parts = std::max(g->mg_parts, g->mg_tiling[l].resid);
+    g->mg_tail = mg_res_doubles(g->mg_geom[0]) + mg_part_doubles(g->mg_parts);
+    for (int l = 1; l < g->mg_levels; ++l) {
+        g->mg_off[l] = g->mg_tail;
+        g->mg_tail += MG_NB * mg_stride(g->mg_geom[l]) + (l < g->mg_levels - 1 ? mg_res_doubles(g->mg_geom[l]) : 0);
+    }
     g->gws = static_cast<double*>(dev_ptr);
     g->gws_bytes = bytes;
     for (int l = 0; l < PT_MG_MAX_LEVELS; ++l) g->mg_cur[l] = 0;

@@ -15,7 +15,7 @@
 //           the same iteration applied to x + d, with the FP64 residual of x as
 //           right-hand side (no old values, no buoyancy, no history term).
 //
-// Work decomposition.  A BX x BY block owns a column of (BX-2) x (BY-2) cells
+// Work decomposition.  A W x H block owns a column of (W-2) x (H-2) cells
 // plus a one-cell halo ring and marches upward through a chunk of g.kz planes.
 // Per plane the block
 //   1. stages the plane's velocities, fluid pressure, permeability, solid
@@ -41,11 +41,12 @@
 //   - two steps per loop round on alternating register sets, so that no loaded
 //     value is copied before it is needed;
 //   - field pointers come from the argument segment at each step, constants
-//     combined on the host, divisions without operand rescaling: 391 vector
+//     combined on the host, divisions without operand rescaling: 397 vector
 //     instructions per plane step of the linear sweep instead of 640.
 // Measured at 511^3 (before -> after): thesis sweep 6.17 -> 5.59 ms, with
 // norms 8.75 -> 6.73, linear 5.68 -> 5.00, residual 6.47 -> 4.40, FP32
-// correction 2.67 -> 2.52; at 32^3 thesis 27.1 -> 22.3 us.
+// correction 2.67 -> 2.52; at 32^3 thesis 27.1 -> 22.3 us.  Small grids gain
+// more from their tiles (sweep_shape, pt_internal.h): 32^3 thesis 22.3 -> 7.7.
 //
 // Damped velocity update of the FP64 sweeps (eq (19) with the script's
 // damping): R' = f/rho_i + d R, V' = V + dtau_V R'.  Between checks the
@@ -58,6 +59,11 @@
 // when the next refresh comes.  The FP32 correction sweeps do the same with
 // the damped residual of the correction.
 #include "pt_internal.h"
+
+// Multiply-adds are fused where an expression of the source has one, not
+// where the optimiser finds one: every variant and tile of the sweep rounds
+// alike, so results do not depend on the tiling.
+#pragma clang fp contract(on)
 
 namespace ptk {
 
@@ -208,14 +214,10 @@ __device__ __forceinline__ T damped_update(const C& c, T v_c, T q, T f, T damp, 
     return v;
 }
 
-// Waves per SIMD a block of n threads is compiled for: what it has itself,
-// but three for small blocks, of which several share a compute unit.
-constexpr int sweep_waves(int n) { return n > 768 ? 4 : (n > 448 && n <= 512) ? 2 : 3; }
-
 // RM: where the damping memory is; RW: store the damped residual R'.  W x H:
 // the block's threads.  BGS: the background shear of eq (32) is on.
 template <typename T, int MODE, bool NORMS, int RM, bool RW, int W, int H, bool BGS>
-__global__ __launch_bounds__(W * H, sweep_waves(W * H)) void k_sweep(SweepArgs<T> args) {
+__global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8)) void k_sweep(SweepArgs<T> args) {
     static_assert(W * H <= 1024, "a block holds at most 1024 threads");
     constexpr bool UPD_LP = (MODE == MD_THESIS);
     constexpr bool RESID = (MODE == MD_RESID);
@@ -703,91 +705,106 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H)) void k_sweep(SweepArgs<T
     }
 }
 
-__global__ __launch_bounds__(256) void k_reduce_max(const double* __restrict__ part, int64_t nb,
-                                                    double* __restrict__ out) {
-    __shared__ double red[4][NNORM];
-    double m[NNORM];
-#pragma unroll
-    for (int q = 0; q < NNORM; ++q) m[q] = 0.0;
-    for (int64_t b = threadIdx.x; b < nb; b += blockDim.x) {
-#pragma unroll
-        for (int q = 0; q < NNORM; ++q) m[q] = nanmax(m[q], part[b * NNORM + q]);
-    }
-#pragma unroll
-    for (int q = 0; q < NNORM; ++q) {
-        double v = m[q];
-        for (int off = 32; off >= 1; off >>= 1) v = nanmax(v, __shfl_xor(v, off, 64));
-        m[q] = v;
-    }
+// The eight maxima over the blocks' partial ones, one block: thread t takes
+// norm t mod 8 of every 128th block, so that a wave reads whole lines.
+constexpr int RT = 1024;
+__global__ __launch_bounds__(RT) void k_reduce_max(const double* __restrict__ part, int64_t nb,
+                                                   double* __restrict__ out) {
+    __shared__ double red[RT / 64][NNORM];
+    double m = 0.0;
+    const int64_t n = nb * NNORM;
+    for (int64_t t = threadIdx.x; t < n; t += RT) m = nanmax(m, part[t]);
+    for (int off = 32; off >= NNORM; off >>= 1) m = nanmax(m, __shfl_xor(m, off, 64));
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) {
-#pragma unroll
-        for (int q = 0; q < NNORM; ++q) red[wave][q] = m[q];
-    }
+    if (lane < NNORM) red[wave][lane] = m;
     __syncthreads();
     if (threadIdx.x < NNORM) {
         double v = 0.0;
-        for (int wv = 0; wv < 4; ++wv) v = nanmax(v, red[wv][threadIdx.x]);
+        for (int w = 0; w < RT / 64; ++w) v = nanmax(v, red[w][threadIdx.x]);
         out[threadIdx.x] = v;
     }
 }
 
 }  // namespace
 
-template <typename T, int MODE, bool NORMS, int RM, bool RW, int H>
-hipError_t launch_sweep(const Geom& g, const Coef& c, const SweepPtrs<T>& p, hipStream_t s) {
+template <typename T, int MODE, bool NORMS, int RM, bool RW, int W, int H>
+hipError_t launch_tile(const Geom& g, const TileShape& t, const Coef& c, const SweepPtrs<T>& p, hipStream_t s) {
     if (g.P > (int64_t)(0x7fffffff / (H * sizeof(T)))) return hipErrorInvalidValue;   // a tile's rows: below 2 GiB
-    const SweepArgs<T> a{sweep_geom(g, BX, H), CT<T>(c), p};
-    const dim3 grid((unsigned)iter_grid_blocks(g, BX, H)), block(BX * H);
+    SweepArgs<T> a{g, CT<T>(c), p};
+    a.g.kz = t.kz;
+    const dim3 grid((unsigned)sweep_blocks(g, t)), block(W * H);
     // the correction system has no background term (it is in its right-hand side)
     if (MODE != MD_CORR && c.gbg_half != 0.0)
-        hipLaunchKernelGGL((k_sweep<T, MODE, NORMS, RM, RW, BX, H, MODE != MD_CORR>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_sweep<T, MODE, NORMS, RM, RW, W, H, MODE != MD_CORR>), grid, block, 0, s, a);
     else
-        hipLaunchKernelGGL((k_sweep<T, MODE, NORMS, RM, RW, BX, H, false>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_sweep<T, MODE, NORMS, RM, RW, W, H, false>), grid, block, 0, s, a);
     return hipGetLastError();
+}
+
+// One sweep variant on the tile chosen for it (the tiles of sweep_shapes).
+template <typename T, int MODE, bool NORMS, int RM, bool RW>
+hipError_t launch_sweep(const Geom& g, const Tiling& tl, const Coef& c, const SweepPtrs<T>& p, hipStream_t s) {
+    constexpr SweepKind kind = sizeof(T) == 8 ? (NORMS ? SK_NORM64 : SK_F64) : (NORMS ? SK_NORM32 : SK_F32);
+    const TileShape& t = tl.shape[kind];
+    const int wh = t.w * 100 + t.h;
+    if constexpr (NORMS) {
+        if (wh == 6607) return launch_tile<T, MODE, NORMS, RM, RW, 66, 7>(g, t, c, p, s);
+    } else {
+        if constexpr (sizeof(T) == 4)
+            if (wh == 6614) return launch_tile<T, MODE, NORMS, RM, RW, 66, 14>(g, t, c, p, s);
+        if (wh == 6610) return launch_tile<T, MODE, NORMS, RM, RW, 66, 10>(g, t, c, p, s);
+        if (wh == 6606) return launch_tile<T, MODE, NORMS, RM, RW, 66, 6>(g, t, c, p, s);
+    }
+    if (wh == 3414) return launch_tile<T, MODE, NORMS, RM, RW, 34, 14>(g, t, c, p, s);
+    if (wh == 3406) return launch_tile<T, MODE, NORMS, RM, RW, 34, 6>(g, t, c, p, s);
+    if constexpr (NORMS || sizeof(T) == 8)
+        if (wh == 3404) return launch_tile<T, MODE, NORMS, RM, RW, 34, 4>(g, t, c, p, s);
+    return hipErrorInvalidValue;
 }
 
 // The sweeps of one mode, by where the damping memory is and whether R' is
 // stored (the combinations the drivers use: R' is always stored with norms).
-template <typename T, int MODE, int H>
-hipError_t launch_mode(const Geom& g, const Coef& c, const SweepPtrs<T>& p, int norms, hipStream_t s) {
+template <typename T, int MODE>
+hipError_t launch_mode(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<T>& p, int norms,
+                       hipStream_t s) {
     if (norms) {
-        if (c.rform) return launch_sweep<T, MODE, true, RM_STORED, true, BY_NORMS>(g, c, p, s);
-        return launch_sweep<T, MODE, true, RM_VPREV, true, BY_NORMS>(g, c, p, s);
-    } else if (c.rwrite) {
-        if (c.rform) return launch_sweep<T, MODE, false, RM_STORED, true, H>(g, c, p, s);
-        return launch_sweep<T, MODE, false, RM_VPREV, true, H>(g, c, p, s);
-    } else {
-        if (c.rform) return launch_sweep<T, MODE, false, RM_STORED, false, H>(g, c, p, s);
-        return launch_sweep<T, MODE, false, RM_VPREV, false, H>(g, c, p, s);
+        if (c.rform) return launch_sweep<T, MODE, true, RM_STORED, true>(g, t, c, p, s);
+        return launch_sweep<T, MODE, true, RM_VPREV, true>(g, t, c, p, s);
     }
+    if (c.rwrite) {
+        if (c.rform) return launch_sweep<T, MODE, false, RM_STORED, true>(g, t, c, p, s);
+        if constexpr (MODE == MD_CORR) return launch_sweep<T, MODE, false, RM_VPREV, true>(g, t, c, p, s);
+        return hipErrorInvalidValue;
+    }
+    if (c.rform) return launch_sweep<T, MODE, false, RM_STORED, false>(g, t, c, p, s);
+    return launch_sweep<T, MODE, false, RM_VPREV, false>(g, t, c, p, s);
 }
 
-hipError_t launch_iteration(const Geom& g, const Coef& c, const SweepPtrs<double>& p, int mode, int norms,
-                            hipStream_t s) {
+hipError_t launch_iteration(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<double>& p, int mode,
+                            int norms, hipStream_t s) {
     switch (mode) {
-        case MD_THESIS: return launch_mode<double, MD_THESIS, BY>(g, c, p, norms, s);
+        case MD_THESIS: return launch_mode<double, MD_THESIS>(g, t, c, p, norms, s);
         case MD_LINEAR:
-            if (c.undamped) return launch_sweep<double, MD_LINEAR, false, RM_NONE, false, BY_LINEAR>(g, c, p, s);
-            return launch_mode<double, MD_LINEAR, BY_LINEAR>(g, c, p, norms, s);
-        case MD_RESID: return launch_sweep<double, MD_RESID, false, RM_NONE, false, BY_NORMS>(g, c, p, s);
+            if (c.undamped) return launch_sweep<double, MD_LINEAR, false, RM_NONE, false>(g, t, c, p, s);
+            return launch_mode<double, MD_LINEAR>(g, t, c, p, norms, s);
+        case MD_RESID: return launch_sweep<double, MD_RESID, false, RM_NONE, false>(g, t, c, p, s);
     }
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_correction(const Geom& g, const Coef& c, const SweepPtrs<float>& p, int norms, hipStream_t s) {
-    if (corr32_short(g)) return launch_mode<float, MD_CORR, BY_CORR32_SHORT>(g, c, p, norms, s);
-    return launch_mode<float, MD_CORR, BY_CORR32>(g, c, p, norms, s);
+hipError_t launch_correction(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<float>& p, int norms,
+                             hipStream_t s) {
+    return launch_mode<float, MD_CORR>(g, t, c, p, norms, s);
 }
 
-hipError_t launch_correction64(const Geom& g, const Coef& c, const SweepPtrs<double>& p, int norms,
+hipError_t launch_correction64(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<double>& p, int norms,
                                hipStream_t s) {
-    if (norms) return launch_sweep<double, MD_CORR, true, RM_STORED, true, BY_NORMS>(g, c, p, s);
-    return launch_sweep<double, MD_CORR, false, RM_STORED, true, BY_LINEAR>(g, c, p, s);
+    if (norms) return launch_sweep<double, MD_CORR, true, RM_STORED, true>(g, t, c, p, s);
+    return launch_sweep<double, MD_CORR, false, RM_STORED, true>(g, t, c, p, s);
 }
 
 hipError_t launch_reduce_max(const double* partials, int64_t nblocks, double* out8, hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce_max, dim3(1), dim3(256), 0, s, partials, nblocks, out8);
+    hipLaunchKernelGGL(k_reduce_max, dim3(1), dim3(RT), 0, s, partials, nblocks, out8);
     return hipGetLastError();
 }
 

@@ -72,25 +72,18 @@ struct SweepPtrs {
 
 constexpr int NNORM = 8;
 
-// Tile of the fused sweep: a BX x BY thread block covers a (BX-2) x (BY-2)
-// output tile plus one halo column/row on every side and marches in z.
-// BX = 66 makes the output tile 64 columns wide: its rows start on 512-byte
+// Tiles of the z-marching kernels: a W x H thread block covers a (W-2) x
+// (H-2) output tile plus one halo column/row on every side and marches in z.
+// W = 66 makes the output tile 64 columns wide: its rows start on 512-byte
 // boundaries of the padded rows (whole cache lines written) and n = 2^k - 1
 // grids fill their last tile; each row's 64 interior columns are one wave,
-// the side halo columns of all rows one more (partial) wave.  The variants
-// that also reduce norms need up to 196 registers, so at most 8 waves: 7
-// rows.  Every cell's arithmetic is the same in every tiling.  Heights: the
-// tallest tile whose
-// waves fit the variant's registers is not always the fastest, since the
-// number of tiles decides how full the last round of blocks is; measured
-// at 511^3 (8-row tiles: 86 tile rows, 10-row tiles: 64).
+// the side halo columns of all rows one more (partial) wave.  Every cell's
+// arithmetic is the same in every tiling.  The sweeps choose theirs per
+// grid (sweep_shape).
 constexpr int BX = 66;
-constexpr int BY = 10;         // thesis sweep
-constexpr int BY_LINEAR = 10;  // linear and FP64 correction sweeps
+constexpr int BY = 10;         // FP64 sweeps on large grids
 constexpr int BY_CORR32 = 14;  // FP32 correction sweep (large grids)
 constexpr int BY_CORR32_SHORT = 10;   // FP32 correction sweep where its tiling costs less
-constexpr int BX_NORMS = 66;     // sweeps with norms (up to 196 VGPRs: 8 waves)
-constexpr int BY_NORMS = 7;
 constexpr int KZ_MAX = 256;
 
 constexpr int KZ_MIN = 4;
@@ -178,15 +171,134 @@ __device__ __forceinline__ void tile_thread(int& tx, int& ty) {
     }
 }
 
-// Blocks that write per-block norm maxima (size of the partials area).
-inline int64_t norm_blocks(const Geom& g) { return iter_grid_blocks(g, BX_NORMS, BY_NORMS); }
+// ---- tile of a sweep launch ----------------------------------------------------
+// Blocks of w x h threads (w - 2 by h - 2 output columns and rows) over
+// chunks of kz planes.
+struct TileShape {
+    int w, h, kz;
+};
+
+// Waves per SIMD that a sweep block of n threads is compiled for: what it has
+// itself, but three for small blocks, of which several share a compute unit.
+// (The FP64 sweeps with norms need more registers: two.)
+constexpr int sweep_waves(int n, bool norms = false) {
+    return n > 768 ? 4 : (norms || (n > 448 && n <= 512)) ? 2 : 3;
+}
+
+// Sweep variants by what their blocks take of a compute unit.
+enum SweepKind { SK_F64, SK_F32, SK_NORM64, SK_NORM32 };
+
+// A launch's time, for choosing its tiles.  A compute unit runs its share of
+// the blocks, as many at a time as its registers hold; a plane step of n
+// resident waves takes max(step + wave n, full n): at first latency, then
+// the vector units or, for grids whose fields outgrow the last-level cache,
+// memory; a block's march takes its chunk's planes and `lead` more.  The
+// constants (in us) fit 900 measured launches (12 tiles, 2 to 12 chunk
+// lengths, grids of 8^3 to 255^3, thesis, linear and FP32 correction
+// sweeps) within 10 %; the tile it picks is within 1.5 % of the fastest of
+// all those measured in FP64 and 2.2 % in FP32 (geometric mean), against
+// 40 % for one tile of 66 x 10 threads: linear sweep 20.6 -> 6.7 us at 16^3,
+// 20.7 -> 7.5 at 32^3, 23.5 -> 16.7 at 64^3, 68.6 -> 40.1 at 95^3,
+// 121 -> 97 at 173 x 131 x 97.
+struct SweepCost {
+    double step, wave, full_cached, full_memory, lead;
+    double cell_bytes;   // streamed per cell
+};
+inline SweepCost sweep_cost(SweepKind k) {
+    if (k == SK_F32 || k == SK_NORM32) return {0.65, 0.105, 0.126, 0.20, 1.4, 84.0};
+    return {1.1, 0.2, 0.28, 0.38, 1.8, 192.0};
+}
+constexpr double LAST_LEVEL_CACHE = 256.0e6;   // bytes
+
+// Tiles each variant is built for, larger ones first.
+constexpr int SWEEP_SHAPES = 5;
+inline const TileShape* sweep_shapes(SweepKind k, int& n) {
+    static constexpr TileShape f64[SWEEP_SHAPES] = {{66, 10, 0}, {66, 6, 0}, {34, 14, 0}, {34, 6, 0}, {34, 4, 0}};
+    static constexpr TileShape f32[SWEEP_SHAPES] = {{66, 14, 0}, {66, 10, 0}, {66, 6, 0}, {34, 14, 0}, {34, 6, 0}};
+    static constexpr TileShape norms[4] = {{66, 7, 0}, {34, 14, 0}, {34, 6, 0}, {34, 4, 0}};
+    if (k == SK_F64) { n = 5; return f64; }
+    if (k == SK_F32) { n = 5; return f32; }
+    n = 4;
+    return norms;
+}
+
+// Blocks of a launch with a tile shape.
+inline int64_t sweep_blocks(const Geom& g, const TileShape& t) {
+    return tiles_xy(g, t.w, t.h) * ((g.nz + t.kz - 1) / t.kz);
+}
+
+// The tile and chunk of a sweep: the cheapest by the model above, over the
+// variant's tiles and, for each, the chunks that fill 1 to 16 blocks per
+// compute unit (no more than 4096 blocks beyond the first).
+inline TileShape sweep_shape(const Geom& g, SweepKind kind) {
+    const SweepCost sc = sweep_cost(kind);
+    const int cus = g.cus > 0 ? g.cus : DEFAULT_CUS;
+    const bool cached = (double)g.nx * g.ny * g.nz * sc.cell_bytes <= LAST_LEVEL_CACHE;
+    const double full = cached ? sc.full_cached : sc.full_memory;
+    int n = 0;
+    const TileShape* shapes = sweep_shapes(kind, n);
+    const bool shorter = kind == SK_F32 && corr32_short(g);
+    TileShape best{};
+    double best_cost = -1.0;
+    for (int q = 0; q < n; ++q) {
+        TileShape t = shapes[q];
+        if (kind == SK_F32 && t.w == BX) {
+            if (g.tall32 && t.h != BY_CORR32) continue;
+            if (t.h == (shorter ? BY_CORR32 : BY_CORR32_SHORT)) continue;
+        } else if (kind == SK_F32 && g.tall32) {
+            continue;
+        }
+        const int64_t tiles = tiles_xy(g, t.w, t.h);
+        const int nw = (t.w * t.h + 63) / 64;
+        const int held = kind == SK_F32 ? 24 : kind == SK_NORM32 ? 16 : 4 * sweep_waves(t.w * t.h, kind == SK_NORM64);
+        const int res = std::max(1, held / nw);
+        auto step = [&](int64_t blocks) { return std::max(sc.step + sc.wave * blocks * nw, full * blocks * nw); };
+        int last = 0;
+        for (int m = 1; m <= 16; ++m) {
+            const int64_t chunks = std::min<int64_t>(std::max<int64_t>(m * (int64_t)cus / tiles, 1), g.nz);
+            t.kz = std::min((int)((g.nz + chunks - 1) / chunks), KZ_MAX);
+            if (t.kz != last) {
+                last = t.kz;
+                const int64_t blocks = tiles * ((g.nz + t.kz - 1) / t.kz);
+                if (m > 1 && blocks > 4096) break;
+                const int64_t per_cu = (blocks + cus - 1) / cus;
+                const int64_t rounds = per_cu / res, rest = per_cu % res;
+                const double cost = (t.kz + sc.lead) * (rounds * step(res) + (rest ? step(rest) : 0.0));
+                if (best_cost < 0.0 || cost < best_cost * (1.0 - 1e-9)) {
+                    best = t;
+                    best_cost = cost;
+                }
+            }
+            if (t.kz == 1) break;
+        }
+    }
+    return best;
+}
+
+// The tiles of a grid's sweeps, chosen once per grid, and the blocks that
+// write per-block norm maxima: of the sweeps with norms and of the residual
+// sweep (which runs the plain sweeps' tiles).
+struct Tiling {
+    TileShape shape[4];
+    int64_t norms64 = 0, norms32 = 0, resid = 0;
+    int64_t most = 0;   // of these three (size of the partials area)
+};
+inline Tiling make_tiling(const Geom& g) {
+    Tiling t;
+    for (int k = 0; k < 4; ++k) t.shape[k] = sweep_shape(g, (SweepKind)k);
+    t.norms64 = sweep_blocks(g, t.shape[SK_NORM64]);
+    t.norms32 = sweep_blocks(g, t.shape[SK_NORM32]);
+    t.resid = sweep_blocks(g, t.shape[SK_F64]);
+    t.most = std::max(t.resid, std::max(t.norms64, t.norms32));
+    return t;
+}
 
 // Launchers (defined in the .hip files).
-hipError_t launch_iteration(const Geom& g, const Coef& c, const SweepPtrs<double>& p, int mode,
+hipError_t launch_iteration(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<double>& p, int mode,
                             int norms, hipStream_t s);
-hipError_t launch_correction(const Geom& g, const Coef& c, const SweepPtrs<float>& p, int norms,
+hipError_t launch_correction(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<float>& p, int norms,
                              hipStream_t s);
-hipError_t launch_correction64(const Geom& g, const Coef& c, const SweepPtrs<double>& p, int norms,
+hipError_t launch_correction64(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<double>& p, int norms,
                                hipStream_t s);
 hipError_t launch_reduce_max(const double* partials, int64_t nblocks, double* out8, hipStream_t s);
 
