@@ -10,6 +10,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libptporo.so")
+# One compiler run each; iter_kernel.hip in three parts (its many sweep kernels).
 SOURCES = ["api.hip", "iter_kernel.hip", "refresh_kernel.hip", "aux_kernels.hip", "adjoint_kernels.hip", "waves.hip",
            "mg_kernels.hip", "krylov_kernels.hip"]
 
@@ -27,16 +28,19 @@ def build(verbose: bool = False, extra=None) -> str:
     inc = ["-I", os.path.join(ROOT, "include"), "-I", CSRC]
     with tempfile.TemporaryDirectory() as objs:
         # one compiler per source, side by side
-        def compile_one(src):
-            obj = os.path.join(objs, src + ".o")
-            cmd = [hipcc, *FLAGS, *(extra or []), *inc, "-c", os.path.join(CSRC, src), "-o", obj]
+        def compile_one(job):
+            src, part = job
+            obj = os.path.join(objs, f"{src}.{part}.o")
+            define = [] if part is None else [f"-DSWEEP_PART={part}"]
+            cmd = [hipcc, *FLAGS, *(extra or []), *define, *inc, "-c", os.path.join(CSRC, src), "-o", obj]
             if verbose:
                 print(" ".join(cmd))
             subprocess.run(cmd, check=True)
             return obj
 
-        with ThreadPoolExecutor(max_workers=min(len(SOURCES), os.cpu_count() or 1)) as pool:
-            built = list(pool.map(compile_one, SOURCES))
+        jobs = [(s, p) for s in SOURCES for p in (range(3) if s == "iter_kernel.hip" else (None,))]
+        with ThreadPoolExecutor(max_workers=min(len(jobs), os.cpu_count() or 1)) as pool:
+            built = list(pool.map(compile_one, jobs))
         link = [hipcc, "-shared", "--offload-arch=gfx950", *built, "-o", tmp]
         if verbose:
             print(" ".join(link))

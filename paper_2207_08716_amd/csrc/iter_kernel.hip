@@ -58,7 +58,16 @@
 // check interval store R' = (V' - V)/dtau_V (c.rwrite), so that it is there
 // when the next refresh comes.  The FP32 correction sweeps do the same with
 // the damped residual of the correction.
+#include "plane.h"
 #include "pt_internal.h"
+
+// The sweeps are many kernels: the build compiles this source three times,
+// side by side, each time one part of the launchers at the end.
+#ifdef SWEEP_PART
+#define SWEEP_HAS(part) (SWEEP_PART == (part))
+#else
+#define SWEEP_HAS(part) 1
+#endif
 
 // Multiply-adds are fused where an expression of the source has one, not
 // where the optimiser finds one: every variant and tile of the sweep rounds
@@ -75,85 +84,6 @@ namespace {
 // what a thread at the rim of the block reads there is never used.
 enum LdsPlane { L_VX, L_VY, L_VZ1, L_PF, L_KC, L_MU, L_MU1, L_PTN, L_TXX, L_TYY, L_TXY, L_TXZ, L_TYZ = L_TXZ + 2,
                 L_CORE = L_TYZ + 2 };   // then, where used: the solid fraction of two planes, tau_zz, the norms' W plane
-
-template <typename T>
-__device__ __forceinline__ T nanmax(T m, T v) {
-    // maximum that lets a NaN through (divergence must not be hidden)
-    return (v > m || v != v) ? v : m;
-}
-
-// Larger of two values as one instruction (fmax would first quiet both
-// operands, one more instruction each, since it cannot see where they come
-// from; the results are the same).
-__device__ __forceinline__ double max1(double a, double b) {
-    double r;
-    asm("v_max_f64 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-__device__ __forceinline__ float max1(float a, float b) {
-    float r;
-    asm("v_max_f32 %0, %1, %2" : "=v"(r) : "v"(a), "v"(b));
-    return r;
-}
-
-// a / b by Newton's iteration on the reciprocal and a corrected quotient,
-// the compiler's division without its rescaling of the operands (which only
-// quotients and divisors near the ends of the exponent range need);
-// infinities, zeros and NaN come out as from the division.
-__device__ __forceinline__ double quot(double a, double b) {
-    double y = __builtin_amdgcn_rcp(b);
-    y = __builtin_fma(__builtin_fma(-b, y, 1.0), y, y);
-    y = __builtin_fma(__builtin_fma(-b, y, 1.0), y, y);
-    const double q = a * y;
-    return __builtin_amdgcn_div_fixup(__builtin_fma(__builtin_fma(-b, q, a), y, q), b, a);
-}
-__device__ __forceinline__ float quot(float a, float b) {
-    float y = __builtin_amdgcn_rcpf(b);
-    y = __builtin_fmaf(__builtin_fmaf(-b, y, 1.0f), y, y);
-    const float q = a * y;
-    return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-b, q, a), y, q), b, a);
-}
-
-// A copy in a register of its own: the queue moves out of the registers a
-// plane was loaded into, which then take the loads after next.  (Left to
-// itself the compiler loads into other registers and copies at the end of a
-// round, which waits for loads just issued.)
-__device__ __forceinline__ double fresh(double v) {
-    double r;
-    asm("v_mov_b64 %0, %1" : "=v"(r) : "v"(v));
-    return r;
-}
-__device__ __forceinline__ float fresh(float v) {
-    float r;
-    asm("v_mov_b32 %0, %1" : "=v"(r) : "v"(v));
-    return r;
-}
-
-// Buffer access to a tile's rows in one plane of a field: their address and
-// size are wave-uniform (scalar registers), a lane brings its byte offset in
-// them.  A lane with offset OFF_NONE, or any lane where the size is
-// given as 0, loads 0 and stores nothing, so that neither the rim of a field
-// needs a branch or a select: every step of a wave issues the same number of
-// loads and stores, and the wait for a plane's loads need not cover the
-// stores and loads issued after them.
-using u32 = unsigned int;
-constexpr u32 OFF_NONE = 0x80000000u;   // beyond any tile (the rows of a tile hold less than 2 GiB)
-constexpr int RSRC_FLAGS = 0x00020000;  // raw 32-bit data
-constexpr int NONTEMPORAL = 2;
-
-template <int AUX = 0, typename T>
-__device__ __forceinline__ T ldp(const T* rows, u32 bytes, u32 off) {
-    const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(rows), 0, (int)bytes, RSRC_FLAGS);
-    if constexpr (sizeof(T) == 8) return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, AUX));
-    else return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(r, (int)off, 0, AUX));
-}
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-template <typename T>
-__device__ __forceinline__ void stp(T* rows, u32 bytes, u32 off, T v) {
-    const auto r = __builtin_amdgcn_make_buffer_rsrc(rows, 0, (int)bytes, RSRC_FLAGS);
-    if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, v), r, (int)off, 0, 0);
-    else __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(u32, v), r, (int)off, 0, 0);
-}
 
 // Constants in the working precision of the sweep, combined on the host (the
 // scalar unit has no floating point: a product formed in the kernel would
@@ -215,8 +145,9 @@ __device__ __forceinline__ T damped_update(const C& c, T v_c, T q, T f, T damp, 
 }
 
 // RM: where the damping memory is; RW: store the damped residual R'.  W x H:
-// the block's threads.  BGS: the background shear of eq (32) is on.
-template <typename T, int MODE, bool NORMS, int RM, bool RW, int W, int H, bool BGS>
+// the block's threads.  BGS: the background shear of eq (32) is on.  STREAM:
+// the fields outgrow the last-level cache.
+template <typename T, int MODE, bool NORMS, int RM, bool RW, int W, int H, bool BGS, bool STREAM>
 __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8)) void k_sweep(SweepArgs<T> args) {
     static_assert(W * H <= 1024, "a block holds at most 1024 threads");
     constexpr bool UPD_LP = (MODE == MD_THESIS);
@@ -322,12 +253,14 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
         cs.pfo = ldp(p->pfo + o, nb, o_q);
         cs.eta = ldp(p->eta + o, nb, o_q);
     };
-    // The tile-only fields are read exactly once per launch: in FP64 they are
-    // loaded non-temporally, which keeps them from displacing halo data in
-    // the caches.  The FP32 sweep keeps ordinary loads: its whole working set
-    // fits the last-level cache at 127^3, where non-temporal loads made the
-    // mixed solve 8 % slower.
-    constexpr int ONCE = sizeof(T) == 8 ? NONTEMPORAL : 0;
+    // Where the fields outgrow the last-level cache, what a launch reads once
+    // (the tile-only fields) and what it writes bypass the caches, which
+    // leaves them to the halo data that neighbouring tiles read again
+    // (measured, none -> loads and stores: 511^3 thesis 5.30 -> 4.92 ms,
+    // linear 4.96 -> 4.85, FP32 correction 2.52 -> 2.34; 255^3 661 -> 639,
+    // 635 -> 616, 302 -> 282 us); where they fit, the next launch finds them
+    // there (110^3 thesis 58.0 us without, 64.4 with).
+    constexpr int ONCE = STREAM ? NONTEMPORAL : 0;
     auto load_f = [&](KPtrs* p, int k, FSet& f) {
         const int64_t o = (int64_t)k * g.S + tile0;
         const u32 nb = (k >= kz0 && k < kz1) ? tile_bytes : 0u;
@@ -357,17 +290,17 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
             stp(p->res_rpt + o, nb, o_sc, float(s.pt));
             stp(p->res_rpf + o, nb, o_sc, float(s.pf));
         } else {
-            stp(p->vx_o + o, nb, o_sx, s.vx);
-            stp(p->vy_o + o, nb, o_sy, s.vy);
-            stp(p->vz_o + o, nbz, o_sc, s.vz);
+            stp<ONCE>(p->vx_o + o, nb, o_sx, s.vx);
+            stp<ONCE>(p->vy_o + o, nb, o_sy, s.vy);
+            stp<ONCE>(p->vz_o + o, nbz, o_sc, s.vz);
             if constexpr (RW) {
-                stp(p->rx_o + o, nb, o_sx, s.rx);
-                stp(p->ry_o + o, nb, o_sy, s.ry);
-                stp(p->rz_o + o, nbz, o_sc, s.rz);
+                stp<ONCE>(p->rx_o + o, nb, o_sx, s.rx);
+                stp<ONCE>(p->ry_o + o, nb, o_sy, s.ry);
+                stp<ONCE>(p->rz_o + o, nbz, o_sc, s.rz);
             }
-            stp(p->pt_o + o, nb, o_sc, s.pt);
-            stp(p->pf_o + o, nb, o_sc, s.pf);
-            if constexpr (UPD_LP) stp(p->lp_o + o, nb, o_sc, s.lp);
+            stp<ONCE>(p->pt_o + o, nb, o_sc, s.pt);
+            stp<ONCE>(p->pf_o + o, nb, o_sc, s.pf);
+            if constexpr (UPD_LP) stp<ONCE>(p->lp_o + o, nb, o_sc, s.lp);
         }
     };
     auto weight = [&](T s) -> T { return c.rhofg * (one - s) + c.rhosg * s; };
@@ -727,7 +660,9 @@ __global__ __launch_bounds__(RT) void k_reduce_max(const double* __restrict__ pa
 
 }  // namespace
 
-template <typename T, int MODE, bool NORMS, int RM, bool RW, int W, int H>
+namespace {
+
+template <typename T, int MODE, bool NORMS, int RM, bool RW, int W, int H, bool STREAM>
 hipError_t launch_tile(const Geom& g, const TileShape& t, const Coef& c, const SweepPtrs<T>& p, hipStream_t s) {
     if (g.P > (int64_t)(0x7fffffff / (H * sizeof(T)))) return hipErrorInvalidValue;   // a tile's rows: below 2 GiB
     SweepArgs<T> a{g, CT<T>(c), p};
@@ -735,9 +670,9 @@ hipError_t launch_tile(const Geom& g, const TileShape& t, const Coef& c, const S
     const dim3 grid((unsigned)sweep_blocks(g, t)), block(W * H);
     // the correction system has no background term (it is in its right-hand side)
     if (MODE != MD_CORR && c.gbg_half != 0.0)
-        hipLaunchKernelGGL((k_sweep<T, MODE, NORMS, RM, RW, W, H, MODE != MD_CORR>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_sweep<T, MODE, NORMS, RM, RW, W, H, MODE != MD_CORR, STREAM>), grid, block, 0, s, a);
     else
-        hipLaunchKernelGGL((k_sweep<T, MODE, NORMS, RM, RW, W, H, false>), grid, block, 0, s, a);
+        hipLaunchKernelGGL((k_sweep<T, MODE, NORMS, RM, RW, W, H, false, STREAM>), grid, block, 0, s, a);
     return hipGetLastError();
 }
 
@@ -747,18 +682,28 @@ hipError_t launch_sweep(const Geom& g, const Tiling& tl, const Coef& c, const Sw
     constexpr SweepKind kind = sizeof(T) == 8 ? (NORMS ? SK_NORM64 : SK_F64) : (NORMS ? SK_NORM32 : SK_F32);
     const TileShape& t = tl.shape[kind];
     const int wh = t.w * 100 + t.h;
+    // (the sweeps with norms and the residual sweep, whose results are read
+    // next, measured the same either way)
+    if constexpr (!NORMS && MODE != MD_RESID)
+        if (t.stream) {
+            if constexpr (sizeof(T) == 4)
+                if (wh == 6614) return launch_tile<T, MODE, NORMS, RM, RW, 66, 14, true>(g, t, c, p, s);
+            if (wh == 6610) return launch_tile<T, MODE, NORMS, RM, RW, 66, 10, true>(g, t, c, p, s);
+            if (wh == 3414) return launch_tile<T, MODE, NORMS, RM, RW, 34, 14, true>(g, t, c, p, s);
+            if (wh == 3406) return launch_tile<T, MODE, NORMS, RM, RW, 34, 6, true>(g, t, c, p, s);
+        }
     if constexpr (NORMS) {
-        if (wh == 6607) return launch_tile<T, MODE, NORMS, RM, RW, 66, 7>(g, t, c, p, s);
+        if (wh == 6607) return launch_tile<T, MODE, NORMS, RM, RW, 66, 7, false>(g, t, c, p, s);
     } else {
         if constexpr (sizeof(T) == 4)
-            if (wh == 6614) return launch_tile<T, MODE, NORMS, RM, RW, 66, 14>(g, t, c, p, s);
-        if (wh == 6610) return launch_tile<T, MODE, NORMS, RM, RW, 66, 10>(g, t, c, p, s);
-        if (wh == 6606) return launch_tile<T, MODE, NORMS, RM, RW, 66, 6>(g, t, c, p, s);
+            if (wh == 6614) return launch_tile<T, MODE, NORMS, RM, RW, 66, 14, false>(g, t, c, p, s);
+        if (wh == 6610) return launch_tile<T, MODE, NORMS, RM, RW, 66, 10, false>(g, t, c, p, s);
+        if (wh == 6606) return launch_tile<T, MODE, NORMS, RM, RW, 66, 6, false>(g, t, c, p, s);
     }
-    if (wh == 3414) return launch_tile<T, MODE, NORMS, RM, RW, 34, 14>(g, t, c, p, s);
-    if (wh == 3406) return launch_tile<T, MODE, NORMS, RM, RW, 34, 6>(g, t, c, p, s);
+    if (wh == 3414) return launch_tile<T, MODE, NORMS, RM, RW, 34, 14, false>(g, t, c, p, s);
+    if (wh == 3406) return launch_tile<T, MODE, NORMS, RM, RW, 34, 6, false>(g, t, c, p, s);
     if constexpr (NORMS || sizeof(T) == 8)
-        if (wh == 3404) return launch_tile<T, MODE, NORMS, RM, RW, 34, 4>(g, t, c, p, s);
+        if (wh == 3404) return launch_tile<T, MODE, NORMS, RM, RW, 34, 4, false>(g, t, c, p, s);
     return hipErrorInvalidValue;
 }
 
@@ -780,13 +725,40 @@ hipError_t launch_mode(const Geom& g, const Tiling& t, const Coef& c, const Swee
     return launch_sweep<T, MODE, false, RM_VPREV, false>(g, t, c, p, s);
 }
 
+}  // namespace
+
+// One PT iteration's sweep of the thesis schedule, and of a linear stage.
+hipError_t launch_thesis(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<double>& p, int norms,
+                         hipStream_t s);
+hipError_t launch_linear(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<double>& p, int norms,
+                         hipStream_t s);
+
+#if SWEEP_HAS(0)
+hipError_t launch_thesis(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<double>& p, int norms,
+                         hipStream_t s) {
+    return launch_mode<double, MD_THESIS>(g, t, c, p, norms, s);
+}
+
+hipError_t launch_reduce_max(const double* partials, int64_t nblocks, double* out8, hipStream_t s) {
+    hipLaunchKernelGGL(k_reduce_max, dim3(1), dim3(RT), 0, s, partials, nblocks, out8);
+    return hipGetLastError();
+}
+#endif
+
+#if SWEEP_HAS(1)
+hipError_t launch_linear(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<double>& p, int norms,
+                         hipStream_t s) {
+    if (c.undamped) return launch_sweep<double, MD_LINEAR, false, RM_NONE, false>(g, t, c, p, s);
+    return launch_mode<double, MD_LINEAR>(g, t, c, p, norms, s);
+}
+#endif
+
+#if SWEEP_HAS(2)
 hipError_t launch_iteration(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<double>& p, int mode,
                             int norms, hipStream_t s) {
     switch (mode) {
-        case MD_THESIS: return launch_mode<double, MD_THESIS>(g, t, c, p, norms, s);
-        case MD_LINEAR:
-            if (c.undamped) return launch_sweep<double, MD_LINEAR, false, RM_NONE, false>(g, t, c, p, s);
-            return launch_mode<double, MD_LINEAR>(g, t, c, p, norms, s);
+        case MD_THESIS: return launch_thesis(g, t, c, p, norms, s);
+        case MD_LINEAR: return launch_linear(g, t, c, p, norms, s);
         case MD_RESID: return launch_sweep<double, MD_RESID, false, RM_NONE, false>(g, t, c, p, s);
     }
     return hipErrorInvalidValue;
@@ -802,10 +774,6 @@ hipError_t launch_correction64(const Geom& g, const Tiling& t, const Coef& c, co
     if (norms) return launch_sweep<double, MD_CORR, true, RM_STORED, true>(g, t, c, p, s);
     return launch_sweep<double, MD_CORR, false, RM_STORED, true>(g, t, c, p, s);
 }
-
-hipError_t launch_reduce_max(const double* partials, int64_t nblocks, double* out8, hipStream_t s) {
-    hipLaunchKernelGGL(k_reduce_max, dim3(1), dim3(RT), 0, s, partials, nblocks, out8);
-    return hipGetLastError();
-}
+#endif
 
 }  // namespace ptk

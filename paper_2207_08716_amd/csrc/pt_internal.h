@@ -175,7 +175,8 @@ __device__ __forceinline__ void tile_thread(int& tx, int& ty) {
 // Blocks of w x h threads (w - 2 by h - 2 output columns and rows) over
 // chunks of kz planes.
 struct TileShape {
-    int w, h, kz;
+    int w = 0, h = 0, kz = 0;
+    bool stream = false;   // the grid's fields outgrow the last-level cache
 };
 
 // Waves per SIMD that a sweep block of n threads is compiled for: what it has
@@ -213,9 +214,9 @@ constexpr double LAST_LEVEL_CACHE = 256.0e6;   // bytes
 // Tiles each variant is built for, larger ones first.
 constexpr int SWEEP_SHAPES = 5;
 inline const TileShape* sweep_shapes(SweepKind k, int& n) {
-    static constexpr TileShape f64[SWEEP_SHAPES] = {{66, 10, 0}, {66, 6, 0}, {34, 14, 0}, {34, 6, 0}, {34, 4, 0}};
-    static constexpr TileShape f32[SWEEP_SHAPES] = {{66, 14, 0}, {66, 10, 0}, {66, 6, 0}, {34, 14, 0}, {34, 6, 0}};
-    static constexpr TileShape norms[4] = {{66, 7, 0}, {34, 14, 0}, {34, 6, 0}, {34, 4, 0}};
+    static constexpr TileShape f64[SWEEP_SHAPES] = {{66, 10}, {66, 6}, {34, 14}, {34, 6}, {34, 4}};
+    static constexpr TileShape f32[SWEEP_SHAPES] = {{66, 14}, {66, 10}, {66, 6}, {34, 14}, {34, 6}};
+    static constexpr TileShape norms[4] = {{66, 7}, {34, 14}, {34, 6}, {34, 4}};
     if (k == SK_F64) { n = 5; return f64; }
     if (k == SK_F32) { n = 5; return f32; }
     n = 4;
@@ -227,31 +228,25 @@ inline int64_t sweep_blocks(const Geom& g, const TileShape& t) {
     return tiles_xy(g, t.w, t.h) * ((g.nz + t.kz - 1) / t.kz);
 }
 
-// The tile and chunk of a sweep: the cheapest by the model above, over the
-// variant's tiles and, for each, the chunks that fill 1 to 16 blocks per
-// compute unit (no more than 4096 blocks beyond the first).
-inline TileShape sweep_shape(const Geom& g, SweepKind kind) {
-    const SweepCost sc = sweep_cost(kind);
+// The cheapest tile and chunk by the model above, over the n shapes given
+// and, for each, the chunks that fill 1 to 16 blocks per compute unit (no
+// more than 4096 blocks beyond the first).  held: waves of a shape's blocks
+// that a compute unit's registers hold; weight: a factor on a shape's cost.
+template <typename Held, typename Weight>
+inline TileShape pick_tile(const Geom& g, const SweepCost& sc, const TileShape* shapes, int n, Held held,
+                           Weight weight) {
     const int cus = g.cus > 0 ? g.cus : DEFAULT_CUS;
     const bool cached = (double)g.nx * g.ny * g.nz * sc.cell_bytes <= LAST_LEVEL_CACHE;
     const double full = cached ? sc.full_cached : sc.full_memory;
-    int n = 0;
-    const TileShape* shapes = sweep_shapes(kind, n);
-    const bool shorter = kind == SK_F32 && corr32_short(g);
     TileShape best{};
     double best_cost = -1.0;
     for (int q = 0; q < n; ++q) {
         TileShape t = shapes[q];
-        if (kind == SK_F32 && t.w == BX) {
-            if (g.tall32 && t.h != BY_CORR32) continue;
-            if (t.h == (shorter ? BY_CORR32 : BY_CORR32_SHORT)) continue;
-        } else if (kind == SK_F32 && g.tall32) {
-            continue;
-        }
+        t.stream = !cached;
         const int64_t tiles = tiles_xy(g, t.w, t.h);
         const int nw = (t.w * t.h + 63) / 64;
-        const int held = kind == SK_F32 ? 24 : kind == SK_NORM32 ? 16 : 4 * sweep_waves(t.w * t.h, kind == SK_NORM64);
-        const int res = std::max(1, held / nw);
+        const int res = std::max(1, held(t, cached) / nw);
+        const double fac = weight(t, cached);
         auto step = [&](int64_t blocks) { return std::max(sc.step + sc.wave * blocks * nw, full * blocks * nw); };
         int last = 0;
         for (int m = 1; m <= 16; ++m) {
@@ -263,7 +258,7 @@ inline TileShape sweep_shape(const Geom& g, SweepKind kind) {
                 if (m > 1 && blocks > 4096) break;
                 const int64_t per_cu = (blocks + cus - 1) / cus;
                 const int64_t rounds = per_cu / res, rest = per_cu % res;
-                const double cost = (t.kz + sc.lead) * (rounds * step(res) + (rest ? step(rest) : 0.0));
+                const double cost = fac * (t.kz + sc.lead) * (rounds * step(res) + (rest ? step(rest) : 0.0));
                 if (best_cost < 0.0 || cost < best_cost * (1.0 - 1e-9)) {
                     best = t;
                     best_cost = cost;
@@ -273,6 +268,24 @@ inline TileShape sweep_shape(const Geom& g, SweepKind kind) {
         }
     }
     return best;
+}
+
+// The tile of a sweep.  Tiles half as wide cost 15 % more where the fields
+// come from memory (rows of 256 bytes; 34 x 14 against 66 x 10 threads at
+// 180^3: 284 and 255 us, at 383^3: 2.32 and 2.15 ms, at equal model cost).  Of
+// the FP32 sweep's 64-column tiles, the 14-row ones are preferred where their
+// tiling costs less rows (corr32_short), and run alone if asked for.
+inline TileShape sweep_shape(const Geom& g, SweepKind kind) {
+    int n = 0;
+    const TileShape* shapes = sweep_shapes(kind, n);
+    if (kind == SK_F32 && g.tall32) n = 1;
+    const int other = kind == SK_F32 ? (corr32_short(g) ? BY_CORR32 : BY_CORR32_SHORT) : 0;
+    return pick_tile(
+        g, sweep_cost(kind), shapes, n,
+        [&](const TileShape& t, bool) {
+            return kind == SK_F32 ? 24 : kind == SK_NORM32 ? 16 : 4 * sweep_waves(t.w * t.h, kind == SK_NORM64);
+        },
+        [&](const TileShape& t, bool cached) { return t.w != BX ? (cached ? 1.0 : 1.15) : t.h == other ? 1.05 : 1.0; });
 }
 
 // The tiles of a grid's sweeps, chosen once per grid, and the blocks that

@@ -5,10 +5,14 @@
 // One launch is one PT iteration on the four iterated cell fields (Xs, Pf,
 // phi, dPf/dt) from iteration-k values.  The only neighbour data are Pf and
 // the permeability k(phi) of the six face neighbours (the Darcy flux of each
-// face), so a 66 x 12 block owns a 64 x 10 column of cells plus a one-cell
-// halo ring and marches up a chunk of planes: per plane it stages Pf and k
-// in LDS (double-buffered: one barrier per plane), keeps the planes below
-// and above of its own column in registers, and updates its tile cells.
+// face), so a W x H block owns a (W-2) x (H-2) column of cells plus a
+// one-cell halo ring and marches up a chunk of planes: per plane it stages
+// Pf and k in LDS (double-buffered: one barrier per plane), keeps the plane
+// above of its own column and the flux from the one below in registers, and
+// updates its tile cells.  Bound by HBM on large grids, by a wave's chain of
+// instructions on small ones; loads and stores go through buffer descriptors
+// whose range check replaces the edges' branches, so that a step waits for
+// its own plane's loads alone (see the two-phase sweep, iter_kernel.hip).
 // The check variant (every nup-th iteration) also takes the maximum of
 // k/beta_P over its output porosity, which the next pseudo step needs, so
 // that only the first pseudo step of a physical step reads the porosity
@@ -18,26 +22,42 @@
 #include <new>
 #include <string>
 
+#include "plane.h"
 #include "pt_internal.h"
 #include "ptwaves.h"
+
+// Multiply-adds are fused where an expression of the source has one: every
+// tile and the check variant round alike.
+#pragma clang fp contract(on)
 
 namespace ptk {
 namespace {
 
-// Block shape: 66 x 12 (64 x 10 output cells; 13 waves of <= 74 VGPRs, two
-// blocks per CU).  Measured at 506 x 506 x 2042, PT iteration with its
-// pseudo-step and check kernels amortised: 8 rows 10.19 ms, 10 rows 10.26,
-// 11 rows 9.74, 12 rows 9.38, 13 rows 9.39, 14 rows 9.47, 15 rows 9.51; the
-// 10-row tiles at one block per CU 9.39; chunks of 64, 128 and 512 planes
-// instead of the cost model's 256: 9.62, 9.48, 9.89; non-temporal loads of
-// the tile-only fields 1-2 % slower at every height.
-constexpr int WW = 66;   // block width (64 output columns)
-constexpr int WH = 12;   // block height (10 output rows)
+// Tiles of the sweep and their cost (pick_tile; constants in us).
+// Tiles of the sweep (pick_tile, constants in us; rms error 14 % over 340
+// measured launches from 8 x 8 x 32 to 95 x 95 x 380, where the tile picked is
+// the fastest measured or within 1 % of it).  Where the fields outgrow the
+// last-level cache, one block at a time on each compute unit: two interleave
+// their planes' accesses in memory (255 x 255 x 1020 1118 -> 1080 us, 506 x
+// 506 x 2042 9.06 -> 8.97 ms; the request for LDS keeps the second one away).
+// Measured, one tile of 66 x 12 threads -> these: 31 x 31 x 124 10.7 -> 5.5 us,
+// 64 x 60 x 250 19.8 -> 15.7, 95 x 95 x 380 78 -> 60, 127 x 127 x 508 170 -> 137,
+// 255 x 255 x 1020 1451 -> 1080, 506 x 506 x 2042 9.22 -> 8.97 ms.
+constexpr TileShape WAVE_TILES[] = {{66, 10}, {34, 14}, {34, 10}, {34, 6}, {34, 4}};
+constexpr unsigned ONE_BLOCK_LDS = 80 * 1024;   // bytes, beside the kernel's own
+inline TileShape waves_tile(const Geom& g) {
+    const SweepCost cost{0.31, 0.089, 0.135, 0.195, 0.73, 88.0};
+    const bool cached = (double)g.nx * g.ny * g.nz * cost.cell_bytes <= LAST_LEVEL_CACHE;
+    return pick_tile(
+        g, cost, WAVE_TILES, cached ? 5 : 2, [](const TileShape&, bool fits) { return fits ? 28 : 1; },
+        [](const TileShape&, bool) { return 1.0; });
+}
 constexpr int RB = 256;  // threads of the reduction kernels
 
 struct WavesCoef {
     double dxi, dyi, dzi, rfg;           // 1/dx, ..., rho_f g
-    double phi0_inv, k_muf0, eta;
+    double hxx, hyy;                     // -1/(2 dx^2), -1/(2 dy^2)
+    double phi0_inv, k_muf0, eta_inv;
     double beta_d, beta_s, beta_f;
     double tau_inv, beta_x, xs_half, xs_max;
     double dt, dti, phi_min, phi_max;
@@ -51,6 +71,11 @@ struct WavesPtrs {
     const double* dtau;                  // pseudo step (device scalar)
     double* partials;                    // [blocks][8]: the block's error, max k/beta_P of its output
 };
+struct WavesArgs {
+    Geom g;
+    WavesCoef c;
+    WavesPtrs p;
+};
 
 __device__ __forceinline__ double perm(const WavesCoef& c, double phi) {
     const double r = phi * c.phi0_inv;
@@ -59,12 +84,12 @@ __device__ __forceinline__ double perm(const WavesCoef& c, double phi) {
 __device__ __forceinline__ double beta_p(const WavesCoef& c, double phi) {
     return phi * c.beta_f + c.beta_d - (1.0 + phi) * c.beta_s;
 }
-__device__ __forceinline__ double nanmax(double m, double v) { return (v > m || v != v) ? v : m; }
 
-template <bool NORMS>
-__global__ __launch_bounds__(WW * WH) void k_waves_sweep(Geom g, WavesCoef c, WavesPtrs p) {
-    constexpr int W = WW, H = WH;
-    __shared__ double spf[2][H][W], skc[2][H][W];
+template <bool NORMS, int W, int H, bool STREAM>
+__global__ __launch_bounds__(W * H) void k_waves_sweep(WavesArgs args) {
+    __shared__ double lds[4 * W * H + 2 * (W + 1)];   // Pf and k of two planes, a margin for the rim's reads
+    const Geom& g = args.g;
+    const WavesCoef& c = args.c;
     const int gx = (g.nx + W - 3) / (W - 2);
     const int gy = (g.ny + H - 3) / (H - 2);
     const int64_t Tt = xcd_tile(blockIdx.x, (int64_t)gridDim.x);
@@ -74,98 +99,152 @@ __global__ __launch_bounds__(WW * WH) void k_waves_sweep(Geom g, WavesCoef c, Wa
     const int i = bx * (W - 2) - 1 + tx;
     const int j = by * (H - 2) - 1 + ty;
     const int kz0 = bz * g.kz, kz1 = min(g.nz, kz0 + g.kz);
-    const bool cell = i >= 0 && i < g.nx && j >= 0 && j < g.ny;
-    const bool tile = cell && tx >= 1 && tx <= W - 2 && ty >= 1 && ty <= H - 2;
-    const int ic = min(max(i, 0), g.nx), jc = min(max(j, 0), g.ny);
-    const int64_t col = (int64_t)jc * g.P + ic;
-    auto at = [&](int k) -> int64_t { return (int64_t)min(max(k, 0), g.nz) * g.S + col; };
-    const double dtau = *p.dtau;
+    const bool in_tile = tx >= 1 && tx <= W - 2 && ty >= 1 && ty <= H - 2;
+    const bool tile = in_tile && i < g.nx && j < g.ny;
+    const bool tile_wave = __builtin_amdgcn_ballot_w64(in_tile) != 0;
 
-    // own column: Pf and k of planes p-1, p, p+1 (zero outside the domain)
-    auto qload = [&](int k, double& pf, double& kc, double& phi) {
-        const int64_t o = at(k);
-        pf = p.pf[o];
-        phi = p.phi[o];
-        const bool ok = cell && k >= 0 && k < g.nz;
-        kc = ok ? perm(c, phi) : 0.0;
-        pf = ok ? pf : 0.0;
+    // Byte offsets in the tile's rows: every column takes the nearest cell's
+    // Pf and k (no flux comes out through the walls), only tile cells the rest.
+    const int row0 = max(by * (H - 2) - 1, 0), rows = min(by * (H - 2) + H - 2, g.ny) - row0 + 1;
+    const int64_t tile0 = (int64_t)row0 * g.P;
+    const u32 o_near = (u32)((min(max(j, 0), g.ny - 1) - row0) * (int)g.P + min(max(i, 0), g.nx - 1)) * 8u;
+    const u32 o_out = tile ? o_near : OFF_NONE;
+    const u32 bytes = (u32)(rows * (int)g.P) * 8u;
+    const double dtau = *args.p.dtau;
+
+    using KPtrs = const __attribute__((address_space(4))) WavesPtrs;
+    KPtrs* const kargs = (KPtrs*)((const __attribute__((address_space(4))) char*)__builtin_amdgcn_kernarg_segment_ptr() +
+                                  offsetof(WavesArgs, p));
+    auto ptrs = [&]() {
+        KPtrs* q = kargs;
+        asm volatile("" : "+s"(q));   // pointers read at each step (see the two-phase sweep)
+        return q;
     };
-    double pf_p, kc_p, phi_p, pf_c, kc_c, phi_c, pf_n, kc_n, phi_n;
-    qload(kz0 - 1, pf_p, kc_p, phi_p);
-    qload(kz0, pf_c, kc_c, phi_c);
-    qload(kz0 + 1, pf_n, kc_n, phi_n);
-    // tile-only values of plane p, loaded one plane ahead
-    double xs = 0.0, dp = 0.0, xso = 0.0, pfo = 0.0, phio = 0.0;
-    auto tload = [&](int k, double& a, double& b, double& d, double& e, double& f) {
-        if (tile) {
-            const int64_t o = at(k);
-            a = p.xs[o]; b = p.dp[o]; d = p.xso[o]; e = p.pfo[o]; f = p.phio[o];
-        }
+
+    // (as in the two-phase sweep: past the last-level cache's size, what is
+    // read once and what is written bypass the caches)
+    constexpr int ONCE = STREAM ? NONTEMPORAL : 0;
+    struct QSet { double pf, phi; };              // plane p+1 of the own column
+    struct CSet { double xs, dp, xso, pfo, phio; };   // tile-only values of plane p
+    struct OSet { double xs, pf, phi, dp; };
+    auto load_q = [&](KPtrs* p, int k, QSet& q) {
+        const int64_t o = (int64_t)k * g.S + tile0;
+        const u32 nb = (k >= 0 && k < g.nz) ? bytes : 0u;
+        q.pf = ldp(p->pf + o, nb, o_near);
+        q.phi = ldp(p->phi + o, nb, o_near);
     };
-    tload(kz0, xs, dp, xso, pfo, phio);
+    auto load_c = [&](KPtrs* p, int k, CSet& q) {
+        const int64_t o = (int64_t)k * g.S + tile0;
+        const u32 nb = k < kz1 ? bytes : 0u;
+        q.xs = ldp<ONCE>(p->xs + o, nb, o_out);
+        q.dp = ldp<ONCE>(p->dp + o, nb, o_out);
+        q.xso = ldp<ONCE>(p->xso + o, nb, o_out);
+        q.pfo = ldp<ONCE>(p->pfo + o, nb, o_out);
+        q.phio = ldp<ONCE>(p->phio + o, nb, o_out);
+    };
+    auto store = [&](KPtrs* p, int k, u32 nb, const OSet& v) {
+        const int64_t o = (int64_t)k * g.S + tile0;
+        stp<ONCE>(p->xs_o + o, nb, o_out, v.xs);
+        stp<ONCE>(p->pf_o + o, nb, o_out, v.pf);
+        stp<ONCE>(p->phi_o + o, nb, o_out, v.phi);
+        stp<ONCE>(p->dp_o + o, nb, o_out, v.dp);
+    };
+
+    double* const me = lds + (W + 1) + ty * W + tx;
+    auto sh = [&](int pl, int dx, int dy) -> double& { return me[pl * (W * H) + dy * W + dx]; };
+
+    // own column: Pf, k and phi of plane p, the Darcy flux through the level below it
+    double pf_c, kc_c, phi_c, qz_c;
     double err = 0.0, kmax = 0.0;
 
-    for (int pz = kz0; pz < kz1; ++pz) {
-        const int buf = pz & 1;
-        // prefetch the next step
-        double pf_nn, kc_nn, phi_nn, xs2 = 0.0, dp2 = 0.0, xso2 = 0.0, pfo2 = 0.0, phio2 = 0.0;
-        qload(pz + 2, pf_nn, kc_nn, phi_nn);
-        tload(pz + 1, xs2, dp2, xso2, pfo2, phio2);
+    auto flux_z = [&](int lev, double pf_lo, double k_lo, double pf_hi, double k_hi) {
+        // through the level between planes lev-1 and lev, zero through the walls;
+        // rounded before it enters a difference
+#pragma clang fp contract(off)
+        const double h = (lev > 0 && lev < g.nz) ? -0.5 : 0.0;
+        return h * (k_lo + k_hi) * ((pf_hi - pf_lo) * c.dzi - c.rfg);
+    };
 
-        spf[buf][ty][tx] = pf_c;
-        skc[buf][ty][tx] = kc_c;
+    auto step = [&](int pz, const QSet& qn, QSet& qnn, const CSet& cc, CSet& cn) __attribute__((always_inline)) {
+        const int b = 2 * (pz & 1);
+        KPtrs* const p = ptrs();
+        load_q(p, pz + 2, qnn);
+        load_c(p, pz + 1, cn);
+        sh(b, 0, 0) = pf_c;
+        sh(b + 1, 0, 0) = kc_c;
+        const double pf_n = qn.pf, phi_n = qn.phi;
+        const double kc_n = perm(c, phi_n);
         __syncthreads();
-
-        if (tile) {
+        OSet out{};
+        if (tile_wave) {
             // Darcy flux of the six faces (zero through the walls), eq (8)'s divergence
-            const double kw = skc[buf][ty][tx - 1], ke = skc[buf][ty][tx + 1];
-            const double ks = skc[buf][ty - 1][tx], kn = skc[buf][ty + 1][tx];
-            const double qxl = (i > 0) ? -0.5 * (kw + kc_c) * (pf_c - spf[buf][ty][tx - 1]) * c.dxi : 0.0;
-            const double qxh = (i < g.nx - 1) ? -0.5 * (kc_c + ke) * (spf[buf][ty][tx + 1] - pf_c) * c.dxi : 0.0;
-            const double qyl = (j > 0) ? -0.5 * (ks + kc_c) * (pf_c - spf[buf][ty - 1][tx]) * c.dyi : 0.0;
-            const double qyh = (j < g.ny - 1) ? -0.5 * (kc_c + kn) * (spf[buf][ty + 1][tx] - pf_c) * c.dyi : 0.0;
-            const double qzl = (pz > 0) ? -0.5 * (kc_p + kc_c) * ((pf_c - pf_p) * c.dzi - c.rfg) : 0.0;
-            const double qzh = (pz < g.nz - 1) ? -0.5 * (kc_c + kc_n) * ((pf_n - pf_c) * c.dzi - c.rfg) : 0.0;
-            const double divq = (qxh - qxl) * c.dxi + (qyh - qyl) * c.dyi + (qzh - qzl) * c.dzi;
+            double qx, qy;
+            {
+#pragma clang fp contract(off)
+                qx = (kc_c + sh(b + 1, 1, 0)) * (sh(b, 1, 0) - pf_c) - (sh(b + 1, -1, 0) + kc_c) * (pf_c - sh(b, -1, 0));
+                qy = (kc_c + sh(b + 1, 0, 1)) * (sh(b, 0, 1) - pf_c) - (sh(b + 1, 0, -1) + kc_c) * (pf_c - sh(b, 0, -1));
+            }
+            const double qz_n = flux_z(pz + 1, pf_c, kc_c, pf_n, kc_n);
+            const double divq = c.hxx * qx + c.hyy * qy + (qz_n - qz_c) * c.dzi;
+            qz_c = qz_n;
 
-            const double pe = -pf_c;
+            const double xs = cc.xs, dp = cc.dp;
             const double xseq = fmin(fmax(c.beta_x * pf_c + c.xs_half, 0.0), c.xs_max);
             const double bp = beta_p(c, phi_c);
-            const double bphi = c.beta_d - c.beta_s / (1.0 - phi_c);
+            const double s = 1.0 - phi_c, s_inv = quot(1.0, s);
+            const double bphi = c.beta_d - c.beta_s * s_inv;
             const double dxsdt = (xseq - xs) * c.tau_inv;
-            const double compaction = pe / (c.eta * (1.0 - phi_c));
-            const double xs_n = xso + c.dt * dxsdt;
-            const double pf_new = pf_c + dtau * dp - dtau * (pf_c - pfo) * c.dti;
-            const double dphidt = (1.0 - phi_c) * (bphi * dp - compaction - c.onepdx / (1.0 - xs) * dxsdt);
-            const double phi_new = fmin(fmax(phio + c.dt * dphidt, c.phi_min), c.phi_max);
-            const double dp_new =
-                (-divq + compaction + c.rho_term * (1.0 - phi_c) * c.onepdx / (1.0 - xs) * dxsdt) / bp;
-            const int64_t o = (int64_t)pz * g.S + col;
-            p.xs_o[o] = xs_n;
-            p.pf_o[o] = pf_new;
-            p.phi_o[o] = phi_new;
-            p.dp_o[o] = dp_new;
-            if (NORMS) {
-                err = nanmax(err, fabs(phi_new - phi_c));
-                err = nanmax(err, fabs(pf_new - pf_c) / 10.0);
-                err = nanmax(err, fabs(xs_n - xs));
+            const double compaction = -pf_c * c.eta_inv * s_inv;
+            const double react = quot(c.onepdx, 1.0 - xs) * dxsdt;
+            out.xs = cc.xso + c.dt * dxsdt;
+            out.pf = pf_c + dtau * dp - dtau * (pf_c - cc.pfo) * c.dti;
+            const double dphidt = s * (bphi * dp - compaction - react);
+            out.phi = fmin(fmax(cc.phio + c.dt * dphidt, c.phi_min), c.phi_max);
+            out.dp = quot(-divq + compaction + c.rho_term * s * react, bp);
+            if (NORMS && tile) {
+                err = nanmax(err, fabs(out.phi - phi_c));
+                err = nanmax(err, fabs(out.pf - pf_c) / 10.0);
+                err = nanmax(err, fabs(out.xs - xs));
                 // the next pseudo step's maximum, over this iteration's output
-                kmax = nanmax(kmax, perm(c, phi_new) / beta_p(c, phi_new));
+                kmax = nanmax(kmax, perm(c, out.phi) / beta_p(c, out.phi));
             }
         }
-        pf_p = pf_c; kc_p = kc_c; phi_p = phi_c;
-        pf_c = pf_n; kc_c = kc_n; phi_c = phi_n;
-        pf_n = pf_nn; kc_n = kc_nn; phi_n = phi_nn;
-        xs = xs2; dp = dp2; xso = xso2; pfo = pfo2; phio = phio2;
+        store(ptrs(), pz, bytes, out);
+        pf_c = fresh(pf_n);
+        kc_c = kc_n;
+        phi_c = fresh(phi_n);
+    };
+
+    QSet qa, qb;
+    CSet ca, cb;
+    {
+        KPtrs* const p = ptrs();
+        QSet q0, q1;
+        load_q(p, kz0 - 1, q0);
+        load_q(p, kz0, q1);
+        load_q(p, kz0 + 1, qa);
+        load_c(p, kz0, ca);
+        // as many (empty) stores as a step ends with, so that the first step
+        // waits for its loads as every other does
+        store(p, kz0, 0u, OSet{});
+        pf_c = q1.pf;
+        phi_c = q1.phi;
+        kc_c = perm(c, q1.phi);
+        qz_c = flux_z(kz0, q0.pf, perm(c, q0.phi), pf_c, kc_c);
     }
-    (void)phi_p;
+    for (int pz = kz0; pz < kz1; pz += 2) {
+        step(pz, qa, qb, ca, cb);
+        if (pz + 1 >= kz1) break;
+        step(pz + 1, qb, qa, cb, ca);
+    }
 
     if constexpr (NORMS) {
-        // wave64 butterfly in each of the H row waves (the halo wave holds
-        // no tile cell), then across them through LDS
-        __shared__ double red[2][WH];
+        // wave64 butterfly in each of the waves of whole tile rows (the halo
+        // wave holds no tile cell), then across them through LDS
+        constexpr int NW = (W - 2) * H / 64;
+        __shared__ double red[2][NW];
         const int L = threadIdx.x, wave = L >> 6, lane = L & 63;
-        if (wave < WH) {
+        if (wave < NW) {
             double v = err, u = kmax;
             for (int off = 32; off >= 1; off >>= 1) {
                 v = nanmax(v, __shfl_xor(v, off, 64));
@@ -180,8 +259,8 @@ __global__ __launch_bounds__(WW * WH) void k_waves_sweep(Geom g, WavesCoef c, Wa
         if (L < NNORM) {
             double r = 0.0;
             if (L < 2)
-                for (int w = 0; w < WH; ++w) r = nanmax(r, red[L][w]);
-            p.partials[(int64_t)blockIdx.x * NNORM + L] = r;
+                for (int w = 0; w < NW; ++w) r = nanmax(r, red[L][w]);
+            args.p.partials[(int64_t)blockIdx.x * NNORM + L] = r;
         }
     }
 }
@@ -242,19 +321,20 @@ struct pt_waves {
     int64_t iter = 0;
     bool checked = false;
     bool kmax_fresh = false;   // the last sweep was a check: max k/beta_P of the present porosity is in hand
+    TileShape tile;            // the sweep's tile on this grid
+    int64_t blocks = 0;        // its blocks
     std::string err;
 };
 
 namespace {
 
-int64_t sweep_blocks(const Geom& g) { return iter_grid_blocks(g, WW, WH); }
 // [sweep partials: blocks x 8][error: 8][dtau: 1][k/beta_P partials: KMAX_BLOCKS]
 size_t waves_ws_needed(const pt_waves* w) {
-    const int64_t n = sweep_blocks(w->geom) * NNORM + NNORM + 1 + KMAX_BLOCKS;
+    const int64_t n = w->blocks * NNORM + NNORM + 1 + KMAX_BLOCKS;
     return (size_t)((n + 31) / 32 * 32) * sizeof(double);
 }
 double* ws_partials(pt_waves* w) { return static_cast<double*>(w->ws); }
-double* ws_error(pt_waves* w) { return ws_partials(w) + sweep_blocks(w->geom) * NNORM; }
+double* ws_error(pt_waves* w) { return ws_partials(w) + w->blocks * NNORM; }
 double* ws_dtau(pt_waves* w) { return ws_error(w) + NNORM; }
 double* ws_kmax(pt_waves* w) { return ws_dtau(w) + 1; }
 
@@ -286,7 +366,9 @@ void waves_coef(pt_waves* w) {
     c.rfg = p.rho_f * p.g;
     c.phi0_inv = 1.0 / p.phi0;
     c.k_muf0 = p.k_muf0;
-    c.eta = p.eta;
+    c.hxx = -0.5 * c.dxi * c.dxi;
+    c.hyy = -0.5 * c.dyi * c.dyi;
+    c.eta_inv = 1.0 / p.eta;
     c.beta_d = p.beta_d; c.beta_s = p.beta_s; c.beta_f = p.beta_f;
     c.tau_inv = 1.0 / p.tau;
     c.beta_x = p.beta_x;
@@ -310,6 +392,32 @@ pt_status waves_ready(pt_waves* w) {
 
 double* wcur(pt_waves* w, int f) { return f < PT_W_NPING ? w->f[f][w->cur[f]] : w->f[f][0]; }
 double* walt(pt_waves* w, int f) { return w->f[f][1 - w->cur[f]]; }
+
+template <bool NORMS, int W, int H, bool STREAM>
+hipError_t launch_waves_tile(pt_waves* w, const WavesPtrs& p) {
+    if (w->geom.P > 0x7fffffff / (H * 8)) return hipErrorInvalidValue;   // a tile's rows: below 2 GiB
+    WavesArgs a{w->geom, w->coef, p};
+    a.g.kz = w->tile.kz;
+    hipLaunchKernelGGL((k_waves_sweep<NORMS, W, H, STREAM>), dim3((unsigned)w->blocks), dim3(W * H),
+                       STREAM ? ONE_BLOCK_LDS : 0, w->stream, a);
+    return hipGetLastError();
+}
+template <bool NORMS>
+hipError_t launch_waves(pt_waves* w, const WavesPtrs& p) {
+    const int wh = w->tile.w * 100 + w->tile.h;
+    if (w->tile.stream) {
+        if (wh == 6610) return launch_waves_tile<NORMS, 66, 10, true>(w, p);
+        if (wh == 3414) return launch_waves_tile<NORMS, 34, 14, true>(w, p);
+    }
+    switch (wh) {
+        case 6610: return launch_waves_tile<NORMS, 66, 10, false>(w, p);
+        case 3414: return launch_waves_tile<NORMS, 34, 14, false>(w, p);
+        case 3410: return launch_waves_tile<NORMS, 34, 10, false>(w, p);
+        case 3406: return launch_waves_tile<NORMS, 34, 6, false>(w, p);
+        case 3404: return launch_waves_tile<NORMS, 34, 4, false>(w, p);
+    }
+    return hipErrorInvalidValue;
+}
 
 pt_status waves_iteration(pt_waves* w, bool refresh_dtau, bool norms) {
     hipError_t e = hipSuccess;
@@ -335,14 +443,10 @@ pt_status waves_iteration(pt_waves* w, bool refresh_dtau, bool norms) {
     p.xs_o = walt(w, PT_W_XS); p.pf_o = walt(w, PT_W_PF); p.phi_o = walt(w, PT_W_PHI); p.dp_o = walt(w, PT_W_DPFDT);
     p.dtau = ws_dtau(w);
     p.partials = ws_partials(w);
-    const Geom v = sweep_geom(w->geom, WW, WH);
-    const dim3 grid((unsigned)sweep_blocks(w->geom)), block(WW * WH);
-    if (norms) hipLaunchKernelGGL(k_waves_sweep<true>, grid, block, 0, w->stream, v, w->coef, p);
-    else hipLaunchKernelGGL(k_waves_sweep<false>, grid, block, 0, w->stream, v, w->coef, p);
-    e = hipGetLastError();
+    e = norms ? launch_waves<true>(w, p) : launch_waves<false>(w, p);
     if (e != hipSuccess) return whip(w, e, "waves sweep");
     if (norms) {
-        e = launch_reduce_max(ws_partials(w), sweep_blocks(w->geom), ws_error(w), w->stream);
+        e = launch_reduce_max(ws_partials(w), w->blocks, ws_error(w), w->stream);
         if (e != hipSuccess) return whip(w, e, "waves error");
         w->checked = true;
     }
@@ -383,6 +487,8 @@ pt_status pt_waves_create(int32_t nx, int32_t ny, int32_t nz, int64_t row_pitch,
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0)
         w->geom.cus = cus;
     (void)hipGetLastError();
+    w->tile = waves_tile(w->geom);
+    w->blocks = sweep_blocks(w->geom, w->tile);
     w->prm = *params;
     std::memset(w->f, 0, sizeof(w->f));
     std::memset(w->cur, 0, sizeof(w->cur));
