@@ -378,12 +378,12 @@ typedef struct {
 } pt_mg_params;
 #define PT_MG_MAX_KRYLOV 8
 
-/* Workspace of a hierarchy (the fine grid's FP32 residual, the
- * restriction's scratch of less than one fine FP64 box, and per coarse
- * grid 25 FP64 boxes plus, above the coarsest, 5 FP32 boxes: about a
- * quarter of the fine grid's fields; with krylov = m, a further 5 (m + 1)
- * FP64 and 5 (m + 1) FP32 fine boxes): query, then bind a device buffer
- * (256-byte aligned) of at least that size; binding clears it (enqueued).
+/* Workspace of a hierarchy (the fine grid's FP32 residual, the restriction's
+ * rows, and per coarse grid 25 FP64 boxes plus, above the coarsest, 5 FP32
+ * boxes: about a quarter of the fine grid's fields; with krylov = m, a
+ * further 5 (m + 1) FP64 and 5 (m + 1) FP32 fine boxes): query, then bind a
+ * device buffer (256-byte aligned) of at least that size; binding clears it
+ * (enqueued).
  * PT_EINVAL if the grid cannot be coarsened to the requested levels, and
  * at binding with krylov > 0 if the row pitch is not a multiple of 4 (the
  * Krylov kernels move 4 columns as one vector). */

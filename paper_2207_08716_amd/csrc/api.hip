@@ -55,7 +55,7 @@ struct pt_grid {
     Tiling mg_tiling[PT_MG_MAX_LEVELS];
     int64_t mg_parts = 0;      // blocks of the coarse grids' partial maxima
     int64_t mg_off[PT_MG_MAX_LEVELS] = {};   // doubles before each coarse grid's boxes
-    int64_t mg_tail = 0;       // doubles before the restriction's scratch
+    int64_t mg_tail = 0;       // doubles before the restriction rows
     int mg_cur[PT_MG_MAX_LEVELS] = {};   // present copy of the coarse grids' iterated fields
     std::string err;
 };
@@ -1264,7 +1264,7 @@ namespace {
 // for the first coarse grid, plus a flag slot); per coarse grid l: 25 FP64
 // boxes (the 8 iterated fields in two copies, ln(1-phi), Fo, the old
 // pressures, k/mu_f, eta_phi, mu_s) and, above the coarsest grid, its FP32
-// residual (5 boxes); the restriction's scratch (less than one fine FP64 box).
+// residual (5 boxes); the restriction rows of every transfer.
 constexpr int MG_NB = 25;
 constexpr int MG_LP = 16, MG_FOX = 17, MG_PTO = 20, MG_PFO = 21, MG_KC = 22, MG_ETA = 23, MG_MUS = 24;
 
@@ -1329,11 +1329,6 @@ int64_t mg_levels_doubles(const Geom* geo, int L) {
     return n;
 }
 
-// Scratch of the separable restriction, sized for the fine grid's (the
-// largest): the x-restricted field and the x- and y-restricted field.
-int64_t mg_scr_a(const Geom* geo) { return ((int64_t)(geo[0].nz + 1) * (geo[0].ny + 1) * geo[1].P + 31) / 32 * 32; }
-int64_t mg_scr_b(const Geom* geo) { return ((int64_t)(geo[0].nz + 1) * (geo[1].ny + 1) * geo[1].P + 31) / 32 * 32; }
-
 // The restriction rows of every grid transfer l -> l + 1: per axis, the rows
 // for cells and for faces normal to it.
 int64_t mg_tab_rows(const Geom& c, int axis) { return (axis == 0 ? c.nx : axis == 1 ? c.ny : c.nz) + 1; }
@@ -1346,7 +1341,7 @@ int64_t mg_tab_doubles(const Geom* geo, int L) {
 
 // Doubles of the hierarchy's pieces (without the Krylov vectors).
 int64_t mg_core_doubles(const Geom* geo, int L) {
-    return mg_levels_doubles(geo, L) + mg_scr_a(geo) + mg_scr_b(geo) + mg_tab_doubles(geo, L);
+    return mg_levels_doubles(geo, L) + mg_tab_doubles(geo, L);
 }
 
 // Krylov vectors after them: the saved iterate and m directions p (5 FP64
@@ -1372,21 +1367,17 @@ float* mg_res(pt_grid* g, int l, int q) {
     return reinterpret_cast<float*>(base) + (int64_t)q * (box_of(g->mg_geom[l]) + 64);
 }
 double* mg_partials(pt_grid* g) { return g->gws + mg_res_doubles(g->mg_geom[0]); }
-double* mg_scr(pt_grid* g, int b) {
-    double* base = g->gws + g->mg_tail;
-    return b == 0 ? base : base + mg_scr_a(g->mg_geom);
-}
 // Rows of the transfer from grid l to l + 1 along `axis` (face: for faces
 // normal to it).
 double* mg_tab(pt_grid* g, int l, int axis, int face) {
-    double* p = mg_scr(g, 1) + mg_scr_b(g->mg_geom);
+    double* p = g->gws + g->mg_tail;
     for (int k = 1; k <= l; ++k)
         for (int a = 0; a < 3; ++a) p += 2 * mg_tab_rows(g->mg_geom[k], a) * MG_TAB;
     for (int a = 0; a < axis; ++a) p += 2 * mg_tab_rows(g->mg_geom[l + 1], a) * MG_TAB;
     return p + (face ? mg_tab_rows(g->mg_geom[l + 1], axis) * MG_TAB : 0);
 }
 double* kry_base(pt_grid* g) {
-    return mg_scr(g, 1) + mg_scr_b(g->mg_geom) + mg_tab_doubles(g->mg_geom, g->mg_levels);
+    return g->gws + g->mg_tail + mg_tab_doubles(g->mg_geom, g->mg_levels);
 }
 double* kry_x(pt_grid* g, int q) { return kry_base(g) + (int64_t)q * mg_stride(g->mg_geom[0]); }
 double* kry_p(pt_grid* g, int s, int q) { return kry_base(g) + (5 + 5 * (int64_t)s + q) * mg_stride(g->mg_geom[0]); }
@@ -1506,30 +1497,38 @@ pt_status mg_correct(pt_grid* g, int l) {
     const int c = l + 1;
     const Geom& gf = g->mg_geom[l];
     const Geom& gc = g->mg_geom[c];
-    const int64_t nbox = box_of(gc);
+    const bool coarsest = c == g->mg_levels - 1;
+    // the coarsest grid's sweeps in one launch where one block holds it
+    const bool whole = coarsest && mg_coarsest_fits(gc);
     hipError_t e = hipSuccess;
-    // the correction starts at zero (the present copies of V, Pt, Pf, R)
+    // the correction starts at zero: the present copies of V, Pt, Pf and, for
+    // the coarsest grid's damped sweeps, R (consecutive boxes)
     const int cp = g->mg_cur[c] ? 8 : 0;
-    for (int b = 0; b < 8 && e == hipSuccess; ++b) e = launch_fill(mg_box(g, c, cp + b), 0.0, nbox, g->stream);
+    if (!whole) e = launch_fill(mg_box(g, c, cp), 0.0, (coarsest ? 8 : 5) * mg_stride(gc), g->stream);
     // right-hand side: the restricted residual in the constant terms
-    for (int a = 0; a < 3 && e == hipSuccess; ++a) {
-        const double* tab[3] = {mg_tab(g, l, 0, a == 0), mg_tab(g, l, 1, a == 1), mg_tab(g, l, 2, a == 2)};
-        e = launch_mg_restrict32(gf, gc, a + 1, mg_res(g, l, a), mg_box(g, c, MG_FOX + a), mg_scr(g, 0), mg_scr(g, 1),
-                                 tab, g->stream);
-    }
     if (e == hipSuccess) {
         const pt_params& p = g->prm;
         // c(-pto + alpha pfo) = a, c(alpha pto - (alpha/B) pfo) = b, c = beta_d/dt
         const double k = p.beta_d / p.dt, al = p.alpha, ab = p.alpha / p.B;
         const double det = k * k * (ab - al * al);
         const double m[4] = {-k * ab / det, -k * al / det, -k * al / det, -k / det};
-        const double* tab[3] = {mg_tab(g, l, 0, 0), mg_tab(g, l, 1, 0), mg_tab(g, l, 2, 0)};
-        e = launch_mg_restrict_fold(gf, gc, mg_res(g, l, 3), mg_res(g, l, 4), mg_box(g, c, MG_PTO),
-                                    mg_box(g, c, MG_PFO), m, mg_scr(g, 0), mg_scr(g, 1), tab, g->stream);
+        const float* res[5];
+        for (int q = 0; q < 5; ++q) res[q] = mg_res(g, l, q);
+        double* const dst[5] = {mg_box(g, c, MG_FOX), mg_box(g, c, MG_FOX + 1), mg_box(g, c, MG_FOX + 2),
+                                mg_box(g, c, MG_PTO), mg_box(g, c, MG_PFO)};
+        const double* tab[3][2];
+        for (int a = 0; a < 3; ++a)
+            for (int face = 0; face < 2; ++face) tab[a][face] = mg_tab(g, l, a, face);
+        e = launch_mg_residual_restrict(gf, gc, res, dst, m, tab, g->stream);
     }
     if (e != hipSuccess) return hip_fail(g, e, "multigrid restriction");
-    pt_status st;
-    if (c == g->mg_levels - 1) {
+    pt_status st = PT_OK;
+    if (whole) {
+        double* out[5];
+        for (int q = 0; q < 5; ++q) out[q] = mg_box(g, c, cp + q);
+        e = launch_mg_coarsest(gc, mg_coef(g, c, true), mg_ptrs(g, c), out, g->mgp.coarse_sweeps, g->stream);
+        if (e != hipSuccess) return hip_fail(g, e, "multigrid coarsest grid");
+    } else if (coarsest) {
         st = mg_smooth(g, c, g->mgp.coarse_sweeps);
     } else {
         st = mg_smooth(g, c, g->mgp.nu1);
@@ -1539,17 +1538,15 @@ pt_status mg_correct(pt_grid* g, int l) {
     }
     if (st != PT_OK) return st;
     // add the interpolated correction to grid l's present copies
-    const int cc = g->mg_cur[c] ? 8 : 0;
-    for (int q = 0; q < 5 && e == hipSuccess; ++q) {
-        double* dst;
-        if (l == 0) {
-            const int fl[5] = {PT_VX, PT_VY, PT_VZ, PT_PT, PT_PF};
-            dst = cur(g, fl[q]);
-        } else {
-            dst = mg_box(g, l, (g->mg_cur[l] ? 8 : 0) + q);
-        }
-        e = launch_mg_prolong_add(gf, gc, q < 3 ? q + 1 : 0, mg_box(g, c, cc + q), dst, g->stream);
+    const int cc = g->mg_cur[c] ? 8 : 0, cl = g->mg_cur[l] ? 8 : 0;
+    const int fl[5] = {PT_VX, PT_VY, PT_VZ, PT_PT, PT_PF};
+    const double* src[5];
+    double* dst[5];
+    for (int q = 0; q < 5; ++q) {
+        src[q] = mg_box(g, c, cc + q);
+        dst[q] = l == 0 ? cur(g, fl[q]) : mg_box(g, l, cl + q);
     }
+    e = launch_mg_prolong_add(gf, gc, src, dst, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "multigrid prolongation");
     return PT_OK;
 }
@@ -1560,17 +1557,16 @@ pt_status mg_coefficients(pt_grid* g) {
     for (int l = 1; l < g->mg_levels && e == hipSuccess; ++l) {
         const Geom& gf = g->mg_geom[l - 1];
         const Geom& gc = g->mg_geom[l];
-        const double* kc = l == 1 ? cur(g, PT_KC) : mg_box(g, l - 1, MG_KC);
-        const double* eta = l == 1 ? cur(g, PT_ETA) : mg_box(g, l - 1, MG_ETA);
-        const double* mus = l == 1 ? cur(g, PT_MUS) : mg_box(g, l - 1, MG_MUS);
-        const double* lp = l == 1 ? cur(g, PT_LP) : mg_box(g, l - 1, MG_LP);
+        const int from[4] = {PT_KC, PT_ETA, PT_MUS, PT_LP}, box[4] = {MG_KC, MG_ETA, MG_MUS, MG_LP};
+        const int mean[4] = {1, g->mgp.eta_mean, 0, 0};
+        const double* src[4];
+        double* dst[4];
+        for (int q = 0; q < 4; ++q) {
+            src[q] = l == 1 ? cur(g, from[q]) : mg_box(g, l - 1, box[q]);
+            dst[q] = mg_box(g, l, box[q]);
+        }
         const double* tab[3] = {mg_tab(g, l - 1, 0, 0), mg_tab(g, l - 1, 1, 0), mg_tab(g, l - 1, 2, 0)};
-        double *sa = mg_scr(g, 0), *sb = mg_scr(g, 1);
-        e = launch_mg_restrict(gf, gc, kc, mg_box(g, l, MG_KC), 1, sa, sb, tab, g->stream);
-        if (e == hipSuccess)
-            e = launch_mg_restrict(gf, gc, eta, mg_box(g, l, MG_ETA), g->mgp.eta_mean, sa, sb, tab, g->stream);
-        if (e == hipSuccess) e = launch_mg_restrict(gf, gc, mus, mg_box(g, l, MG_MUS), 0, sa, sb, tab, g->stream);
-        if (e == hipSuccess) e = launch_mg_restrict(gf, gc, lp, mg_box(g, l, MG_LP), 0, sa, sb, tab, g->stream);
+        e = launch_mg_coef_restrict(gf, gc, src, dst, mean, tab, g->stream);
     }
     if (e != hipSuccess) return hip_fail(g, e, "multigrid coefficients");
     return PT_OK;

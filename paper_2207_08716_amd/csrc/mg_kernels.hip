@@ -61,11 +61,10 @@ __device__ __forceinline__ void prange(int J, int nf, int nc, bool face, int& lo
     }
 }
 
-// The x taps of a restriction, in registers: fine indices lo .. lo + 7 and
-// P's entries for coarse index I (a coarse grid has ceil(n/2) cells, so the
-// ratio is at most 2 and the candidate range spans at most 7 fine points).
+// Candidate taps of coarse index J: P's entries for the fine indices lo ..
+// lo + n - 1 (a coarse grid has ceil(n/2) cells, so the ratio is at most 2
+// and the candidates span at most 7 fine points).
 constexpr int MAXT = 8;
-static_assert(MG_TAB == 2 + MAXT, "a restriction row holds its first index, its count and MAXT weights");
 struct Taps {
     int lo, n;
     double w[MAXT];
@@ -95,51 +94,14 @@ struct Ext {
 };
 __host__ __device__ inline Ext ext(const Geom& g) { return Ext{g.nx, g.ny, g.nz, g.P, g.S}; }
 
-// One axis of the separable restriction.  The restriction is a tensor
-// product of one-dimensional rows, each normalised to weight sum 1, so it
-// runs as three passes (x, then y, then z), each reading its input once in
-// rows instead of gathering every coarse point's 3D neighbourhood.  dst
-// holds the points (i, j, k) < (ex, ey, ez) whose coordinate along `axis`
-// is coarse and whose other coordinates are src's; strides sP, sS (src) and
-// dP, dS (dst).  tab: the axis's normalised rows (MG_TAB doubles per coarse
-// index: first fine index, count, weights), built once per hierarchy.
-// Launched on a 3D grid of GX x GY blocks (x: i, y: j, z: k), so that no
-// thread divides its index.
 constexpr int GX = 64, GY = 4;
-
-// mean: 0 arithmetic; 1 harmonic, 2 geometric (the x pass averages 1/v or
-// ln v, the z pass maps the average back), so that the passes stay linear.
-template <typename TI>
-__global__ __launch_bounds__(GX * GY) void k_mg_r1(const TI* __restrict__ src, int64_t sP, int64_t sS,
-                                                  double* __restrict__ dst, int64_t dP, int64_t dS, int ex, int ey,
-                                                  int axis, const double* __restrict__ tab, int mean) {
-    const int i = blockIdx.x * GX + threadIdx.x, j = blockIdx.y * GY + threadIdx.y, k = blockIdx.z;
-    if (i < ex && j < ey) {
-        const int64_t step = axis == 0 ? 1 : (axis == 1 ? sP : sS);
-        const int J = axis == 0 ? i : (axis == 1 ? j : k);
-        const double* row = tab + (int64_t)J * MG_TAB;
-        const int lo = (int)row[0], cnt = (int)row[1];
-        const int64_t base = (axis == 0 ? (int64_t)k * sS + (int64_t)j * sP
-                                        : (axis == 1 ? (int64_t)k * sS + i : (int64_t)j * sP + i)) +
-                             (int64_t)lo * step;
-        double r = 0.0;
-#pragma unroll
-        for (int q = 0; q < MAXT; ++q)
-            if (q < cnt) {
-                double v = (double)src[base + q * step];
-                if (axis == 0 && mean) v = mean == 1 ? 1.0 / v : log(v);
-                r += row[2 + q] * v;
-            }
-        if (axis == 2 && mean && cnt > 0) r = mean == 1 ? 1.0 / r : exp(r);
-        dst[(int64_t)k * dS + (int64_t)j * dP + i] = r;
-    }
-}
-
-dim3 grid3(int ex, int ey, int ez) { return dim3((unsigned)((ex + GX - 1) / GX), (unsigned)((ey + GY - 1) / GY), (unsigned)ez); }
 
 // The normalised restriction rows of one axis (fine nf, coarse nc points;
 // face: the field sits on faces normal to it, whose wall faces carry no
-// equation: skipped as inputs, rows of weight 0 for the coarse walls).
+// equation: skipped as inputs, rows of no tap for the coarse walls).  A row is
+// the first fine index, the number of taps and MG_TAPS weights.  The weights
+// of linear interpolation at a ratio of at most 2 are zero outside an open
+// interval 4 fine points wide, so at most MG_TAPS of them are not.
 __global__ __launch_bounds__(TB) void k_mg_taps(double* __restrict__ tab, int nf, int nc, bool face) {
     const int J = blockIdx.x * TB + threadIdx.x;
     if (J > nc - 1 + face) return;
@@ -147,76 +109,266 @@ __global__ __launch_bounds__(TB) void k_mg_taps(double* __restrict__ tab, int nf
     Taps tt;
     taps(J, nf, nc, face, face, tt);
     const bool none = (face && (J == 0 || J == nc)) || !(tt.sum > 0.0);
-    row[0] = tt.lo;
-    row[1] = none ? 0 : tt.n;
+    int first = 0, last = -1;
 #pragma unroll
-    for (int q = 0; q < MAXT; ++q) row[2 + q] = none ? 0.0 : tt.w[q] / tt.sum;
+    for (int q = 0; q < MAXT; ++q)
+        if (tt.w[q] != 0.0) {
+            if (last < 0) first = q;
+            last = q;
+        }
+    const int n = none ? 0 : min(last - first + 1, MG_TAPS);
+    row[0] = none ? min(max(tt.lo, 0), nf - 1) : tt.lo + first;
+    row[1] = n;
+#pragma unroll
+    for (int q = 0; q < MG_TAPS; ++q) row[2 + q] = 0.0;
+#pragma unroll
+    for (int q = 0; q < MAXT; ++q)
+        if (!none && q >= first && q - first < n) row[2 + q - first] = tt.w[q] / tt.sum;
 }
 
-// Restricted pressure residuals (a, b) folded into old-pressure fields in
-// place: pto = m00 a + m01 b, pfo = m10 a + m11 b, the values whose terms
-// in r_Pt and r_Pf at the zero state are a and b.
-__global__ __launch_bounds__(TB) void k_mg_fold(Ext c, double* __restrict__ pto, double* __restrict__ pfo,
-                                                double m00, double m01, double m10, double m11) {
-    const int64_t n = (int64_t)c.nx * c.ny * c.nz;
-    for (int64_t t = (int64_t)blockIdx.x * TB + threadIdx.x; t < n; t += (int64_t)gridDim.x * TB) {
-        const int I = (int)(t % c.nx), J = (int)((t / c.nx) % c.ny), K = (int)(t / ((int64_t)c.nx * c.ny));
-        const int64_t o = (int64_t)K * c.S + (int64_t)J * c.P + I;
-        const double a = pto[o], b = pfo[o];
-        pto[o] = m00 * a + m01 * b;
-        pfo[o] = m10 * a + m11 * b;
-    }
-}
+// Restriction of up to five fields in one launch.  The restriction is a
+// tensor product of one-dimensional rows of at most four weights, each
+// normalised to sum 1.  A thread owns a coarse column (I, J) of one field and
+// marches up a chunk of coarse planes: it averages each fine plane around
+// (I, J) once (up to 16 values through the caches) and keeps the last four
+// of these averages in registers, from which every coarse plane takes its
+// own; neighbouring threads read the same lines, so the fine field comes from
+// memory about once.  One launch instead of three passes per field through
+// scratch and a fold: on small grids the launches were the cost (127^3: 16
+// launches of 2.4 to 7 us per transfer), on large ones the passes' traffic.
+// mean (cells): 0 arithmetic, 1 harmonic, 2 geometric, by averaging v, 1/v
+// or ln v.  A field's fine value is src or, with src2, m0 src + m1 src2.
+struct RestrictField {
+    const void* src;
+    const void* src2;
+    double* dst;
+    const double* tab[3];
+    double m0, m1;
+    int ex, ey, ez;      // coarse extent
+    int mean;
+};
+struct RestrictArgs {
+    RestrictField f[5];
+    int64_t fP, fS, cP, cS;
+    int kc;              // coarse planes per chunk
+    int chunks;
+};
 
-// fine += P coarse for one field of staggering (fx, fy, fz); the walls'
-// normal faces keep their values.
-__global__ __launch_bounds__(GX * GY) void k_mg_prolong_add(Ext f, Ext c, bool fx, bool fy, bool fz,
-                                                            const double* __restrict__ src,
-                                                            double* __restrict__ dst) {
-    const int ex = f.nx + fx, ey = f.ny + fy;
-    const int i = blockIdx.x * GX + threadIdx.x, j = blockIdx.y * GY + threadIdx.y, k = blockIdx.z;
-    if (i < ex && j < ey) {
-        if ((fx && (i == 0 || i == f.nx)) || (fy && (j == 0 || j == f.ny)) || (fz && (k == 0 || k == f.nz))) return;
-        int x0, y0, z0;
-        double tx, ty, tz;
-        pw(i, f.nx, c.nx, fx, x0, tx);
-        pw(j, f.ny, c.ny, fy, y0, ty);
-        pw(k, f.nz, c.nz, fz, z0, tz);
-        // the second point of an axis: inside the coarse extent (its weight
-        // is zero where the first point is the last one)
-        const int x1 = min(x0 + 1, c.nx - 1 + fx), y1 = min(y0 + 1, c.ny - 1 + fy), z1 = min(z0 + 1, c.nz - 1 + fz);
-        auto at = [&](int a, int b, int d) { return src[(int64_t)d * c.S + (int64_t)b * c.P + a]; };
-        const double v0 = (1.0 - tx) * at(x0, y0, z0) + tx * at(x1, y0, z0);
-        const double v1 = (1.0 - tx) * at(x0, y1, z0) + tx * at(x1, y1, z0);
-        const double v2 = (1.0 - tx) * at(x0, y0, z1) + tx * at(x1, y0, z1);
-        const double v3 = (1.0 - tx) * at(x0, y1, z1) + tx * at(x1, y1, z1);
-        const double v = (1.0 - tz) * ((1.0 - ty) * v0 + ty * v1) + tz * ((1.0 - ty) * v2 + ty * v3);
-        dst[(int64_t)k * f.S + (int64_t)j * f.P + i] += v;
-    }
-}
-
-unsigned blocks_for(int64_t n) { return (unsigned)std::min<int64_t>((n + TB - 1) / TB, 65536); }
-
-}  // namespace
-
-namespace {
-
-// The three passes of a separable restriction of an FP32 fine field
-// (scratch sa: (nz_f + 1) (ny_f + 1) P_c doubles, sb: (nz_f + 1) (ny_c + 1) P_c;
-// tab: the rows of the x, y, z axes for this field's staggering).
 template <typename TI>
-hipError_t restrict_sep(const Geom& gf, const Geom& gc, int kind, const TI* src, double* dst, double* sa,
-                        double* sb, const double* const tab[3], int mean, hipStream_t s) {
-    const bool fx = kind == 1, fy = kind == 2, fz = kind == 3;
-    const int64_t aS = gc.P * (int64_t)(gf.ny + 1), bS = gc.P * (int64_t)(gc.ny + 1);
-    const dim3 blk(GX, GY);
-    hipLaunchKernelGGL(k_mg_r1<TI>, grid3(gc.nx + fx, gf.ny + fy, gf.nz + fz), blk, 0, s, src, gf.P, gf.S, sa,
-                       gc.P, aS, gc.nx + fx, gf.ny + fy, 0, tab[0], mean);
-    hipLaunchKernelGGL(k_mg_r1<double>, grid3(gc.nx + fx, gc.ny + fy, gf.nz + fz), blk, 0, s, (const double*)sa,
-                       gc.P, aS, sb, gc.P, bS, gc.nx + fx, gc.ny + fy, 1, tab[1], mean);
-    hipLaunchKernelGGL(k_mg_r1<double>, grid3(gc.nx + fx, gc.ny + fy, gc.nz + fz), blk, 0, s, (const double*)sb,
-                       gc.P, bS, dst, gc.P, gc.S, gc.nx + fx, gc.ny + fy, 2, tab[2], mean);
-    return hipGetLastError();
+__global__ __launch_bounds__(GX * GY) void k_mg_restrict(RestrictArgs a) {
+    const RestrictField& f = a.f[blockIdx.z / a.chunks];
+    const int I = blockIdx.x * GX + threadIdx.x, J = blockIdx.y * GY + threadIdx.y;
+    const int K0 = (int)(blockIdx.z % a.chunks) * a.kc, K1 = min(f.ez, K0 + a.kc);
+    if (I >= f.ex || J >= f.ey || K0 >= f.ez) return;
+    const TI* src = static_cast<const TI*>(f.src);
+    const TI* src2 = static_cast<const TI*>(f.src2);
+    const double* rx = f.tab[0] + (int64_t)I * MG_TAB;
+    const double* ry = f.tab[1] + (int64_t)J * MG_TAB;
+    const int nx = (int)rx[1], ny = (int)ry[1];
+    double wx[MG_TAPS], wy[MG_TAPS];
+    int64_t ox[MG_TAPS], oy[MG_TAPS];
+#pragma unroll
+    for (int q = 0; q < MG_TAPS; ++q) {
+        // taps past the row's last repeat it with weight 0
+        wx[q] = rx[2 + q];
+        wy[q] = ry[2 + q];
+        ox[q] = (int)rx[0] + max(min(q, nx - 1), 0);
+        oy[q] = (int64_t)((int)ry[0] + max(min(q, ny - 1), 0)) * a.fP;
+    }
+    auto plane = [&](int k) -> double {
+        const int64_t o = (int64_t)k * a.fS;
+        double r = 0.0;
+#pragma unroll
+        for (int y = 0; y < MG_TAPS; ++y) {
+            double v = 0.0;
+#pragma unroll
+            for (int x = 0; x < MG_TAPS; ++x) {
+                double u = (double)src[o + oy[y] + ox[x]];
+                if (src2) u = f.m0 * u + f.m1 * (double)src2[o + oy[y] + ox[x]];
+                if (f.mean) u = f.mean == 1 ? 1.0 / u : log(u);
+                v += wx[x] * u;
+            }
+            r += wy[y] * v;
+        }
+        return r;
+    };
+    // averages of the fine planes base .. base + 3
+    double s[MG_TAPS] = {};
+    int base = 0, have = 0;
+    for (int K = K0; K < K1; ++K) {
+        const double* rz = f.tab[2] + (int64_t)K * MG_TAB;
+        const int lo = (int)rz[0], nz = (int)rz[1];
+        double r = 0.0;
+        if (nx > 0 && ny > 0 && nz > 0) {
+            // keep what the planes before left, drop what lies below lo
+            const int drop = have ? min(lo - base, have) : 0;
+            for (int d = 0; d < drop; ++d) {
+                s[0] = s[1]; s[1] = s[2]; s[2] = s[3];
+            }
+            have -= drop;
+            base = lo;
+#pragma unroll
+            for (int q = 0; q < MG_TAPS; ++q)
+                if (q >= have && q < nz) s[q] = plane(lo + q);
+            have = max(have, nz);
+#pragma unroll
+            for (int q = 0; q < MG_TAPS; ++q)
+                if (q < nz) r += rz[2 + q] * s[q];
+            if (f.mean) r = f.mean == 1 ? 1.0 / r : exp(r);
+        } else {
+            have = 0;
+        }
+        f.dst[(int64_t)K * a.cS + (int64_t)J * a.cP + I] = r;
+    }
+}
+
+dim3 grid3(int ex, int ey, int ez) { return dim3((unsigned)((ex + GX - 1) / GX), (unsigned)((ey + GY - 1) / GY), (unsigned)ez); }
+
+// fine += P coarse for the three velocities and the two pressures, one launch
+// (a block's field and fine plane in its third index); the walls' normal
+// faces keep their values.
+struct ProlongArgs {
+    Ext f, c;
+    const double* src[5];
+    double* dst[5];
+};
+__global__ __launch_bounds__(GX * GY) void k_mg_prolong_add(ProlongArgs a) {
+    const Ext& f = a.f;
+    const Ext& c = a.c;
+    const int q = blockIdx.z % 5, k = blockIdx.z / 5;
+    const bool fx = q == 0, fy = q == 1, fz = q == 2;
+    const int i = blockIdx.x * GX + threadIdx.x, j = blockIdx.y * GY + threadIdx.y;
+    if (i >= f.nx + fx || j >= f.ny + fy || k >= f.nz + fz) return;
+    if ((fx && (i == 0 || i == f.nx)) || (fy && (j == 0 || j == f.ny)) || (fz && (k == 0 || k == f.nz))) return;
+    int x0, y0, z0;
+    double tx, ty, tz;
+    pw(i, f.nx, c.nx, fx, x0, tx);
+    pw(j, f.ny, c.ny, fy, y0, ty);
+    pw(k, f.nz, c.nz, fz, z0, tz);
+    // the second point of an axis: inside the coarse extent (its weight
+    // is zero where the first point is the last one)
+    const int x1 = min(x0 + 1, c.nx - 1 + fx), y1 = min(y0 + 1, c.ny - 1 + fy), z1 = min(z0 + 1, c.nz - 1 + fz);
+    const double* src = a.src[q];
+    auto at = [&](int u, int v, int w) { return src[(int64_t)w * c.S + (int64_t)v * c.P + u]; };
+    const double v0 = (1.0 - tx) * at(x0, y0, z0) + tx * at(x1, y0, z0);
+    const double v1 = (1.0 - tx) * at(x0, y1, z0) + tx * at(x1, y1, z0);
+    const double v2 = (1.0 - tx) * at(x0, y0, z1) + tx * at(x1, y0, z1);
+    const double v3 = (1.0 - tx) * at(x0, y1, z1) + tx * at(x1, y1, z1);
+    const double v = (1.0 - tz) * ((1.0 - ty) * v0 + ty * v1) + tz * ((1.0 - ty) * v2 + ty * v3);
+    a.dst[q][(int64_t)k * f.S + (int64_t)j * f.P + i] += v;
+}
+
+// ---- the coarsest grid's damped PT sweeps, in one launch -------------------------
+// n sweeps of the linear PT iteration from the zero state on a grid of at
+// most 1024 cells, by one block with one thread per cell (and the three
+// faces at its low sides).  The state stays in registers, neighbours are read
+// from LDS planes with a rim of zeros, every coefficient, including the
+// quotients of the pseudo steps, is formed once; two barriers per sweep.
+// Bound by the latency of a sweep's chain through LDS: fifty sweeps of the
+// 8^3 grid take 44 us, where fifty launches of the sweep kernel on its
+// smallest tile took 7 us each (22 us each on the 66 x 10 tile that every
+// grid once had).
+struct CoarseArgs {
+    int nx, ny, nz, n;
+    int64_t P, S;
+    double dxi, dyi, dzi;
+    double bdt, alpha, ab;          // beta_d/dt, alpha, alpha/B
+    double gdts, beta_n, rho_i_inv;
+    double dtauv_c, dtaupt_c, dtaupf_c, dampx, dampy, dampz;
+    const double *lp, *kc, *eta, *mus, *fox, *foy, *foz, *pto, *pfo;
+    double *vx, *vy, *vz, *pt, *pf;
+};
+
+__global__ __launch_bounds__(1024) void k_mg_coarsest(CoarseArgs a) {
+    extern __shared__ double lds[];
+    const int X = a.nx + 2, XY = X * (a.ny + 2), N = XY * (a.nz + 2);   // a plane of the rimmed grid
+    double *vx = lds, *vy = vx + N, *vz = vy + N, *pf = vz + N, *sx = pf + N, *sy = sx + N, *sz = sy + N, *txy = sz + N,
+           *txz = txy + N, *tyz = txz + N;
+    for (int t = threadIdx.x; t < 10 * N; t += blockDim.x) lds[t] = 0.0;
+    const int cells = a.nx * a.ny * a.nz;
+    const bool on = (int)threadIdx.x < cells;
+    const int c = on ? threadIdx.x : 0;
+    const int i = c % a.nx, j = (c / a.nx) % a.ny, k = c / (a.nx * a.ny);
+    const int64_t o = (int64_t)k * a.S + (int64_t)j * a.P + i;
+    const int me = (k + 1) * XY + (j + 1) * X + i + 1;
+    const bool lx = i >= 1, ly = j >= 1, lz = k >= 1;
+    __syncthreads();
+    // coefficients of neighbours through two of the planes
+    const double mu = a.mus[o], kc = a.kc[o];
+    if (on) {
+        sx[me] = mu;
+        sy[me] = kc;
+    }
+    __syncthreads();
+    const double mw = sx[me - 1], ms = sx[me - X], mb = sx[me - XY];
+    auto maxwell = [&](double m) { return 2.0 * m / (1.0 + m * a.gdts); };
+    const double b = maxwell(mu);
+    // half the edge coefficients (the strain rates come without their 1/2); zero on the walls
+    const double exy = lx && ly ? 0.5 * maxwell(0.25 * (sx[me - X - 1] + ms + mw + mu)) : 0.0;
+    const double exz = lx && lz ? 0.5 * maxwell(0.25 * (sx[me - XY - 1] + mb + mw + mu)) : 0.0;
+    const double eyz = ly && lz ? 0.5 * maxwell(0.25 * (sx[me - XY - X] + mb + ms + mu)) : 0.0;
+    const double dvx = lx ? a.dtauv_c / fmax(mu, mw) : 0.0, dvy = ly ? a.dtauv_c / fmax(mu, ms) : 0.0,
+                 dvz = lz ? a.dtauv_c / fmax(mu, mb) : 0.0;
+    const double kw = sy[me - 1], ke = sy[me + 1], ks = sy[me - X], kn = sy[me + X], kb = sy[me - XY], kt = sy[me + XY];
+    const double qx = 0.5 * a.dxi * a.dxi, qy = 0.5 * a.dyi * a.dyi, qz = 0.5 * a.dzi * a.dzi;
+    const double cw = lx ? qx * (kw + kc) : 0.0, ce = i + 1 < a.nx ? qx * (kc + ke) : 0.0;
+    const double cs = ly ? qy * (ks + kc) : 0.0, cn = j + 1 < a.ny ? qy * (kc + kn) : 0.0;
+    const double cb = lz ? qz * (kb + kc) : 0.0, ct = k + 1 < a.nz ? qz * (kc + kt) : 0.0;
+    const double kl = fmax(fmax(fmax(kc, kw), fmax(ke, ks)), fmax(fmax(kn, kb), kt));   // zero outside the domain
+    const double chi = 1.0 / (a.eta[o] * exp(a.lp[o]));
+    const double dtp = a.dtaupt_c * mu, dtf = a.dtaupf_c / kl;
+    const double tp = dtp / (1.0 + dtp * (a.bdt + chi)), tf = dtf / (1.0 + dtf * (a.bdt * a.ab + chi));
+    const double pto = a.pto[o], pfo = a.pfo[o];
+    // r_Pt = div V + rp0 + Pt rpp - Pf cross, r_Pf = div q + rf0 + Pf rff - Pt cross
+    const double rp0 = a.bdt * (a.alpha * pfo - pto), rf0 = a.bdt * (a.alpha * pto - a.ab * pfo);
+    const double rpp = a.bdt + chi, rff = a.bdt * a.ab + chi, cross = a.bdt * a.alpha + chi;
+    const double fox = lx ? a.fox[o] : 0.0, foy = ly ? a.foy[o] : 0.0, foz = lz ? a.foz[o] : 0.0;
+    __syncthreads();
+    if (on) sx[me] = sy[me] = 0.0;
+    __syncthreads();
+    double u = 0.0, v = 0.0, w = 0.0, p = 0.0, f = 0.0, ru = 0.0, rv = 0.0, rw = 0.0;
+    for (int it = 0; it < a.n; ++it) {
+        // (the planes written here are read before the second barrier, those
+        // written between the barriers after it: no third barrier is needed)
+        if (on) {
+            vx[me] = u; vy[me] = v; vz[me] = w; pf[me] = f;
+        }
+        __syncthreads();
+        const double ex = (vx[me + 1] - u) * a.dxi, ey = (vy[me + X] - v) * a.dyi, ez = (vz[me + XY] - w) * a.dzi;
+        const double div = ex + ey + ez;
+        const double rpt = div + rp0 + p * rpp - f * cross;
+        const double divq = cw * (f - pf[me - 1]) - ce * (pf[me + 1] - f) + cs * (f - pf[me - X]) - cn * (pf[me + X] - f) +
+                            cb * (f - pf[me - XY]) - ct * (pf[me + XY] - f);
+        const double rpf = divq + rf0 + f * rff - p * cross;
+        const double ptn = p - tp * rpt;
+        const double m = a.beta_n * rpt - div * (1.0 / 3.0);
+        const double nx = b * (ex + m) - ptn, ny = b * (ey + m) - ptn, nz = b * (ez + m) - ptn;
+        const double hxy = exy * ((u - vx[me - X]) * a.dyi + (v - vy[me - 1]) * a.dxi);
+        const double hxz = exz * ((u - vx[me - XY]) * a.dzi + (w - vz[me - 1]) * a.dxi);
+        const double hyz = eyz * ((v - vy[me - XY]) * a.dzi + (w - vz[me - X]) * a.dyi);
+        if (on) {
+            sx[me] = nx; sy[me] = ny; sz[me] = nz;
+            txy[me] = hxy; txz[me] = hxz; tyz[me] = hyz;
+        }
+        f -= tf * rpf;
+        p = ptn;
+        __syncthreads();
+        const double gx = (nx - sx[me - 1]) * a.dxi + (txy[me + X] - hxy) * a.dyi + (txz[me + XY] - hxz) * a.dzi + fox;
+        const double gy = (txy[me + 1] - hxy) * a.dxi + (ny - sy[me - X]) * a.dyi + (tyz[me + XY] - hyz) * a.dzi + foy;
+        const double gz = (txz[me + 1] - hxz) * a.dxi + (tyz[me + X] - hyz) * a.dyi + (nz - sz[me - XY]) * a.dzi + foz;
+        ru = gx * a.rho_i_inv + a.dampx * ru;
+        rv = gy * a.rho_i_inv + a.dampy * rv;
+        rw = gz * a.rho_i_inv + a.dampz * rw;
+        u += dvx * ru;
+        v += dvy * rv;
+        w += dvz * rw;
+    }
+    if (on) {
+        // (wall faces hold their zero)
+        a.vx[o] = u; a.vy[o] = v; a.vz[o] = w;
+        a.pt[o] = p;
+        a.pf[o] = f;
+    }
 }
 
 }  // namespace
@@ -226,32 +378,95 @@ hipError_t launch_mg_taps(double* tab, int nf, int nc, int face, hipStream_t s) 
     return hipGetLastError();
 }
 
-hipError_t launch_mg_restrict(const Geom& gf, const Geom& gc, const double* src, double* dst, int mean, double* sa,
-                              double* sb, const double* const tab[3], hipStream_t s) {
-    return restrict_sep(gf, gc, 0, src, dst, sa, sb, tab, mean, s);
-}
+namespace {
 
-hipError_t launch_mg_restrict32(const Geom& gf, const Geom& gc, int kind, const float* src, double* dst,
-                                double* sa, double* sb, const double* const tab[3], hipStream_t s) {
-    return restrict_sep(gf, gc, kind, src, dst, sa, sb, tab, 0, s);
-}
-
-hipError_t launch_mg_restrict_fold(const Geom& gf, const Geom& gc, const float* rpt, const float* rpf, double* pto,
-                                   double* pfo, const double m[4], double* sa, double* sb, const double* const tab[3],
-                                   hipStream_t s) {
-    hipError_t e = restrict_sep(gf, gc, 0, rpt, pto, sa, sb, tab, 0, s);
-    if (e == hipSuccess) e = restrict_sep(gf, gc, 0, rpf, pfo, sa, sb, tab, 0, s);
-    if (e != hipSuccess) return e;
-    const int64_t n = (int64_t)gc.nx * gc.ny * gc.nz;
-    hipLaunchKernelGGL(k_mg_fold, dim3(blocks_for(n)), dim3(TB), 0, s, ext(gc), pto, pfo, m[0], m[1], m[2], m[3]);
+// Coarse planes per chunk: a chunk's first plane averages four fine planes,
+// the others two, so long chunks read less; short ones give a small grid
+// more blocks (at least two per compute unit while a chunk has a plane).
+template <typename TI>
+hipError_t launch_restrict(const Geom& gf, const Geom& gc, RestrictArgs& a, int n, hipStream_t s) {
+    a.fP = gf.P; a.fS = gf.S; a.cP = gc.P; a.cS = gc.S;
+    const dim3 cols = grid3(gc.nx + 1, gc.ny + 1, 1);
+    const int64_t per = (int64_t)cols.x * cols.y * n;
+    const int cus = gf.cus > 0 ? gf.cus : DEFAULT_CUS;
+    a.kc = (int)std::min<int64_t>(16, std::max<int64_t>(1, (int64_t)(gc.nz + 1) * per / (2 * cus)));
+    a.chunks = (gc.nz + a.kc) / a.kc;
+    hipLaunchKernelGGL(k_mg_restrict<TI>, dim3(cols.x, cols.y, (unsigned)(n * a.chunks)), dim3(GX, GY), 0, s, a);
     return hipGetLastError();
 }
 
-hipError_t launch_mg_prolong_add(const Geom& gf, const Geom& gc, int kind, const double* src, double* dst,
+}  // namespace
+
+hipError_t launch_mg_residual_restrict(const Geom& gf, const Geom& gc, const float* const res[5], double* const dst[5],
+                                       const double m[4], const double* const tab[3][2], hipStream_t s) {
+    RestrictArgs a{};
+    for (int q = 0; q < 5; ++q) {
+        RestrictField& f = a.f[q];
+        f.dst = dst[q];
+        f.ex = gc.nx + (q == 0); f.ey = gc.ny + (q == 1); f.ez = gc.nz + (q == 2);
+        for (int x = 0; x < 3; ++x) f.tab[x] = tab[x][x == q];
+        if (q < 3) {
+            f.src = res[q];
+        } else {
+            f.src = res[3];
+            f.src2 = res[4];
+            f.m0 = m[2 * (q - 3)];
+            f.m1 = m[2 * (q - 3) + 1];
+        }
+    }
+    return launch_restrict<float>(gf, gc, a, 5, s);
+}
+
+hipError_t launch_mg_coef_restrict(const Geom& gf, const Geom& gc, const double* const src[4], double* const dst[4],
+                                   const int mean[4], const double* const tab[3], hipStream_t s) {
+    RestrictArgs a{};
+    for (int q = 0; q < 4; ++q) {
+        RestrictField& f = a.f[q];
+        f.src = src[q];
+        f.dst = dst[q];
+        f.ex = gc.nx; f.ey = gc.ny; f.ez = gc.nz;
+        for (int x = 0; x < 3; ++x) f.tab[x] = tab[x];
+        f.mean = mean[q];
+    }
+    return launch_restrict<double>(gf, gc, a, 4, s);
+}
+
+hipError_t launch_mg_prolong_add(const Geom& gf, const Geom& gc, const double* const src[5], double* const dst[5],
                                  hipStream_t s) {
-    const bool fx = kind == 1, fy = kind == 2, fz = kind == 3;
-    hipLaunchKernelGGL(k_mg_prolong_add, grid3(gf.nx + fx, gf.ny + fy, gf.nz + fz), dim3(GX, GY), 0, s, ext(gf),
-                       ext(gc), fx, fy, fz, src, dst);
+    ProlongArgs a{ext(gf), ext(gc), {}, {}};
+    for (int q = 0; q < 5; ++q) {
+        a.src[q] = src[q];
+        a.dst[q] = dst[q];
+    }
+    const dim3 g = grid3(gf.nx + 1, gf.ny + 1, 1);
+    hipLaunchKernelGGL(k_mg_prolong_add, dim3(g.x, g.y, (unsigned)(5 * (gf.nz + 1))), dim3(GX, GY), 0, s, a);
+    return hipGetLastError();
+}
+
+namespace {
+size_t coarsest_lds(const Geom& g) { return (size_t)10 * (g.nx + 2) * (g.ny + 2) * (g.nz + 2) * sizeof(double); }
+}  // namespace
+
+bool mg_coarsest_fits(const Geom& g) {
+    return (int64_t)g.nx * g.ny * g.nz <= 1024 && coarsest_lds(g) <= 150 * 1024;
+}
+
+hipError_t launch_mg_coarsest(const Geom& g, const Coef& c, const SweepPtrs<double>& p, double* const out[5], int n,
+                              hipStream_t s) {
+    CoarseArgs a{};
+    a.nx = g.nx; a.ny = g.ny; a.nz = g.nz; a.n = n;
+    a.P = g.P; a.S = g.S;
+    a.dxi = c.dxi; a.dyi = c.dyi; a.dzi = c.dzi;
+    a.bdt = c.beta_d * c.dti; a.alpha = c.alpha; a.ab = c.ab;
+    a.gdts = c.gdts_inv; a.beta_n = c.beta_n; a.rho_i_inv = c.rho_i_inv;
+    // with the mechanics off V and Pt keep their zero
+    a.dtauv_c = c.mech_off ? 0.0 : c.dtauv_c; a.dtaupt_c = c.mech_off ? 0.0 : c.dtaupt_c; a.dtaupf_c = c.dtaupf_c;
+    a.dampx = c.dampx; a.dampy = c.dampy; a.dampz = c.dampz;
+    a.lp = p.lp; a.kc = p.kc; a.eta = p.eta; a.mus = p.mus;
+    a.fox = p.fox; a.foy = p.foy; a.foz = p.foz; a.pto = p.pto; a.pfo = p.pfo;
+    a.vx = out[0]; a.vy = out[1]; a.vz = out[2]; a.pt = out[3]; a.pf = out[4];
+    const int threads = (g.nx * g.ny * g.nz + 63) / 64 * 64;
+    hipLaunchKernelGGL(k_mg_coarsest, dim3(1), dim3(threads), coarsest_lds(g), s, a);
     return hipGetLastError();
 }
 

@@ -378,29 +378,32 @@ hipError_t launch_exp_cells(const Geom& g, const double* src, double* dst, hipSt
 hipError_t launch_apply_correction(const Geom& g, const MixedPtrs& m, hipStream_t s);
 
 // Multigrid transfers between a fine grid gf and its coarse grid gc
-// (mg_kernels.hip).  kind: 0 cells, 1/2/3 faces normal to x/y/z.
-// Restriction of a cell field: averages (mean 0: arithmetic, 1: harmonic,
-// 2: geometric) of the fine values around each coarse point, by the
-// separable passes below (their scratch and rows).
-hipError_t launch_mg_restrict(const Geom& gf, const Geom& gc, const double* src, double* dst, int mean, double* sa,
-                              double* sb, const double* const tab[3], hipStream_t s);
+// (mg_kernels.hip).
 // Normalised restriction rows of one axis (fine nf, coarse nc points; face:
 // faces normal to the axis): MG_TAB doubles per coarse index (first fine
-// index, count, MG_TAB - 2 weights), nc + face rows.
-constexpr int MG_TAB = 10;
+// index, count, weights), nc + face rows.
+constexpr int MG_TAPS = 4;
+constexpr int MG_TAB = 2 + MG_TAPS;
 hipError_t launch_mg_taps(double* tab, int nf, int nc, int face, hipStream_t s);
-// An FP32 fine field restricted by three separable passes through scratch
-// sa ((nz_f + 1) (ny_f + 1) P_c doubles) and sb ((nz_f + 1) (ny_c + 1) P_c),
-// with the rows of the x, y and z axes for its staggering.
-hipError_t launch_mg_restrict32(const Geom& gf, const Geom& gc, int kind, const float* src, double* dst,
-                                double* sa, double* sb, const double* const tab[3], hipStream_t s);
-// Restricted r_Pt, r_Pf (a, b) -> pto = m[0] a + m[1] b, pfo = m[2] a + m[3] b.
-hipError_t launch_mg_restrict_fold(const Geom& gf, const Geom& gc, const float* rpt, const float* rpf, double* pto,
-                                   double* pfo, const double m[4], double* sa, double* sb, const double* const tab[3],
-                                   hipStream_t s);
-// dst (fine) += interpolated src (coarse); the walls' normal faces are kept.
-hipError_t launch_mg_prolong_add(const Geom& gf, const Geom& gc, int kind, const double* src, double* dst,
+// The fine grid's FP32 residual (momentum rows on the x, y, z faces, r_Pt,
+// r_Pf) restricted to the coarse grid's constant terms: dst[0..2] the
+// momentum rows, dst[3] = m[0] a + m[1] b, dst[4] = m[2] a + m[3] b of the
+// restricted r_Pt, r_Pf (a, b).  tab[axis][face]: the rows of each axis.
+hipError_t launch_mg_residual_restrict(const Geom& gf, const Geom& gc, const float* const res[5], double* const dst[5],
+                                       const double m[4], const double* const tab[3][2], hipStream_t s);
+// Four cell fields averaged onto the coarse grid (mean 0: arithmetic, 1:
+// harmonic, 2: geometric).
+hipError_t launch_mg_coef_restrict(const Geom& gf, const Geom& gc, const double* const src[4], double* const dst[4],
+                                   const int mean[4], const double* const tab[3], hipStream_t s);
+// dst (fine V, Pt, Pf) += interpolated src (coarse); the walls' normal faces
+// are kept.
+hipError_t launch_mg_prolong_add(const Geom& gf, const Geom& gc, const double* const src[5], double* const dst[5],
                                  hipStream_t s);
+// n damped linear PT sweeps from the zero state on a grid of at most 1024
+// cells, in one launch; the result (V, Pt, Pf) to out.
+bool mg_coarsest_fits(const Geom& g);
+hipError_t launch_mg_coarsest(const Geom& g, const Coef& c, const SweepPtrs<double>& p, double* const out[5], int n,
+                              hipStream_t s);
 
 // Krylov acceleration of the multigrid cycle (krylov_kernels.hip): the
 // cycles' iterates recombined over a subspace of their own steps.
