@@ -94,8 +94,6 @@ struct Ext {
 };
 __host__ __device__ inline Ext ext(const Geom& g) { return Ext{g.nx, g.ny, g.nz, g.P, g.S}; }
 
-constexpr int GX = 64, GY = 4;
-
 // The normalised restriction rows of one axis (fine nf, coarse nc points;
 // face: the field sits on faces normal to it, whose wall faces carry no
 // equation: skipped as inputs, rows of no tap for the coarse walls).  A row is
@@ -126,136 +124,214 @@ __global__ __launch_bounds__(TB) void k_mg_taps(double* __restrict__ tab, int nf
         if (!none && q >= first && q - first < n) row[2 + q - first] = tt.w[q] / tt.sum;
 }
 
-// Restriction of up to five fields in one launch.  The restriction is a
-// tensor product of one-dimensional rows of at most four weights, each
-// normalised to sum 1.  A thread owns a coarse column (I, J) of one field and
-// marches up a chunk of coarse planes: it averages each fine plane around
-// (I, J) once (up to 16 values through the caches) and keeps the last four
-// of these averages in registers, from which every coarse plane takes its
-// own; neighbouring threads read the same lines, so the fine field comes from
-// memory about once.  One launch instead of three passes per field through
-// scratch and a fold: on small grids the launches were the cost (127^3: 16
-// launches of 2.4 to 7 us per transfer), on large ones the passes' traffic.
+// Restriction of several fields in one launch.  The restriction is a tensor
+// product of one-dimensional rows of at most four weights, each normalised to
+// sum 1.  A thread owns a coarse column (I, J) of one field (or of a pair of
+// fields whose combinations are wanted) and marches up a chunk of coarse
+// planes: it averages each fine plane around (I, J) once (up to 16 values
+// through the caches) and keeps the last four of these averages, from which
+// every coarse plane takes its own; neighbouring threads read the same lines,
+// so the fine field comes from memory about once.  Bound by the latency of
+// these reads: two fine planes' are in flight at once, columns are dealt out
+// along the rows without gaps (a coarse row seldom fills whole wavefronts),
+// and the chunk's z rows are in LDS.  The five residuals of 300x255x201 in
+// 251 us (820 us with one plane's reads behind a branch at a time), of 127^3 in
+// 43 us (210), of 16^3 in 7.5 us (21).
 // mean (cells): 0 arithmetic, 1 harmonic, 2 geometric, by averaging v, 1/v
-// or ln v.  A field's fine value is src or, with src2, m0 src + m1 src2.
+// or ln v.
 struct RestrictField {
     const void* src;
-    const void* src2;
     double* dst;
     const double* tab[3];
-    double m0, m1;
     int ex, ey, ez;      // coarse extent
     int mean;
 };
 struct RestrictArgs {
-    RestrictField f[5];
+    RestrictField f[4];
+    // with a pair: field 3 and src2 give dst = m[0] f + m[1] f2, dst2 = m[2] f + m[3] f2
+    const void* src2;
+    double* dst2;
+    double m[4];
     int64_t fP, fS, cP, cS;
-    int kc;              // coarse planes per chunk
-    int chunks;
+    int kc;              // coarse planes per chunk (at most MAX_KC)
 };
+constexpr int MAX_KC = 16;
 
-template <typename TI>
-__global__ __launch_bounds__(GX * GY) void k_mg_restrict(RestrictArgs a) {
-    const RestrictField& f = a.f[blockIdx.z / a.chunks];
-    const int I = blockIdx.x * GX + threadIdx.x, J = blockIdx.y * GY + threadIdx.y;
-    const int K0 = (int)(blockIdx.z % a.chunks) * a.kc, K1 = min(f.ez, K0 + a.kc);
-    if (I >= f.ex || J >= f.ey || K0 >= f.ez) return;
-    const TI* src = static_cast<const TI*>(f.src);
-    const TI* src2 = static_cast<const TI*>(f.src2);
+template <typename TI, bool PAIR>
+__device__ __forceinline__ void restrict_column(const RestrictArgs& a, const RestrictField& f, int I, int J, int K0, int K1,
+                                                const double (*rows)[MG_TAB]) {
+    constexpr int NS = PAIR ? 2 : 1, T = MG_TAPS;
+    const TI* __restrict__ src[2] = {static_cast<const TI*>(f.src), static_cast<const TI*>(a.src2)};
     const double* rx = f.tab[0] + (int64_t)I * MG_TAB;
     const double* ry = f.tab[1] + (int64_t)J * MG_TAB;
     const int nx = (int)rx[1], ny = (int)ry[1];
-    double wx[MG_TAPS], wy[MG_TAPS];
-    int64_t ox[MG_TAPS], oy[MG_TAPS];
+    double wx[T], wy[T];
+    int ox[T];
+    int64_t oy[T];
 #pragma unroll
-    for (int q = 0; q < MG_TAPS; ++q) {
+    for (int q = 0; q < T; ++q) {
         // taps past the row's last repeat it with weight 0
         wx[q] = rx[2 + q];
         wy[q] = ry[2 + q];
         ox[q] = (int)rx[0] + max(min(q, nx - 1), 0);
         oy[q] = (int64_t)((int)ry[0] + max(min(q, ny - 1), 0)) * a.fP;
     }
-    auto plane = [&](int k) -> double {
-        const int64_t o = (int64_t)k * a.fS;
-        double r = 0.0;
-#pragma unroll
-        for (int y = 0; y < MG_TAPS; ++y) {
-            double v = 0.0;
-#pragma unroll
-            for (int x = 0; x < MG_TAPS; ++x) {
-                double u = (double)src[o + oy[y] + ox[x]];
-                if (src2) u = f.m0 * u + f.m1 * (double)src2[o + oy[y] + ox[x]];
-                if (f.mean) u = f.mean == 1 ? 1.0 / u : log(u);
-                v += wx[x] * u;
-            }
-            r += wy[y] * v;
-        }
-        return r;
-    };
-    // averages of the fine planes base .. base + 3
-    double s[MG_TAPS] = {};
+    const bool any = nx > 0 && ny > 0;
+    double s[NS][T] = {};      // averages of the fine planes base .. base + have - 1
     int base = 0, have = 0;
     for (int K = K0; K < K1; ++K) {
-        const double* rz = f.tab[2] + (int64_t)K * MG_TAB;
+        const double* rz = rows[K - K0];
         const int lo = (int)rz[0], nz = (int)rz[1];
-        double r = 0.0;
-        if (nx > 0 && ny > 0 && nz > 0) {
-            // keep what the planes before left, drop what lies below lo
+        double r[NS] = {};
+        if (any && nz > 0) {
+            // drop what lies below lo
             const int drop = have ? min(lo - base, have) : 0;
-            for (int d = 0; d < drop; ++d) {
-                s[0] = s[1]; s[1] = s[2]; s[2] = s[3];
-            }
+            for (int d = 0; d < drop; ++d)
+#pragma unroll
+                for (int n = 0; n < NS; ++n) {
+                    s[n][0] = s[n][1]; s[n][1] = s[n][2]; s[n][2] = s[n][3];
+                }
             have -= drop;
             base = lo;
+            while (have < nz) {
+                TI raw[NS][2][T][T];
 #pragma unroll
-            for (int q = 0; q < MG_TAPS; ++q)
-                if (q >= have && q < nz) s[q] = plane(lo + q);
-            have = max(have, nz);
+                for (int n = 0; n < NS; ++n)
 #pragma unroll
-            for (int q = 0; q < MG_TAPS; ++q)
-                if (q < nz) r += rz[2 + q] * s[q];
-            if (f.mean) r = f.mean == 1 ? 1.0 / r : exp(r);
+                    for (int p = 0; p < 2; ++p) {
+                        const int64_t o = (int64_t)(lo + min(have + p, nz - 1)) * a.fS;
+#pragma unroll
+                        for (int y = 0; y < T; ++y)
+#pragma unroll
+                            for (int x = 0; x < T; ++x) raw[n][p][y][x] = src[n][o + oy[y] + ox[x]];
+                    }
+#pragma unroll
+                for (int n = 0; n < NS; ++n)
+#pragma unroll
+                    for (int p = 0; p < 2; ++p) {
+                        double v = 0.0;
+#pragma unroll
+                        for (int y = 0; y < T; ++y) {
+                            double t = 0.0;
+#pragma unroll
+                            for (int x = 0; x < T; ++x) {
+                                double u = (double)raw[n][p][y][x];
+                                if (!PAIR && f.mean) u = f.mean == 1 ? 1.0 / u : log(u);
+                                t += wx[x] * u;
+                            }
+                            v += wy[y] * t;
+                        }
+#pragma unroll
+                        for (int q = 0; q < T; ++q)
+                            if (q == have + p) s[n][q] = v;
+                    }
+                have += 2;
+            }
+            have = nz;
+#pragma unroll
+            for (int n = 0; n < NS; ++n)
+#pragma unroll
+                for (int q = 0; q < T; ++q)
+                    if (q < nz) r[n] += rz[2 + q] * s[n][q];
+            if (!PAIR && f.mean) r[0] = f.mean == 1 ? 1.0 / r[0] : exp(r[0]);
         } else {
             have = 0;
         }
-        f.dst[(int64_t)K * a.cS + (int64_t)J * a.cP + I] = r;
+        const int64_t o = (int64_t)K * a.cS + (int64_t)J * a.cP + I;
+        if (PAIR) {
+            f.dst[o] = a.m[0] * r[0] + a.m[1] * r[NS - 1];
+            a.dst2[o] = a.m[2] * r[0] + a.m[3] * r[NS - 1];
+        } else {
+            f.dst[o] = r[0];
+        }
     }
 }
 
-dim3 grid3(int ex, int ey, int ez) { return dim3((unsigned)((ex + GX - 1) / GX), (unsigned)((ey + GY - 1) / GY), (unsigned)ez); }
+template <typename TI, bool PAIR>
+__global__ __launch_bounds__(TB) void k_mg_restrict(RestrictArgs a) {
+    __shared__ double rows[MAX_KC][MG_TAB];
+    const RestrictField& f = a.f[blockIdx.y];
+    const int K0 = (int)blockIdx.z * a.kc, K1 = min(f.ez, K0 + a.kc);
+    if (K0 >= K1) return;
+    for (int t = threadIdx.x; t < (K1 - K0) * MG_TAB; t += TB) rows[t / MG_TAB][t % MG_TAB] = f.tab[2][(int64_t)K0 * MG_TAB + t];
+    __syncthreads();
+    const unsigned t = blockIdx.x * TB + threadIdx.x;
+    const int J = (int)(t / (unsigned)f.ex), I = (int)(t - (unsigned)J * f.ex);
+    if (J >= f.ey) return;
+    if (PAIR && blockIdx.y == 3)
+        restrict_column<TI, PAIR>(a, f, I, J, K0, K1, rows);
+    else
+        restrict_column<TI, false>(a, f, I, J, K0, K1, rows);
+}
 
 // fine += P coarse for the three velocities and the two pressures, one launch
-// (a block's field and fine plane in its third index); the walls' normal
-// faces keep their values.
+// (a block's field in its second index, its chunk of fine planes in the
+// third); the walls' normal faces keep their values.  A thread owns a fine
+// column and keeps the interpolations within the two coarse planes around
+// its plane, so that a fine value costs its own read and write and about two
+// reads through the caches; four planes' reads are in flight.  Onto
+// 300x255x201 in 274 us, 4.9 TB/s of the fine fields' reads and writes, onto
+// 127^3 in 42 us (about 480 and 70 us for a thread per fine point, which read
+// eight coarse values and divided for its weights).
 struct ProlongArgs {
     Ext f, c;
     const double* src[5];
     double* dst[5];
+    int kc;              // fine planes per chunk (at most MAX_PC)
 };
-__global__ __launch_bounds__(GX * GY) void k_mg_prolong_add(ProlongArgs a) {
+constexpr int MAX_PC = 64;
+__global__ __launch_bounds__(TB) void k_mg_prolong_add(ProlongArgs a) {
+    __shared__ double st[MAX_PC];
+    __shared__ int sz[MAX_PC];
     const Ext& f = a.f;
     const Ext& c = a.c;
-    const int q = blockIdx.z % 5, k = blockIdx.z / 5;
+    const int q = blockIdx.y;
     const bool fx = q == 0, fy = q == 1, fz = q == 2;
-    const int i = blockIdx.x * GX + threadIdx.x, j = blockIdx.y * GY + threadIdx.y;
-    if (i >= f.nx + fx || j >= f.ny + fy || k >= f.nz + fz) return;
-    if ((fx && (i == 0 || i == f.nx)) || (fy && (j == 0 || j == f.ny)) || (fz && (k == 0 || k == f.nz))) return;
-    int x0, y0, z0;
-    double tx, ty, tz;
+    const int K0 = (int)blockIdx.z * a.kc, K1 = min(f.nz + fz, K0 + a.kc);
+    if (K0 >= K1) return;
+    if ((int)threadIdx.x < K1 - K0) pw(K0 + threadIdx.x, f.nz, c.nz, fz, sz[threadIdx.x], st[threadIdx.x]);
+    __syncthreads();
+    const unsigned ex = f.nx + fx, t = blockIdx.x * TB + threadIdx.x;
+    const int j = (int)(t / ex), i = (int)(t - (unsigned)j * ex);
+    if (j >= f.ny + fy || (fx && (i == 0 || i == f.nx)) || (fy && (j == 0 || j == f.ny))) return;
+    int x0, y0;
+    double tx, ty;
     pw(i, f.nx, c.nx, fx, x0, tx);
     pw(j, f.ny, c.ny, fy, y0, ty);
-    pw(k, f.nz, c.nz, fz, z0, tz);
     // the second point of an axis: inside the coarse extent (its weight
     // is zero where the first point is the last one)
-    const int x1 = min(x0 + 1, c.nx - 1 + fx), y1 = min(y0 + 1, c.ny - 1 + fy), z1 = min(z0 + 1, c.nz - 1 + fz);
-    const double* src = a.src[q];
-    auto at = [&](int u, int v, int w) { return src[(int64_t)w * c.S + (int64_t)v * c.P + u]; };
-    const double v0 = (1.0 - tx) * at(x0, y0, z0) + tx * at(x1, y0, z0);
-    const double v1 = (1.0 - tx) * at(x0, y1, z0) + tx * at(x1, y1, z0);
-    const double v2 = (1.0 - tx) * at(x0, y0, z1) + tx * at(x1, y0, z1);
-    const double v3 = (1.0 - tx) * at(x0, y1, z1) + tx * at(x1, y1, z1);
-    const double v = (1.0 - tz) * ((1.0 - ty) * v0 + ty * v1) + tz * ((1.0 - ty) * v2 + ty * v3);
-    a.dst[q][(int64_t)k * f.S + (int64_t)j * f.P + i] += v;
+    const int x1 = min(x0 + 1, c.nx - 1 + fx), y1 = min(y0 + 1, c.ny - 1 + fy), zmax = c.nz - 1 + fz;
+    const double* __restrict__ src = a.src[q];
+    double* __restrict__ dst = a.dst[q] + (int64_t)j * f.P + i;
+    const int64_t o00 = (int64_t)y0 * c.P + x0, o01 = (int64_t)y0 * c.P + x1;
+    const int64_t o10 = (int64_t)y1 * c.P + x0, o11 = (int64_t)y1 * c.P + x1;
+    auto plane = [&](int z) {
+        const double* p = src + (int64_t)z * c.S;
+        const double v0 = (1.0 - tx) * p[o00] + tx * p[o01];
+        const double v1 = (1.0 - tx) * p[o10] + tx * p[o11];
+        return (1.0 - ty) * v0 + ty * v1;
+    };
+    int zc = sz[0];
+    double c0 = plane(zc), c1 = plane(min(zc + 1, zmax));
+    for (int k = K0; k < K1; k += 4) {
+        double d[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) d[u] = dst[(int64_t)min(k + u, K1 - 1) * f.S];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            if (k + u >= K1) break;
+            const int z0 = sz[k + u - K0];
+            const double tz = st[k + u - K0];
+            // (the coarse grid is the coarser one: z0 rises by at most 1)
+            if (z0 != zc) {
+                zc = z0;
+                c0 = c1;
+                c1 = plane(min(zc + 1, zmax));
+            }
+            if (fz && (k + u == 0 || k + u == f.nz)) continue;
+            dst[(int64_t)(k + u) * f.S] = d[u] + ((1.0 - tz) * c0 + tz * c1);
+        }
+    }
 }
 
 // ---- the coarsest grid's damped PT sweeps, in one launch -------------------------
@@ -380,18 +456,22 @@ hipError_t launch_mg_taps(double* tab, int nf, int nc, int face, hipStream_t s) 
 
 namespace {
 
-// Coarse planes per chunk: a chunk's first plane averages four fine planes,
-// the others two, so long chunks read less; short ones give a small grid
-// more blocks (at least two per compute unit while a chunk has a plane).
-template <typename TI>
-hipError_t launch_restrict(const Geom& gf, const Geom& gc, RestrictArgs& a, int n, hipStream_t s) {
+// Planes per chunk: a chunk starts with reads that its neighbour below also
+// makes (two fine planes more than the two per coarse plane), so long chunks
+// read less; short ones give a small grid enough blocks, four per compute
+// unit while a chunk has a plane.
+int chunk(const Geom& g, int64_t planes, int64_t blocks, int most) {
+    const int cus = g.cus > 0 ? g.cus : DEFAULT_CUS;
+    return (int)std::min<int64_t>(most, std::max<int64_t>(1, planes * blocks / (4 * cus)));
+}
+unsigned column_blocks(const Geom& g) { return (unsigned)(((int64_t)(g.nx + 1) * (g.ny + 1) + TB - 1) / TB); }
+
+template <typename TI, bool PAIR>
+hipError_t launch_restrict(const Geom& gf, const Geom& gc, RestrictArgs& a, hipStream_t s) {
     a.fP = gf.P; a.fS = gf.S; a.cP = gc.P; a.cS = gc.S;
-    const dim3 cols = grid3(gc.nx + 1, gc.ny + 1, 1);
-    const int64_t per = (int64_t)cols.x * cols.y * n;
-    const int cus = gf.cus > 0 ? gf.cus : DEFAULT_CUS;
-    a.kc = (int)std::min<int64_t>(16, std::max<int64_t>(1, (int64_t)(gc.nz + 1) * per / (2 * cus)));
-    a.chunks = (gc.nz + a.kc) / a.kc;
-    hipLaunchKernelGGL(k_mg_restrict<TI>, dim3(cols.x, cols.y, (unsigned)(n * a.chunks)), dim3(GX, GY), 0, s, a);
+    const unsigned cols = column_blocks(gc);
+    a.kc = chunk(gf, gc.nz + 1, (int64_t)cols * 4, MAX_KC);
+    hipLaunchKernelGGL((k_mg_restrict<TI, PAIR>), dim3(cols, 4, (unsigned)((gc.nz + a.kc) / a.kc)), dim3(TB), 0, s, a);
     return hipGetLastError();
 }
 
@@ -400,21 +480,17 @@ hipError_t launch_restrict(const Geom& gf, const Geom& gc, RestrictArgs& a, int 
 hipError_t launch_mg_residual_restrict(const Geom& gf, const Geom& gc, const float* const res[5], double* const dst[5],
                                        const double m[4], const double* const tab[3][2], hipStream_t s) {
     RestrictArgs a{};
-    for (int q = 0; q < 5; ++q) {
+    for (int q = 0; q < 4; ++q) {
         RestrictField& f = a.f[q];
+        f.src = res[q];
         f.dst = dst[q];
         f.ex = gc.nx + (q == 0); f.ey = gc.ny + (q == 1); f.ez = gc.nz + (q == 2);
         for (int x = 0; x < 3; ++x) f.tab[x] = tab[x][x == q];
-        if (q < 3) {
-            f.src = res[q];
-        } else {
-            f.src = res[3];
-            f.src2 = res[4];
-            f.m0 = m[2 * (q - 3)];
-            f.m1 = m[2 * (q - 3) + 1];
-        }
     }
-    return launch_restrict<float>(gf, gc, a, 5, s);
+    a.src2 = res[4];
+    a.dst2 = dst[4];
+    for (int q = 0; q < 4; ++q) a.m[q] = m[q];
+    return launch_restrict<float, true>(gf, gc, a, s);
 }
 
 hipError_t launch_mg_coef_restrict(const Geom& gf, const Geom& gc, const double* const src[4], double* const dst[4],
@@ -428,18 +504,21 @@ hipError_t launch_mg_coef_restrict(const Geom& gf, const Geom& gc, const double*
         for (int x = 0; x < 3; ++x) f.tab[x] = tab[x];
         f.mean = mean[q];
     }
-    return launch_restrict<double>(gf, gc, a, 4, s);
+    return launch_restrict<double, false>(gf, gc, a, s);
 }
 
 hipError_t launch_mg_prolong_add(const Geom& gf, const Geom& gc, const double* const src[5], double* const dst[5],
                                  hipStream_t s) {
-    ProlongArgs a{ext(gf), ext(gc), {}, {}};
+    ProlongArgs a{};
+    a.f = ext(gf);
+    a.c = ext(gc);
     for (int q = 0; q < 5; ++q) {
         a.src[q] = src[q];
         a.dst[q] = dst[q];
     }
-    const dim3 g = grid3(gf.nx + 1, gf.ny + 1, 1);
-    hipLaunchKernelGGL(k_mg_prolong_add, dim3(g.x, g.y, (unsigned)(5 * (gf.nz + 1))), dim3(GX, GY), 0, s, a);
+    const unsigned cols = column_blocks(gf);
+    a.kc = chunk(gf, gf.nz + 1, (int64_t)cols * 5, MAX_PC);
+    hipLaunchKernelGGL(k_mg_prolong_add, dim3(cols, 5, (unsigned)((gf.nz + a.kc) / a.kc)), dim3(TB), 0, s, a);
     return hipGetLastError();
 }
 
