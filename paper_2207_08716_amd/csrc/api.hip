@@ -1,4 +1,5 @@
 // Host side of the C ABI declared in include/ptporo.h.
+#include <chrono>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -6,6 +7,7 @@
 #include <algorithm>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "pt_internal.h"
@@ -57,6 +59,10 @@ struct pt_grid {
     int64_t mg_off[PT_MG_MAX_LEVELS] = {};   // doubles before each coarse grid's boxes
     int64_t mg_tail = 0;       // doubles before the restriction rows
     int mg_cur[PT_MG_MAX_LEVELS] = {};   // present copy of the coarse grids' iterated fields
+    // the checks of solves: their number, and the last two's results in host
+    // memory that the device writes
+    int64_t checks = 0;
+    double* slots = nullptr;
     std::string err;
 };
 
@@ -230,7 +236,7 @@ pt_status check_ready(pt_grid* g) {
 // flag: 1], padded to a multiple of 256 bytes.  The flag is set (to 1) by the
 // kernels that write ln(1-phi) where phi leaves (0, 1).
 size_t ws_needed(const pt_grid* g) {
-    const int64_t head = g->tiling.most * NNORM + NNORM + 1;
+    const int64_t head = g->tiling.most * NNORM + NNORM + 1 + GATE_DOUBLES;
     return (size_t)((head + 31) / 32 * 32) * sizeof(double);
 }
 
@@ -238,6 +244,7 @@ double* domain_flag(pt_grid* g) {
     double* a = norm_area(g);
     return a ? a + g->tiling.most * NNORM + NNORM : nullptr;
 }
+double* gate(pt_grid* g) { return domain_flag(g) + 1; }
 
 pt_status clear_domain(pt_grid* g) {
     hipError_t e = launch_fill(domain_flag(g), 0.0, 1, g->stream);
@@ -287,8 +294,21 @@ pt_status reduce_norms(pt_grid* g, int64_t nb) {
     return PT_OK;
 }
 
-pt_status iteration_impl(pt_grid* g, int update_lp, int norms, bool keep_r = false) {
+// The same as a check of a solve behind its gate; the host reads its results
+// with read_check.
+pt_status check_norms(pt_grid* g, int64_t nb, const CheckRule& r) {
+    ++g->checks;
+    hipError_t e = launch_check(norm_area(g), nb, norm_area(g) + g->tiling.most * NNORM, domain_flag(g), gate(g), r,
+                                g->slots + (g->checks & 1) * SLOT_DOUBLES, (double)g->checks, g->stream);
+    if (e != hipSuccess) return hip_fail(g, e, "check");
+    g->norms_pending = true;
+    return PT_OK;
+}
+
+// keep_r: a sweep of a solve, behind its gate; with norms and a rule, a check.
+pt_status iteration_impl(pt_grid* g, int update_lp, int norms, bool keep_r = false, const CheckRule* rule = nullptr) {
     SweepPtrs<double> p = sweep_ptrs(g);
+    if (keep_r) p.gate = gate(g);
     Coef c = g->coef;
     // the damping memory: V - V_prev when the other copy of V is the previous
     // iterate under these pseudo steps, the stored R otherwise; R is stored
@@ -308,7 +328,7 @@ pt_status iteration_impl(pt_grid* g, int update_lp, int norms, bool keep_r = fal
     hipError_t e = launch_iteration(g->geom, g->tiling, c, p, update_lp ? MD_THESIS : MD_LINEAR, norms, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "iteration");
     if (norms) {
-        pt_status st = reduce_norms(g, g->tiling.norms64);
+        pt_status st = rule ? check_norms(g, g->tiling.norms64, *rule) : reduce_norms(g, g->tiling.norms64);
         if (st != PT_OK) return st;
     }
     for (int f = 0; f < PT_NPING; ++f) {
@@ -350,6 +370,16 @@ int64_t mx_stride(const pt_grid* g) { return mx_box(g) + 64; }   // floats
 size_t mx_needed(const pt_grid* g) { return (size_t)(MX_NBOX * mx_stride(g)) * sizeof(float); }
 float* mx(pt_grid* g, int b) { return g->mws + (int64_t)b * mx_stride(g); }
 
+// The eight reduced norms and the domain flag of a check.
+pt_status take_norms(pt_grid* g, const double* host, pt_norms* out) {
+    out->f = host[0]; out->rpt = host[1]; out->rpf = host[2]; out->dl = host[3];
+    out->dpt = host[4]; out->dpf = host[5]; out->dvz = host[6]; out->dv = host[7];
+    for (int q = 0; q < NNORM; ++q)
+        if (!std::isfinite(host[q])) return fail(g, PT_EDIVERGED, "non-finite residual norm");
+    if (host[NNORM] != 0.0) return fail(g, PT_EDOMAIN, "porosity left (0, 1): ln(1-phi) not in (-inf, 0)");
+    return PT_OK;
+}
+
 // The eight reduced norms and the domain flag (copied together).
 pt_status read_norms(pt_grid* g, pt_norms* out) {
     double host[NNORM + 1];
@@ -358,12 +388,56 @@ pt_status read_norms(pt_grid* g, pt_norms* out) {
     const hipError_t es = hipStreamSynchronize(g->stream);   // also on a failed copy: host is local
     if (e == hipSuccess) e = es;
     if (e != hipSuccess) return hip_fail(g, e, "norms copy");
-    out->f = host[0]; out->rpt = host[1]; out->rpf = host[2]; out->dl = host[3];
-    out->dpt = host[4]; out->dpf = host[5]; out->dvz = host[6]; out->dv = host[7];
-    for (int q = 0; q < NNORM; ++q)
-        if (!std::isfinite(host[q])) return fail(g, PT_EDIVERGED, "non-finite residual norm");
-    if (host[NNORM] != 0.0) return fail(g, PT_EDOMAIN, "porosity left (0, 1): ln(1-phi) not in (-inf, 0)");
-    return PT_OK;
+    return take_norms(g, host, out);
+}
+
+// Opens the gate of a solve; the host memory of the checks, one small block
+// per handle, comes with its first solve.
+pt_status open_gate(pt_grid* g) {
+    hipError_t e = hipSuccess;
+    if (!g->slots) {
+        void* m = nullptr;
+        e = hipHostMalloc(&m, 2 * SLOT_DOUBLES * sizeof(double), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent);
+        if (e != hipSuccess) return hip_fail(g, e, "host memory of the checks");
+        g->slots = static_cast<double*>(m);
+        for (int q = 0; q < 2 * SLOT_DOUBLES; ++q) g->slots[q] = 0.0;
+    }
+    e = launch_fill(gate(g), 0.0, 1, g->stream);
+    return e == hipSuccess ? PT_OK : hip_fail(g, e, "gate");
+}
+
+// Waits for check `number` of the handle (one of the last two) and takes its
+// norms; stop: it closed the gate.  Polls the check's number in host memory
+// (the stream already holds the next sweeps), asking the stream now and then
+// so that a device error or a stream that ended without it ends the wait.
+pt_status read_check(pt_grid* g, int64_t number, pt_norms* out, bool* stop) {
+    const double* slot = g->slots + (number & 1) * SLOT_DOUBLES;
+    const double want = (double)number;
+    auto there = [&] {
+        double v;
+        __atomic_load(slot + NNORM + 2, &v, __ATOMIC_ACQUIRE);
+        return v == want;
+    };
+    const auto t0 = std::chrono::steady_clock::now();
+    for (int64_t spins = 0; !there(); ++spins) {
+        if (spins < 4096 || std::chrono::steady_clock::now() - t0 < std::chrono::microseconds(500)) continue;
+        const hipError_t e = hipStreamQuery(g->stream);
+        if (e == hipErrorNotReady) {
+            std::this_thread::sleep_for(std::chrono::microseconds(50));
+            continue;
+        }
+        if (e != hipSuccess) return hip_fail(g, e, "check");
+        if (!there()) return fail(g, PT_EDEVICE, "a check ended without its norms");
+    }
+    *stop = slot[NNORM + 1] != 0.0;
+    return take_norms(g, slot, out);
+}
+
+// The end of a solve that returns to its caller: what was launched behind the
+// closed gate has left the stream.
+pt_status drain(pt_grid* g, pt_status st) {
+    const hipError_t e = hipStreamSynchronize(g->stream);
+    return e == hipSuccess || st < 0 ? st : hip_fail(g, e, "solve");
 }
 
 // Largest value of a cell field (synchronises; uses the norm area, so the
@@ -448,6 +522,7 @@ pt_status pt_create(int32_t nx, int32_t ny, int32_t nz, int64_t row_pitch, const
 }
 
 pt_status pt_destroy(pt_grid* g) {
+    if (g && g->slots) (void)hipHostFree(g->slots);
     delete g;
     return PT_OK;
 }
@@ -625,28 +700,69 @@ pt_status solve_linear_core(pt_grid* g, double rtol, int64_t max_iter, int64_t* 
     const int64_t nup = g->prm.nup;
     double r = INFINITY;
     int64_t it = 0;
-    while (it < max_iter) {
-        ++it;
-        const bool want = (it == 1 && !g->ref_set) || (it % nup == 0);
-        st = iteration_impl(g, 0, want ? 1 : 0, true);
-        if (st != PT_OK) return st;
-        if (!want) continue;
+    auto rho_of = [&](const pt_norms& nm) {
+        r = 0.0;
+        if (g->ref_v > 0.0) r = std::fmax(r, nm.f / g->ref_v);
+        if (g->ref_p > 0.0) r = std::fmax(r, std::fmax(nm.rpt, nm.rpf) / g->ref_p);
+    };
+    st = open_gate(g);
+    if (st != PT_OK) return st;
+    bool done = false;
+    if (!g->ref_set) {
+        // the first sweep's norms are the reference
         pt_norms nm;
+        it = 1;
+        st = iteration_impl(g, 0, 1, true);
+        if (st != PT_OK) return st;
         st = read_norms(g, &nm);
         if (st != PT_OK) {
             if (iters) *iters = it;
             return st;
         }
-        const double gv = nm.f, gp = std::fmax(nm.rpt, nm.rpf);
-        if (!g->ref_set) {
-            g->ref_v = gv;
-            g->ref_p = gp;
-            g->ref_set = true;
+        g->ref_v = nm.f;
+        g->ref_p = std::fmax(nm.rpt, nm.rpf);
+        g->ref_set = true;
+        rho_of(nm);
+        done = it % nup == 0 && r <= rtol;
+    }
+    // the sweeps up to the next check are launched before this check is read;
+    // if it ended the solve they did nothing, and the handle goes back to
+    // where it stood at the check
+    const CheckRule rule{g->ref_v, g->ref_p, rtol, 0.0, 0.0, -1.0, 0, 0};
+    for (int64_t waiting = 0; !done;) {
+        int at_cur[PT_NPING];
+        std::copy(g->cur, g->cur + PT_NPING, at_cur);
+        const int64_t at_it = it, at_iter = g->iter;
+        const bool at_r = g->r_ok, at_vp = g->vp_ok;
+        bool chk = false;
+        while (it < max_iter && !chk) {
+            ++it;
+            chk = it % nup == 0;
+            st = iteration_impl(g, 0, chk ? 1 : 0, true, &rule);
+            if (st != PT_OK) return st;
         }
-        r = 0.0;
-        if (g->ref_v > 0.0) r = std::fmax(r, gv / g->ref_v);
-        if (g->ref_p > 0.0) r = std::fmax(r, gp / g->ref_p);
-        if (it % nup == 0 && r <= rtol) break;
+        const bool last = it == at_it;
+        if (waiting) {
+            pt_norms nm;
+            bool stop = false;
+            st = read_check(g, waiting, &nm, &stop);
+            if (st == PT_OK) rho_of(nm);
+            if (st != PT_OK || stop) {
+                std::copy(at_cur, at_cur + PT_NPING, g->cur);
+                it = at_it;
+                g->iter = at_iter;
+                g->r_ok = at_r;
+                g->vp_ok = at_vp;
+                st = drain(g, st);
+                if (st != PT_OK) {
+                    if (iters) *iters = it;
+                    return st;
+                }
+                break;
+            }
+        }
+        if (last) break;
+        waiting = chk ? g->checks : 0;
     }
     if (iters) *iters = it;
     if (rho) *rho = r;
@@ -659,8 +775,8 @@ pt_status solve_linear_core(pt_grid* g, double rtol, int64_t max_iter, int64_t* 
 // kernel (on the host it is a stand-in, not a device address): the address
 // is looked up once per device with hipGetSymbolAddress, with that device
 // current, and kept here.
-constexpr int64_t STATIC_SCRATCH_DOUBLES = 131072;   // 1 MiB
-__device__ __align__(256) double scratch[STATIC_SCRATCH_DOUBLES];
+constexpr int64_t STATIC_SCRATCH_DOUBLES = 131072;   // 1 MiB for norms and domain flag; the gate follows
+__device__ __align__(256) double scratch[STATIC_SCRATCH_DOUBLES + GATE_DOUBLES];
 constexpr int MAX_DEVICES = 64;
 std::mutex scratch_mutex;
 double* scratch_ptr[MAX_DEVICES] = {};
@@ -873,7 +989,7 @@ namespace {
 // nothing) and stored only by the sweeps that end a check interval or the
 // correction (rwrite); in between the sweep takes it from the two copies of
 // d, three streams fewer.
-pt_status correction_sweep(pt_grid* g, int cp, int cr, int norms, bool rform, bool rwrite) {
+pt_status correction_sweep(pt_grid* g, int cp, int cr, int norms, bool rform, bool rwrite, const CheckRule& rule) {
     SweepPtrs<float> p{};
     const int src = cp ? 8 : 0, dst = cp ? 0 : 8;
     const int rsrc = cr ? 8 : 0, rdst = cr ? 0 : 8;
@@ -891,12 +1007,13 @@ pt_status correction_sweep(pt_grid* g, int cp, int cr, int norms, bool rform, bo
     p.pto = mx(g, MX_RES + 3); p.pfo = mx(g, MX_RES + 4);
     p.kc = mx(g, 21); p.mus = mx(g, 22); p.eta = mx(g, 23);
     p.partials = norm_area(g);
+    p.gate = gate(g);
     Coef c = g->coef;
     c.rform = rform ? 1 : 0;
     c.rwrite = rwrite ? 1 : 0;
     hipError_t e = launch_correction(g->geom, g->tiling, c, p, norms, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "correction sweep");
-    if (norms) return reduce_norms(g, g->tiling.norms32);
+    if (norms) return check_norms(g, g->tiling.norms32, rule);
     return PT_OK;
 }
 
@@ -992,31 +1109,44 @@ pt_status mixed_core(pt_grid* g, const MixedTarget& t, double rtol, double eta_i
         int cp = copy, cr = copy;
         e = hipMemsetAsync(mx(g, cp ? 8 : 0), 0, 5 * box_bytes, g->stream);
         if (e != hipSuccess) return hip_fail(g, e, "correction clear");
-        double best = INFINITY;
-        int since_best = 0;
-        for (int64_t it = 1; it <= max_inner; ++it) {
-            const bool chk = (it % nup == 0);
-            // every exit of this loop follows a check or the last sweep: R_d stored there
-            const bool rwrite = chk || it == max_inner;
-            st = correction_sweep(g, cp, cr, chk ? 1 : 0, it == 1, rwrite);
-            if (st != PT_OK) return st;
-            cp ^= 1;
-            if (rwrite) cr ^= 1;
-            ++inner_total;
-            if (chk) {
-                pt_norms ni;
-                st = read_norms(g, &ni);
+        st = open_gate(g);
+        if (st != PT_OK) return st;
+        CheckRule rule{gv, gp, eta_in, ref_v, ref_p, target_margin * rtol, stall_checks, 1};
+        int64_t it = 0;
+        for (int64_t waiting = 0;;) {
+            // (the sweeps up to the next check before this one is read, as
+            // in solve_linear_core)
+            const int at_cp = cp, at_cr = cr;
+            const int64_t at_it = it;
+            bool chk = false;
+            while (it < max_inner && !chk) {
+                ++it;
+                chk = it % nup == 0;
+                // every exit of this loop follows a check or the last sweep: R_d stored there
+                const bool rwrite = chk || it == max_inner;
+                st = correction_sweep(g, cp, cr, chk ? 1 : 0, it == 1, rwrite, rule);
                 if (st != PT_OK) return st;
-                const double ri = group_rho(ni, gv, gp);
-                if (ri <= eta_in || group_rho(ni, ref_v, ref_p) <= target_margin * rtol) break;
-                if (ri < 0.99 * best) {
-                    best = ri;
-                    since_best = 0;
-                } else if (++since_best >= stall_checks) {
+                cp ^= 1;
+                if (rwrite) cr ^= 1;
+            }
+            if (chk) rule.first = 0;
+            const bool last = it == at_it;
+            if (waiting) {
+                pt_norms ni;
+                bool stop = false;
+                st = read_check(g, waiting, &ni, &stop);
+                if (st != PT_OK) return st;
+                if (stop) {
+                    cp = at_cp;
+                    cr = at_cr;
+                    it = at_it;
                     break;
                 }
             }
+            if (last) break;
+            waiting = chk ? g->checks : 0;
         }
+        inner_total += it;
         const int b = cp ? 8 : 0;
         m.dvx = mx(g, b + 0); m.dvy = mx(g, b + 1); m.dvz = mx(g, b + 2);
         m.dpt = mx(g, b + 3); m.dpf = mx(g, b + 4);
@@ -1167,34 +1297,56 @@ pt_status transposed_solve(pt_grid* g, const double* kc, const double* mus, doub
     double r = 0.0;
     if (ref > 0.0) {
         const int64_t nup = g->prm.nup;
+        const CheckRule rule{ref, ref, rtol, 0.0, 0.0, -1.0, 0, 0};
         r = INFINITY;
-        while (it < max_iter) {
-            ++it;
-            const bool chk = (it % nup == 0);
-            SweepPtrs<double> p{};
-            const int src = cp ? 8 : 0, dst = cp ? 0 : 8;
-            p.vx = ad(g, src + 0); p.vy = ad(g, src + 1); p.vz = ad(g, src + 2);
-            p.pt = ad(g, src + 3); p.pf = ad(g, src + 4);
-            p.rx = ad(g, src + 5); p.ry = ad(g, src + 6); p.rz = ad(g, src + 7);
-            p.vx_o = ad(g, dst + 0); p.vy_o = ad(g, dst + 1); p.vz_o = ad(g, dst + 2);
-            p.pt_o = ad(g, dst + 3); p.pf_o = ad(g, dst + 4);
-            p.rx_o = ad(g, dst + 5); p.ry_o = ad(g, dst + 6); p.rz_o = ad(g, dst + 7);
-            p.fox = ad(g, AD_RHS); p.foy = ad(g, AD_RHS + 1); p.foz = ad(g, AD_RHS + 2);
-            p.pto = ad(g, AD_RHS + 3); p.pfo = ad(g, AD_RHS + 4);
-            p.eta = ad(g, AD_CHI); p.kc = kc; p.mus = mus;
-            p.partials = norm_area(g);
-            e = launch_correction64(g->geom, g->tiling, g->coef, p, chk ? 1 : 0, g->stream);
-            if (e != hipSuccess) return hip_fail(g, e, "adjoint sweep");
-            cp ^= 1;
-            if (chk) {
-                st = reduce_norms(g, g->tiling.norms64);
-                if (st != PT_OK) return st;
+        st = open_gate(g);
+        if (st != PT_OK) return st;
+        for (int64_t waiting = 0;;) {
+            // (the sweeps up to the next check before this one is read, as
+            // in solve_linear_core)
+            const int at_cp = cp;
+            const int64_t at_it = it;
+            bool chk = false;
+            while (it < max_iter && !chk) {
+                ++it;
+                chk = it % nup == 0;
+                SweepPtrs<double> p{};
+                const int src = cp ? 8 : 0, dst = cp ? 0 : 8;
+                p.vx = ad(g, src + 0); p.vy = ad(g, src + 1); p.vz = ad(g, src + 2);
+                p.pt = ad(g, src + 3); p.pf = ad(g, src + 4);
+                p.rx = ad(g, src + 5); p.ry = ad(g, src + 6); p.rz = ad(g, src + 7);
+                p.vx_o = ad(g, dst + 0); p.vy_o = ad(g, dst + 1); p.vz_o = ad(g, dst + 2);
+                p.pt_o = ad(g, dst + 3); p.pf_o = ad(g, dst + 4);
+                p.rx_o = ad(g, dst + 5); p.ry_o = ad(g, dst + 6); p.rz_o = ad(g, dst + 7);
+                p.fox = ad(g, AD_RHS); p.foy = ad(g, AD_RHS + 1); p.foz = ad(g, AD_RHS + 2);
+                p.pto = ad(g, AD_RHS + 3); p.pfo = ad(g, AD_RHS + 4);
+                p.eta = ad(g, AD_CHI); p.kc = kc; p.mus = mus;
+                p.partials = norm_area(g);
+                p.gate = gate(g);
+                e = launch_correction64(g->geom, g->tiling, g->coef, p, chk ? 1 : 0, g->stream);
+                if (e != hipSuccess) return hip_fail(g, e, "adjoint sweep");
+                cp ^= 1;
+                if (chk) {
+                    st = check_norms(g, g->tiling.norms64, rule);
+                    if (st != PT_OK) return st;
+                }
+            }
+            const bool last = it == at_it;
+            if (waiting) {
                 pt_norms nm;
-                st = read_norms(g, &nm);
+                bool stop = false;
+                st = read_check(g, waiting, &nm, &stop);
+                if (st != PT_OK || stop) st = drain(g, st);
                 if (st != PT_OK) return st;
                 r = group_rho(nm, ref, ref);
-                if (r <= rtol) break;
+                if (stop) {
+                    cp = at_cp;
+                    it = at_it;
+                    break;
+                }
             }
+            if (last) break;
+            waiting = chk ? g->checks : 0;
         }
     }
     *lam_copy = cp;

@@ -156,6 +156,7 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
     constexpr bool WNORM = NORMS || RESID;
     constexpr bool LATE_C = UPD_LP;
     constexpr bool RREAD = !RESID && RM != RM_NONE;
+    constexpr bool GATED = (MODE == MD_LINEAR || CORR) && RM != RM_NONE;   // the sweeps of solves
     constexpr int L_S = L_CORE, L_TZZ = L_S + (UPD_LP ? 2 : 0), L_W = L_TZZ + (UPD_LP ? 1 : 0), NPL = L_W + (NORMS ? 1 : 0);
     constexpr int WH = W * H;
     __shared__ T lds[NPL * WH + 2 * (W + 1)];
@@ -598,6 +599,13 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
         // step waits for its loads as every other does
         store(p, p0, false, OSet{});
         load_f(p, p0, ff);
+        if constexpr (GATED) {
+            // behind a closed gate the block ends here; its first loads are
+            // under way while the gate's value comes
+            const auto* gate = (const __attribute__((address_space(4))) double*)p->gate;
+            asm volatile("" ::: "memory");
+            if (gate && *gate != 0.0) return;
+        }
         vx_c = qb.vx; vy_c = qb.vy; vz_c = qb.vz; pf_c = qb.pf; kc_c = qb.kc; lp_c = qb.lp; mu_c = qb.mu;
         s_c = solid(lp_c);
     }
@@ -641,8 +649,7 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
 // The eight maxima over the blocks' partial ones, one block: thread t takes
 // norm t mod 8 of every 128th block, so that a wave reads whole lines.
 constexpr int RT = 1024;
-__global__ __launch_bounds__(RT) void k_reduce_max(const double* __restrict__ part, int64_t nb,
-                                                   double* __restrict__ out) {
+__device__ __forceinline__ double reduce_max(const double* __restrict__ part, int64_t nb) {
     __shared__ double red[RT / 64][NNORM];
     double m = 0.0;
     const int64_t n = nb * NNORM;
@@ -651,11 +658,61 @@ __global__ __launch_bounds__(RT) void k_reduce_max(const double* __restrict__ pa
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     if (lane < NNORM) red[wave][lane] = m;
     __syncthreads();
-    if (threadIdx.x < NNORM) {
-        double v = 0.0;
+    double v = 0.0;
+    if (threadIdx.x < NNORM)
         for (int w = 0; w < RT / 64; ++w) v = nanmax(v, red[w][threadIdx.x]);
-        out[threadIdx.x] = v;
+    return v;   // of thread q < NNORM: norm q
+}
+
+__global__ __launch_bounds__(RT) void k_reduce_max(const double* __restrict__ part, int64_t nb,
+                                                   double* __restrict__ out) {
+    const double v = reduce_max(part, nb);
+    if (threadIdx.x < NNORM) out[threadIdx.x] = v;
+}
+
+// A check of a solve (see CheckRule).  The host waits for the number, which
+// is written after the rest, not for a copy and the stream.
+__global__ __launch_bounds__(RT) void k_check(const double* __restrict__ part, int64_t nb, double* __restrict__ out,
+                                              const double* __restrict__ domain, double* __restrict__ gate, CheckRule r,
+                                              double* __restrict__ slot, double number) {
+    if (gate[0] != 0.0) return;
+    const double v = reduce_max(part, nb);
+    if (threadIdx.x >= 64) return;
+    double n[NNORM];
+    bool finite = true;
+    for (int q = 0; q < NNORM; ++q) {
+        n[q] = __shfl(v, q, 64);
+        finite = finite && isfinite(n[q]);
     }
+    if (threadIdx.x != 0) return;
+    auto rho = [&](double gv, double gp) {
+        double x = 0.0;
+        if (gv > 0.0) x = fmax(x, n[0] / gv);
+        if (gp > 0.0) x = fmax(x, fmax(n[1], n[2]) / gp);
+        return x;
+    };
+    const double flag = *domain;
+    const double now = rho(r.ref_v, r.ref_p);
+    bool stop = !finite || flag != 0.0 || now <= r.tol || rho(r.ref_v2, r.ref_p2) <= r.tol2;
+    if (!stop && r.stall > 0) {
+        const double best = r.first ? INFINITY : gate[1];
+        if (now < 0.99 * best) {
+            gate[1] = now;
+            gate[2] = 0.0;
+        } else {
+            const double since = (r.first ? 0.0 : gate[2]) + 1.0;
+            gate[2] = since;
+            stop = since >= (double)r.stall;
+        }
+    }
+    if (stop) gate[0] = 1.0;
+    for (int q = 0; q < NNORM; ++q) {
+        out[q] = n[q];
+        slot[q] = n[q];
+    }
+    slot[NNORM] = flag;
+    slot[NNORM + 1] = stop ? 1.0 : 0.0;
+    __hip_atomic_store(slot + NNORM + 2, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 }  // namespace
@@ -741,6 +798,12 @@ hipError_t launch_thesis(const Geom& g, const Tiling& t, const Coef& c, const Sw
 
 hipError_t launch_reduce_max(const double* partials, int64_t nblocks, double* out8, hipStream_t s) {
     hipLaunchKernelGGL(k_reduce_max, dim3(1), dim3(RT), 0, s, partials, nblocks, out8);
+    return hipGetLastError();
+}
+
+hipError_t launch_check(const double* partials, int64_t nblocks, double* out8, const double* domain, double* gate,
+                        const CheckRule& r, double* slot, double number, hipStream_t s) {
+    hipLaunchKernelGGL(k_check, dim3(1), dim3(RT), 0, s, partials, nblocks, out8, domain, gate, r, slot, number);
     return hipGetLastError();
 }
 #endif
