@@ -261,9 +261,9 @@ pt_status refresh_impl(pt_grid* g, double r_eta, double r_mu) {
     g->vp_ok = false;
     const RefreshCoef r = make_refresh(g, r_eta, r_mu);
     const AuxPtrs a = aux(g);
-    hipError_t e = launch_refresh(g->geom, g->coef, r, a, g->stream);
+    hipError_t e = launch_refresh(g->geom, g->tiling.shape[SK_F64], g->coef, r, a, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "refresh");
-    e = launch_fo(g->geom, g->coef, r, a, g->stream);
+    e = launch_fo_tiled(g->geom, g->tiling.shape[SK_F64], g->coef, r, a, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "fo");
     g->refreshed = true;
     return PT_OK;
@@ -622,7 +622,7 @@ pt_status pt_begin_step(pt_grid* g, int32_t update_history) {
     if (update_history || rule) {
         // the folded history term with this step's Maxwell coefficients
         const RefreshCoef r = make_refresh(g, 1.0, 1.0);
-        e = launch_fo(g->geom, g->coef, r, a, g->stream);
+        e = launch_fo_tiled(g->geom, g->tiling.shape[SK_F64], g->coef, r, a, g->stream);
         if (e != hipSuccess) return hip_fail(g, e, "fo");
     }
     g->steps += 1;

@@ -377,14 +377,11 @@ hipError_t launch_begin_step(const Geom& g, const Coef& c, const AuxPtrs& a, int
     return hipGetLastError();
 }
 
-hipError_t launch_refresh(const Geom& g, const Coef& c, const RefreshCoef& r, const AuxPtrs& a, hipStream_t s) {
-    if (r.powerlaw || r.dpcap) return launch_refresh_tiled(g, c, r, a, s);
+hipError_t launch_refresh(const Geom& g, const TileShape& t, const Coef& c, const RefreshCoef& r, const AuxPtrs& a,
+                          hipStream_t s) {
+    if (r.powerlaw || r.dpcap) return launch_refresh_tiled(g, t, c, r, a, s);
     hipLaunchKernelGGL(k_refresh, box_grid(g), dim3(AB), 0, s, g, c, r, a);
     return hipGetLastError();
-}
-
-hipError_t launch_fo(const Geom& g, const Coef& c, const RefreshCoef& r, const AuxPtrs& a, hipStream_t s) {
-    return launch_fo_tiled(g, c, r, a, s);
 }
 
 hipError_t launch_porosity_step(const Geom& g, const Coef& c, const AuxPtrs& a, hipStream_t s) {

@@ -38,6 +38,15 @@ __device__ __forceinline__ double quot(double a, double b) {
     const double q = a * y;
     return __builtin_amdgcn_div_fixup(__builtin_fma(__builtin_fma(-b, q, a), y, q), b, a);
 }
+// Two quotients by the same divisor.
+__device__ __forceinline__ void quot2(double a, double b, double d, double& qa, double& qb) {
+    double y = __builtin_amdgcn_rcp(d);
+    y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+    y = __builtin_fma(__builtin_fma(-d, y, 1.0), y, y);
+    const double p = a * y, q = b * y;
+    qa = __builtin_amdgcn_div_fixup(__builtin_fma(__builtin_fma(-d, p, a), y, p), d, a);
+    qb = __builtin_amdgcn_div_fixup(__builtin_fma(__builtin_fma(-d, q, b), y, q), d, b);
+}
 __device__ __forceinline__ float quot(float a, float b) {
     float y = __builtin_amdgcn_rcpf(b);
     y = __builtin_fmaf(__builtin_fmaf(-b, y, 1.0f), y, y);

@@ -359,13 +359,14 @@ struct RefreshCoef {
 
 hipError_t launch_begin_step(const Geom& g, const Coef& c, const AuxPtrs& a, int update_history,
                              hipStream_t s);
-hipError_t launch_refresh(const Geom& g, const Coef& c, const RefreshCoef& r, const AuxPtrs& a,
+// t: the tile of the grid's plain FP64 sweeps (refresh with the stress
+// invariant, history divergence).
+hipError_t launch_refresh(const Geom& g, const TileShape& t, const Coef& c, const RefreshCoef& r, const AuxPtrs& a,
                           hipStream_t s);
-hipError_t launch_refresh_tiled(const Geom& g, const Coef& c, const RefreshCoef& r, const AuxPtrs& a,
+hipError_t launch_refresh_tiled(const Geom& g, const TileShape& t, const Coef& c, const RefreshCoef& r, const AuxPtrs& a,
                                 hipStream_t s);
-hipError_t launch_fo_tiled(const Geom& g, const Coef& c, const RefreshCoef& r, const AuxPtrs& a, hipStream_t s);
-hipError_t launch_fo(const Geom& g, const Coef& c, const RefreshCoef& r, const AuxPtrs& a,
-                     hipStream_t s);
+hipError_t launch_fo_tiled(const Geom& g, const TileShape& t, const Coef& c, const RefreshCoef& r, const AuxPtrs& a,
+                           hipStream_t s);
 hipError_t launch_porosity_step(const Geom& g, const Coef& c, const AuxPtrs& a, hipStream_t s);
 hipError_t launch_copy(const double* src, double* dst, int64_t n, hipStream_t s);
 // ln(1-phi) and its old value from a porosity field; domain <- 1 where phi is
