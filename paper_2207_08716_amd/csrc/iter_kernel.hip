@@ -155,7 +155,6 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
     constexpr bool RESID = (MODE == MD_RESID);
     constexpr bool CORR = (MODE == MD_CORR);
     constexpr bool WNORM = NORMS || RESID;
-    constexpr bool LATE_C = UPD_LP;
     constexpr bool RREAD = !RESID && RM != RM_NONE;
     constexpr bool GATED = (MODE == MD_LINEAR || CORR) && RM != RM_NONE;   // the sweeps of solves
     constexpr int L_DTV = L_CORE, L_S = L_DTV + (RESID ? 0 : 2), L_TZZ = L_S + (UPD_LP ? 2 : 0), L_W = L_TZZ + (UPD_LP ? 1 : 0), NPL = L_W + (NORMS ? 1 : 0);
@@ -242,6 +241,10 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
         q.vy = ldp(p->vy + o, nb, o_vy);
         q.vz = ldp(p->vz + o, nbz, o_cell);
         q.pf = ldp(p->pf + o, nb, o_near);
+    };
+    auto load_q2 = [&](KPtrs* p, int k, QSet& q) {
+        const int64_t o = (int64_t)k * g.S + tile0;
+        const u32 nb = (k >= 0 && k < g.nz) ? tile_bytes : 0u;
         q.kc = ldp(p->kc + o, nb, o_near);
         q.mu = ldp(p->mus + o, nb, o_cell);
         if constexpr (CORR) q.lp = zero;
@@ -322,10 +325,17 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
 
     FSet ff;   // face set of plane p, loaded at the end of the step before
 
-    // One plane step: the loads of the next step go to qnn and cn, plane
-    // pz + 1 of the queue is in qn, the cell set of plane pz in cc (both
-    // loaded one step ahead).
-    auto step = [&](int pz, const QSet& qn, QSet& qnn, CSet& cc, CSet& cn) __attribute__((always_inline)) {
+    // One plane step: plane pz + 1 of the queue is in qn, the cell set of
+    // plane pz in cc (both loaded one step ahead), the queue's loads of the
+    // next step go to qnn.  The loads are issued in four groups over the step
+    // (the queue's before and after the first barrier, the cell set's before
+    // the second, the face set's at the end): issued together at its start
+    // they hold the waves up until the memory pipeline has taken them
+    // (measured, together -> spread: linear sweep without damping 127^3 72.7 ->
+    // 58.3 us, 300x255x201 555 -> 490 us; thesis 173x131x97 104 -> 97 us,
+    // 255x255x510 1255 -> 1203 us, 511^3 4.76 -> 4.71 ms; FP32 95^3 17.6 ->
+    // 16.7 us).
+    auto step = [&](int pz, const QSet& qn, QSet& qnn, CSet& cc) __attribute__((always_inline)) {
         const bool plc = pz >= 0;                // plane pz is a real plane
         const bool pln = pz + 1 < g.nz;          // plane pz+1 is a real plane
         const bool live = pz >= kz0;             // outputs of this plane belong to the block
@@ -334,7 +344,6 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
 
         // prefetch what the next step needs
         load_q(p, pz + 2, qnn);
-        if constexpr (!LATE_C) load_c(p, pz + 1, cn);
 
         const T vx_n = qn.vx, vy_n = qn.vy, vz_n = qn.vz, pf_n = qn.pf, kc_n = qn.kc;
         const T lp_n = qn.lp, mu_n = qn.mu;
@@ -350,6 +359,7 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
         sh(L_MU, 0, 0) = mu_c;
         sh(L_MU1, 0, 0) = mu_n;
         __syncthreads();
+        load_q2(ptrs(), pz + 2, qnn);
 
         // Cells outside the domain compute values from zeros that nothing
         // reads but the faces on the walls, which are not stored.
@@ -500,7 +510,7 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
         if constexpr (NORMS) sh(L_W, 0, 0) = w;
         sh(L_TXZ + bn, 0, 0) = txz_n;
         sh(L_TYZ + bn, 0, 0) = tyz_n;
-        if constexpr (LATE_C) load_c(ptrs(), pz + 1, cc);
+        load_c(ptrs(), pz + 1, cc);
         __syncthreads();
 
         // ---- momentum (eq (19)) and damped velocity update on the tile ----
@@ -592,13 +602,15 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
     // register sets: no copy of a set still being loaded makes the wave wait
     // for it at the end of a step.
     QSet qa, qb;
-    CSet ca, cb;
+    CSet cs;
     {
         const int p0 = kz0 - 1;
         KPtrs* const p = ptrs();
         load_q(p, p0, qb);
+        load_q2(p, p0, qb);
         load_q(p, p0 + 1, qa);
-        load_c(p, p0, ca);
+        load_q2(p, p0 + 1, qa);
+        load_c(p, p0, cs);
         // as many (empty) stores as a step ends with, so that the first
         // step waits for its loads as every other does
         store(p, p0, false, OSet{});
@@ -614,10 +626,9 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
         s_c = solid(lp_c);
     }
     for (int pz = kz0 - 1; pz < kz1; pz += 2) {
-        step(pz, qa, qb, ca, cb);
+        step(pz, qa, qb, cs);
         if (pz + 1 >= kz1) break;
-        if constexpr (LATE_C) step(pz + 1, qb, qa, ca, ca);
-        else step(pz + 1, qb, qa, cb, ca);
+        step(pz + 1, qb, qa, cs);
     }
 
     if constexpr (WNORM) {

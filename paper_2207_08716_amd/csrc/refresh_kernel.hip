@@ -371,7 +371,6 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H)) void k_fo_tiled(RefreshA
         const bool live = pz >= at.kz0;
         KAux* const p = fields();
         load_q(p, pz + 2, qnn);
-        load_c(p, pz + 1, cn);
 
         const double mu_n = mus_of(qn.mn);
         const double a_c = maxwell_a(mu_c, c.gdts_inv);
@@ -381,6 +380,7 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H)) void k_fo_tiled(RefreshA
         sh(L_ASX, 0, 0) = asx;
         sh(L_ASY, 0, 0) = asy;
         __syncthreads();
+        load_c(fields(), pz + 1, cn);
 
         const int lv = pz + 1;
         double e_xy = 0.0, e_xz = 0.0, e_yz = 0.0;
