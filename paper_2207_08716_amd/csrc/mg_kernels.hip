@@ -99,7 +99,10 @@ __host__ __device__ inline Ext ext(const Geom& g) { return Ext{g.nx, g.ny, g.nz,
 // equation: skipped as inputs, rows of no tap for the coarse walls).  A row is
 // the first fine index, the number of taps and MG_TAPS weights.  The weights
 // of linear interpolation at a ratio of at most 2 are zero outside an open
-// interval 4 fine points wide, so at most MG_TAPS of them are not.
+// interval 4 fine points wide, so at most MG_TAPS of them are not.  A row
+// starts MG_TAPS points before the end of the axis at the latest (taps of
+// weight 0 in front), so that the MG_TAPS values from its first index on
+// always belong to the field (a fine grid has at least 4 cells per axis).
 __global__ __launch_bounds__(TB) void k_mg_taps(double* __restrict__ tab, int nf, int nc, bool face) {
     const int J = blockIdx.x * TB + threadIdx.x;
     if (J > nc - 1 + face) return;
@@ -114,14 +117,15 @@ __global__ __launch_bounds__(TB) void k_mg_taps(double* __restrict__ tab, int nf
             if (last < 0) first = q;
             last = q;
         }
-    const int n = none ? 0 : min(last - first + 1, MG_TAPS);
-    row[0] = none ? min(max(tt.lo, 0), nf - 1) : tt.lo + first;
+    const int at = min(max(tt.lo + first, 0), nf + face - MG_TAPS), pad = tt.lo + first - at;
+    const int n = none ? 0 : min(last - first + 1 + pad, MG_TAPS);
+    row[0] = at;
     row[1] = n;
 #pragma unroll
     for (int q = 0; q < MG_TAPS; ++q) row[2 + q] = 0.0;
 #pragma unroll
     for (int q = 0; q < MAXT; ++q)
-        if (!none && q >= first && q - first < n) row[2 + q - first] = tt.w[q] / tt.sum;
+        if (!none && q >= first && q - first + pad < n) row[2 + q - first + pad] = tt.w[q] / tt.sum;
 }
 
 // Restriction of several fields in one launch.  The restriction is a tensor
@@ -132,11 +136,12 @@ __global__ __launch_bounds__(TB) void k_mg_taps(double* __restrict__ tab, int nf
 // through the caches) and keeps the last four of these averages, from which
 // every coarse plane takes its own; neighbouring threads read the same lines,
 // so the fine field comes from memory about once.  Bound by the latency of
-// these reads: two fine planes' are in flight at once, columns are dealt out
-// along the rows without gaps (a coarse row seldom fills whole wavefronts),
-// and the chunk's z rows are in LDS.  The five residuals of 300x255x201 in
-// 251 us (820 us with one plane's reads behind a branch at a time), of 127^3 in
-// 43 us (210), of 16^3 in 7.5 us (21).
+// these reads: a row's four values come as one load, two fine planes' are in
+// flight at once, columns are dealt out along the rows without gaps (a coarse
+// row seldom fills whole wavefronts), and the chunk's z rows are in LDS.  The five residuals of 300x255x201 in
+// 133 us, of 127^3 in 28 us, of 16^3 in 6.3 us (251, 43 and 7.5 us with a load
+// per value; 820, 210 and 21 us with one plane's loads behind a branch at a
+// time).
 // mean (cells): 0 arithmetic, 1 harmonic, 2 geometric, by averaging v, 1/v
 // or ln v.
 struct RestrictField {
@@ -166,15 +171,12 @@ __device__ __forceinline__ void restrict_column(const RestrictArgs& a, const Res
     const double* ry = f.tab[1] + (int64_t)J * MG_TAB;
     const int nx = (int)rx[1], ny = (int)ry[1];
     double wx[T], wy[T];
-    int ox[T];
     int64_t oy[T];
 #pragma unroll
     for (int q = 0; q < T; ++q) {
-        // taps past the row's last repeat it with weight 0
         wx[q] = rx[2 + q];
         wy[q] = ry[2 + q];
-        ox[q] = (int)rx[0] + max(min(q, nx - 1), 0);
-        oy[q] = (int64_t)((int)ry[0] + max(min(q, ny - 1), 0)) * a.fP;
+        oy[q] = (int64_t)((int)ry[0] + q) * a.fP + (int)rx[0];
     }
     const bool any = nx > 0 && ny > 0;
     double s[NS][T] = {};      // averages of the fine planes base .. base + have - 1
@@ -201,9 +203,7 @@ __device__ __forceinline__ void restrict_column(const RestrictArgs& a, const Res
                     for (int p = 0; p < 2; ++p) {
                         const int64_t o = (int64_t)(lo + min(have + p, nz - 1)) * a.fS;
 #pragma unroll
-                        for (int y = 0; y < T; ++y)
-#pragma unroll
-                            for (int x = 0; x < T; ++x) raw[n][p][y][x] = src[n][o + oy[y] + ox[x]];
+                        for (int y = 0; y < T; ++y) __builtin_memcpy(raw[n][p][y], src[n] + o + oy[y], sizeof raw[n][p][y]);
                     }
 #pragma unroll
                 for (int n = 0; n < NS; ++n)
