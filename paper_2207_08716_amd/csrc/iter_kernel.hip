@@ -25,8 +25,9 @@
 //      low halo, shear stresses on edges, and Pf', ln(1-phi)' on the tile;
 //   3. after one more barrier, updates the three face velocities of every
 //      tile cell.
-// The next plane's loads are issued one step ahead.  Stresses and Darcy
-// fluxes never touch HBM; the iterated fields are written once.
+// The next plane's loads are issued one step ahead, in groups over the step.
+// Stresses and Darcy fluxes never touch HBM; the iterated fields are written
+// once.
 //
 // What bounds it: HBM on large grids (the 24 streams of a thesis sweep, at
 // the rate that many concurrent streams reach), one wave's chain of dependent
@@ -41,12 +42,13 @@
 //   - two steps per loop round on alternating register sets, so that no loaded
 //     value is copied before it is needed;
 //   - field pointers come from the argument segment at each step, constants
-//     combined on the host, divisions without operand rescaling: 397 vector
-//     instructions per plane step of the linear sweep instead of 640.
-// Measured at 511^3 (before -> after): thesis sweep 6.17 -> 5.59 ms, with
-// norms 8.75 -> 6.73, linear 5.68 -> 5.00, residual 6.47 -> 4.40, FP32
-// correction 2.67 -> 2.52; at 32^3 thesis 27.1 -> 22.3 us.  Small grids gain
-// more from their tiles (sweep_shape, pt_internal.h): 32^3 thesis 22.3 -> 7.7.
+//     combined on the host, divisions without operand rescaling, one
+//     pseudo-step quotient per cell: 355 vector instructions per plane step of
+//     the linear sweep instead of 640.
+// Measured at 511^3 (before all of this -> now): thesis sweep 6.17 -> 4.77 ms
+// (5.7 TB/s of its 24 streams; a copy reaches 6.0), with norms 8.75 -> 6.49,
+// linear 5.68 -> 4.39, residual 6.47 -> 3.78, FP32 correction 2.67 -> 2.21; at
+// 32^3, mostly by its tile (sweep_shape, pt_internal.h), thesis 27.1 -> 7.7 us.
 //
 // Damped velocity update of the FP64 sweeps (eq (19) with the script's
 // damping): R' = f/rho_i + d R, V' = V + dtau_V R'.  Between checks the

@@ -26,7 +26,7 @@ from collections import defaultdict
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 KERNEL_SRC = os.path.join(ROOT, "paper_2207_08716_amd", "csrc", "iter_kernel.hip")
-DOMINANT = "k_sweep<double, 0, false"   # thesis sweep without norms
+DOMINANT = "k_sweep<double, 0, false, 0"   # thesis sweep between checks
 COPY = "k_copy"
 
 
@@ -101,7 +101,7 @@ if __name__ == "__main__":
         nx, ny, nz = (int(v) for v in sys.argv[4:7])
         pitch = ((nx + 1 + 31) // 32) * 32
         traffic_summary(sys.argv[2], sys.argv[3], nx, sys.argv[7], sys.argv[8], " ".join(sys.argv[9:]),
-                        copy_elems=(nz + 1) * (ny + 1) * pitch, dominant="k_waves_sweep<false>",
+                        copy_elems=(nz + 1) * (ny + 1) * pitch, dominant="k_waves_sweep<false",
                         a_eff=11 * nx * ny * nz * 8, grid=f"{nx}x{ny}x{nz}",
                         kernel_src=os.path.join(ROOT, "paper_2207_08716_amd", "csrc", "waves.hip"))
     else:
