@@ -96,7 +96,8 @@ inline int64_t tiles_xy(const Geom& g, int bx = BX, int by = BY) {
 // Planes per z chunk for a tiling: the sweep blocks occupy one CU each, so a
 // launch takes ceil(blocks / CUs) rounds of (chunk + 2) plane steps (two
 // planes of halo and prefetch per chunk); the chunk minimising that wins,
-// the longer one on ties.
+// the longer one on ties.  (Serves the preference among the FP32 tiles and the
+// grids that the static scratch refuses; the launches take pick_tile's chunks.)
 inline int choose_kz(const Geom& g, int bx, int by, int64_t* cost_out = nullptr) {
     const int64_t t = tiles_xy(g, bx, by);
     int best = KZ_MAX;
