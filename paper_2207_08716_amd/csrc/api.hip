@@ -433,8 +433,10 @@ pt_status read_check(pt_grid* g, int64_t number, pt_norms* out, bool* stop) {
     return take_norms(g, slot, out);
 }
 
-// The end of a solve that returns to its caller: what was launched behind the
-// closed gate has left the stream.
+// The end of a solve, on every way out of it: its sweeps have left the stream,
+// those behind a closed gate and, at an iteration limit between two checks,
+// those past the last check.  Both read the gate, which is the caller's
+// memory or the static scratch again once the solve has returned.
 pt_status drain(pt_grid* g, pt_status st) {
     const hipError_t e = hipStreamSynchronize(g->stream);
     return e == hipSuccess || st < 0 ? st : hip_fail(g, e, "solve");
@@ -693,10 +695,8 @@ pt_status pt_last_norms(pt_grid* g, pt_norms* out) {
 }  // extern "C"
 
 namespace {
-// The linear solve of pt_solve_linear on whatever norm area is in force.
-pt_status solve_linear_core(pt_grid* g, double rtol, int64_t max_iter, int64_t* iters, double* rho) {
-    pt_status st = check_ready(g);
-    if (st != PT_OK) return st;
+// The sweeps of solve_linear_core.
+pt_status linear_sweeps(pt_grid* g, double rtol, int64_t max_iter, int64_t* iters, double* rho) {
     const int64_t nup = g->prm.nup;
     double r = INFINITY;
     int64_t it = 0;
@@ -705,7 +705,7 @@ pt_status solve_linear_core(pt_grid* g, double rtol, int64_t max_iter, int64_t* 
         if (g->ref_v > 0.0) r = std::fmax(r, nm.f / g->ref_v);
         if (g->ref_p > 0.0) r = std::fmax(r, std::fmax(nm.rpt, nm.rpf) / g->ref_p);
     };
-    st = open_gate(g);
+    pt_status st = open_gate(g);
     if (st != PT_OK) return st;
     bool done = false;
     if (!g->ref_set) {
@@ -753,7 +753,6 @@ pt_status solve_linear_core(pt_grid* g, double rtol, int64_t max_iter, int64_t* 
                 g->iter = at_iter;
                 g->r_ok = at_r;
                 g->vp_ok = at_vp;
-                st = drain(g, st);
                 if (st != PT_OK) {
                     if (iters) *iters = it;
                     return st;
@@ -767,6 +766,13 @@ pt_status solve_linear_core(pt_grid* g, double rtol, int64_t max_iter, int64_t* 
     if (iters) *iters = it;
     if (rho) *rho = r;
     return (r <= rtol) ? PT_OK : PT_ENOTCONV;
+}
+
+// The linear solve of pt_solve_linear on whatever norm area is in force.
+pt_status solve_linear_core(pt_grid* g, double rtol, int64_t max_iter, int64_t* iters, double* rho) {
+    const pt_status st = check_ready(g);
+    if (st != PT_OK) return st;
+    return drain(g, linear_sweeps(g, rtol, max_iter, iters, rho));
 }
 
 // ---- the static scratch of pt_solve_linear_static -------------------------
@@ -818,10 +824,13 @@ pt_status pt_solve_linear_static(pt_grid* g, double rtol, int64_t max_iter, int6
     pt_status st = static_scratch(g, &sp);
     if (st != PT_OK) return st;
     g->nw = sp;
+    st = check_ready(g);
     // the domain flag must start at zero (the linear sweep never sets it);
     // a fill kernel, so that the call can sit in a captured graph
-    hipError_t e = launch_fill(domain_flag(g), 0.0, 1, g->stream);
-    if (e != hipSuccess) st = hip_fail(g, e, "static scratch clear");
+    if (st == PT_OK) {
+        const hipError_t e = launch_fill(domain_flag(g), 0.0, 1, g->stream);
+        if (e != hipSuccess) st = hip_fail(g, e, "static scratch clear");
+    }
     if (st == PT_OK) st = solve_linear_core(g, rtol, max_iter, iters, rho);
     // the norms of the last check stay readable only until the next call
     // that computes norms into the bound workspace
@@ -1277,8 +1286,8 @@ pt_status misfit_impl(pt_grid* g, const int64_t* sensors, int32_t ns, const doub
 // correction sweep (J_F is symmetric).  lambda starts at zero; convergence
 // when both residual groups fall to rtol times max|xbar|.  Returns the copy
 // (0 or 1) holding lambda.
-pt_status transposed_solve(pt_grid* g, const double* kc, const double* mus, double rtol, int64_t max_iter,
-                           int* lam_copy, int64_t* iters, double* rho) {
+pt_status transposed_sweeps(pt_grid* g, const double* kc, const double* mus, double rtol, int64_t max_iter,
+                            int* lam_copy, int64_t* iters, double* rho) {
     const int64_t box_bytes = ad_stride(g) * (int64_t)sizeof(double);
     hipError_t e = hipMemsetAsync(ad(g, 0), 0, 16 * box_bytes, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "adjoint clear");
@@ -1336,7 +1345,6 @@ pt_status transposed_solve(pt_grid* g, const double* kc, const double* mus, doub
                 pt_norms nm;
                 bool stop = false;
                 st = read_check(g, waiting, &nm, &stop);
-                if (st != PT_OK || stop) st = drain(g, st);
                 if (st != PT_OK) return st;
                 r = group_rho(nm, ref, ref);
                 if (stop) {
@@ -1353,6 +1361,10 @@ pt_status transposed_solve(pt_grid* g, const double* kc, const double* mus, doub
     if (iters) *iters += it;
     if (rho) *rho = std::fmax(*rho, r);
     return (r <= rtol) ? PT_OK : PT_ENOTCONV;
+}
+pt_status transposed_solve(pt_grid* g, const double* kc, const double* mus, double rtol, int64_t max_iter,
+                           int* lam_copy, int64_t* iters, double* rho) {
+    return drain(g, transposed_sweeps(g, kc, mus, rtol, max_iter, lam_copy, iters, rho));
 }
 // The same transposed solve by defect correction: FP64 residual F(lambda) =
 // J_F lambda - xbar (the stage residual with gravity off, the history term

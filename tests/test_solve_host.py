@@ -1,0 +1,43 @@
+"""The host side of the solves on a model of the device (solve_probe.hip): what
+they leave in their stream when they return."""
+import os
+import shutil
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+
+
+@pytest.fixture(scope="module")
+def run(tmp_path_factory):
+    if not shutil.which(HIPCC) and not os.path.exists(HIPCC):
+        pytest.skip("hipcc not available")
+    exe = str(tmp_path_factory.mktemp("solve") / "probe")
+    # (host code alone, linked without the HIP runtime, whose calls the model answers)
+    subprocess.run([HIPCC, "-x", "hip", "-std=c++17", "--offload-arch=gfx950", "--offload-host-only", "-fuse-cuid=none",
+                    "-no-hip-rt", "-I", os.path.join(ROOT, "include"),
+                    "-I", os.path.join(ROOT, "paper_2207_08716_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "solve_probe.hip"), "-o", exe], check=True, capture_output=True)
+
+    def go(scenario):
+        out = subprocess.run([exe, scenario], check=True, capture_output=True, text=True, timeout=60).stdout
+        return {k: float(v) for k, v in (line.split() for line in out.splitlines())}
+    return go
+
+
+@pytest.mark.parametrize("scenario", ["tail", "tail_static"])
+def test_a_solve_at_its_limit_leaves_nothing_queued(run, scenario):
+    # 15 sweeps to a check and 3 more: those read the gate, which in the
+    # static scratch the next handle's solve writes over
+    r = run(scenario)
+    assert r["covers"] == 1 and r["status_a"] == 1 and r["iters_a"] == 18
+    assert r["status_b"] == 0 and r["steps_b"] == r["iters_b"]
+    assert r["queued_a"] == 0 and r["queued_b"] == 0
+    assert r["steps_a"] == 18
+
+
+def test_a_transposed_solve_at_its_limit_leaves_nothing_queued(run):
+    r = run("tail_transposed")
+    assert r["status"] == 1 and r["iters"] == 18 and r["steps"] == 18 and r["queued"] == 0
