@@ -1068,9 +1068,9 @@ struct MixedTarget {
 // PT sweeps on A d = -r from d = 0, the damped residual of d carried over in
 // correction copy `copy`, until the residual of d is eta_in times r, or
 // rtol/2 on the outer scale, or stalls; x += d }.
-pt_status mixed_core(pt_grid* g, const MixedTarget& t, double rtol, double eta_in, int64_t max_inner,
-                     int32_t max_outer, double& ref_v, double& ref_p, bool& ref_set, int& copy,
-                     int64_t* inner_iters, int32_t* outer_iters, double* rho) {
+pt_status mixed_sweeps(pt_grid* g, const MixedTarget& t, double rtol, double eta_in, int64_t max_inner,
+                       int32_t max_outer, double& ref_v, double& ref_p, bool& ref_set, int& copy,
+                       int64_t* inner_iters, int32_t* outer_iters, double* rho) {
     const int64_t box_bytes = mx_stride(g) * (int64_t)sizeof(float);
     MixedPtrs m = t.m;
     m.kc32 = mx(g, 21); m.mus32 = mx(g, 22); m.chi32 = mx(g, 23);
@@ -1170,6 +1170,13 @@ pt_status mixed_core(pt_grid* g, const MixedTarget& t, double rtol, double eta_i
     if (outer_iters) *outer_iters += outer;
     if (rho) *rho = r;
     return (r <= rtol) ? PT_OK : PT_ENOTCONV;
+}
+
+pt_status mixed_core(pt_grid* g, const MixedTarget& t, double rtol, double eta_in, int64_t max_inner,
+                     int32_t max_outer, double& ref_v, double& ref_p, bool& ref_set, int& copy,
+                     int64_t* inner_iters, int32_t* outer_iters, double* rho) {
+    return drain(g, mixed_sweeps(g, t, rtol, eta_in, max_inner, max_outer, ref_v, ref_p, ref_set, copy, inner_iters,
+                                 outer_iters, rho));
 }
 
 pt_status mixed_ready(pt_grid* g) {

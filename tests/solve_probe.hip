@@ -28,7 +28,7 @@ struct Stream {
 };
 std::map<hipStream_t, Stream> streams;
 int mallocs = 0, frees = 0;
-bool refuse_mallocs = false, poison = false;   // poison: norms are NaN
+bool refuse_mallocs = false, poison = false;   // poison: the FP32 sweeps' norms are NaN
 
 hipError_t put(hipStream_t s, std::function<void()> t) {
     streams[s].tasks.push_back(std::move(t));
@@ -42,7 +42,7 @@ hipError_t sweep(const ptk::SweepPtrs<T>& p, int64_t blocks, bool step, hipStrea
         if (p.gate && *p.gate != 0.0) return;
         const T n = p.vx[0] + T(step ? 1 : 0);
         if (step) p.vx_o[0] = n;
-        for (int64_t q = 0; q < blocks * ptk::NNORM; ++q) p.partials[q] = poison ? NAN : std::pow(0.5, (double)n);
+        for (int64_t q = 0; q < blocks * ptk::NNORM; ++q) p.partials[q] = poison && sizeof(T) == 4 ? NAN : std::pow(0.5, (double)n);
     });
 }
 
@@ -240,6 +240,17 @@ void tail_transposed() {
     say("steps", ad(a.g, copy ? 8 : 0)[0]);
 }
 
+// A mixed solve whose first check finds a NaN.
+void mixed_nan() {
+    Handle a(8, 0x100);
+    fake::poison = true;
+    int64_t inner = 0;
+    int32_t outer = 0;
+    double rho = 0.0;
+    say("status", pt_solve_mixed(a.g, 1e-8, 1e-2, 1000, 10, &inner, &outer, &rho));
+    say("queued", fake::queued(a.s));
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -247,6 +258,7 @@ int main(int argc, char** argv) {
     if (what == "tail") tail(false);
     else if (what == "tail_static") tail(true);
     else if (what == "tail_transposed") tail_transposed();
+    else if (what == "mixed_nan") mixed_nan();
     else return 2;
     return 0;
 }

@@ -41,3 +41,15 @@ def test_a_solve_at_its_limit_has_left_its_stream(static):
     torch.cuda.synchronize()
     for n in STATE:
         assert np.array_equal(a.get(n), alone.get(n)), n
+
+
+def test_a_mixed_solve_that_diverges_has_left_its_stream():
+    # the FP64 residual is finite; an FP32 coefficient that overflows makes
+    # the first correction's norms non-finite
+    g = _grid((127, 127, 127))
+    kc = g.get("kc")
+    kc[60, 61, 62] = 1e300
+    g.set("kc", kc)
+    with pytest.raises(Exception, match="non-finite"):
+        g.solve_mixed(1e-8, 1e-2, 1000, 5)
+    assert g.stream.query()

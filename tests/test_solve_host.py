@@ -41,3 +41,8 @@ def test_a_solve_at_its_limit_leaves_nothing_queued(run, scenario):
 def test_a_transposed_solve_at_its_limit_leaves_nothing_queued(run):
     r = run("tail_transposed")
     assert r["status"] == 1 and r["iters"] == 18 and r["steps"] == 18 and r["queued"] == 0
+
+
+def test_a_mixed_solve_that_diverges_leaves_nothing_queued(run):
+    r = run("mixed_nan")
+    assert r["status"] == -3 and r["queued"] == 0
