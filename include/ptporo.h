@@ -19,8 +19,10 @@
  *   needs is in caller buffers bound with pt_bind_workspace (and, for the
  *   mixed-precision solves and the adjoints, pt_bind_mixed_workspace and
  *   pt_bind_adjoint_workspace; the run adjoint's tape is an argument).
- *   A handle's first solve allocates 176 bytes of host memory that the device
- *   writes the checks' norms to; pt_destroy frees them.
+ *   A handle's first solve, but for pt_solve_linear_static, allocates 176
+ *   bytes of host memory that the device writes the checks' norms to (without
+ *   them the same solve waits for the device at each check); pt_destroy frees
+ *   them.
  *   Bound pointers must stay valid while the handle uses them.
  * Layout.  Every field is an FP64 array in one common padded box layout:
  *   element (i, j, k) of any staggered field is at offset

@@ -60,7 +60,7 @@ struct pt_grid {
     int64_t mg_tail = 0;       // doubles before the restriction rows
     int mg_cur[PT_MG_MAX_LEVELS] = {};   // present copy of the coarse grids' iterated fields
     // the checks of solves: their number, and the last two's results in host
-    // memory that the device writes
+    // memory that the device writes (null: read by copies)
     int64_t checks = 0;
     double* slots = nullptr;
     std::string err;
@@ -299,7 +299,7 @@ pt_status reduce_norms(pt_grid* g, int64_t nb) {
 pt_status check_norms(pt_grid* g, int64_t nb, const CheckRule& r) {
     ++g->checks;
     hipError_t e = launch_check(norm_area(g), nb, norm_area(g) + g->tiling.most * NNORM, domain_flag(g), gate(g), r,
-                                g->slots + (g->checks & 1) * SLOT_DOUBLES, (double)g->checks, g->stream);
+                                g->slots ? g->slots + (g->checks & 1) * SLOT_DOUBLES : nullptr, (double)g->checks, g->stream);
     if (e != hipSuccess) return hip_fail(g, e, "check");
     g->norms_pending = true;
     return PT_OK;
@@ -392,17 +392,21 @@ pt_status read_norms(pt_grid* g, pt_norms* out) {
 }
 
 // Opens the gate of a solve; the host memory of the checks, one small block
-// per handle, comes with its first solve.
+// per handle, comes with its first solve that may allocate.  Without it (the
+// static scratch in force, or no memory to be had) each check is read before
+// the next sweeps are launched.
 pt_status open_gate(pt_grid* g) {
-    hipError_t e = hipSuccess;
-    if (!g->slots) {
+    if (!g->slots && !g->nw) {
         void* m = nullptr;
-        e = hipHostMalloc(&m, 2 * SLOT_DOUBLES * sizeof(double), hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent);
-        if (e != hipSuccess) return hip_fail(g, e, "host memory of the checks");
-        g->slots = static_cast<double*>(m);
-        for (int q = 0; q < 2 * SLOT_DOUBLES; ++q) g->slots[q] = 0.0;
+        if (hipHostMalloc(&m, 2 * SLOT_DOUBLES * sizeof(double),
+                          hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
+            g->slots = static_cast<double*>(m);
+            for (int q = 0; q < 2 * SLOT_DOUBLES; ++q) g->slots[q] = 0.0;
+        } else {
+            (void)hipGetLastError();
+        }
     }
-    e = launch_fill(gate(g), 0.0, 1, g->stream);
+    const hipError_t e = launch_fill(gate(g), 0.0, 1, g->stream);
     return e == hipSuccess ? PT_OK : hip_fail(g, e, "gate");
 }
 
@@ -410,7 +414,18 @@ pt_status open_gate(pt_grid* g) {
 // norms; stop: it closed the gate.  Polls the check's number in host memory
 // (the stream already holds the next sweeps), asking the stream now and then
 // so that a device error or a stream that ended without it ends the wait.
+// Without host memory: the last check's results by a copy from the norm area.
 pt_status read_check(pt_grid* g, int64_t number, pt_norms* out, bool* stop) {
+    if (!g->slots) {
+        double host[NNORM + 2];   // norms, domain flag, gate
+        hipError_t e = hipMemcpyAsync(host, norm_area(g) + g->tiling.most * NNORM, sizeof(host), hipMemcpyDeviceToHost,
+                                      g->stream);
+        const hipError_t es = hipStreamSynchronize(g->stream);   // also on a failed copy: host is local
+        if (e == hipSuccess) e = es;
+        if (e != hipSuccess) return hip_fail(g, e, "check copy");
+        *stop = host[NNORM + 1] != 0.0;
+        return take_norms(g, host, out);
+    }
     const double* slot = g->slots + (number & 1) * SLOT_DOUBLES;
     const double want = (double)number;
     auto there = [&] {
@@ -730,10 +745,15 @@ pt_status linear_sweeps(pt_grid* g, double rtol, int64_t max_iter, int64_t* iter
     // where it stood at the check
     const CheckRule rule{g->ref_v, g->ref_p, rtol, 0.0, 0.0, -1.0, 0, 0};
     for (int64_t waiting = 0; !done;) {
-        int at_cur[PT_NPING];
-        std::copy(g->cur, g->cur + PT_NPING, at_cur);
-        const int64_t at_it = it, at_iter = g->iter;
-        const bool at_r = g->r_ok, at_vp = g->vp_ok;
+        struct { int cur[PT_NPING]; int64_t it, iter; bool r_ok, vp_ok; } at;
+        auto here = [&] {
+            std::copy(g->cur, g->cur + PT_NPING, at.cur);
+            at.it = it;
+            at.iter = g->iter;
+            at.r_ok = g->r_ok;
+            at.vp_ok = g->vp_ok;
+        };
+        here();
         bool chk = false;
         while (it < max_iter && !chk) {
             ++it;
@@ -741,18 +761,22 @@ pt_status linear_sweeps(pt_grid* g, double rtol, int64_t max_iter, int64_t* iter
             st = iteration_impl(g, 0, chk ? 1 : 0, true, &rule);
             if (st != PT_OK) return st;
         }
-        const bool last = it == at_it;
+        const bool last = it == at.it;
+        if (chk && !g->slots) {
+            waiting = g->checks;
+            here();
+        }
         if (waiting) {
             pt_norms nm;
             bool stop = false;
             st = read_check(g, waiting, &nm, &stop);
             if (st == PT_OK) rho_of(nm);
             if (st != PT_OK || stop) {
-                std::copy(at_cur, at_cur + PT_NPING, g->cur);
-                it = at_it;
-                g->iter = at_iter;
-                g->r_ok = at_r;
-                g->vp_ok = at_vp;
+                std::copy(at.cur, at.cur + PT_NPING, g->cur);
+                it = at.it;
+                g->iter = at.iter;
+                g->r_ok = at.r_ok;
+                g->vp_ok = at.vp_ok;
                 if (st != PT_OK) {
                     if (iters) *iters = it;
                     return st;
@@ -761,7 +785,7 @@ pt_status linear_sweeps(pt_grid* g, double rtol, int64_t max_iter, int64_t* iter
             }
         }
         if (last) break;
-        waiting = chk ? g->checks : 0;
+        waiting = chk && g->slots ? g->checks : 0;
     }
     if (iters) *iters = it;
     if (rho) *rho = r;
@@ -1125,8 +1149,8 @@ pt_status mixed_sweeps(pt_grid* g, const MixedTarget& t, double rtol, double eta
         for (int64_t waiting = 0;;) {
             // (the sweeps up to the next check before this one is read, as
             // in solve_linear_core)
-            const int at_cp = cp, at_cr = cr;
-            const int64_t at_it = it;
+            int at_cp = cp, at_cr = cr;
+            int64_t at_it = it;
             bool chk = false;
             while (it < max_inner && !chk) {
                 ++it;
@@ -1140,6 +1164,12 @@ pt_status mixed_sweeps(pt_grid* g, const MixedTarget& t, double rtol, double eta
             }
             if (chk) rule.first = 0;
             const bool last = it == at_it;
+            if (chk && !g->slots) {
+                waiting = g->checks;
+                at_cp = cp;
+                at_cr = cr;
+                at_it = it;
+            }
             if (waiting) {
                 pt_norms ni;
                 bool stop = false;
@@ -1153,7 +1183,7 @@ pt_status mixed_sweeps(pt_grid* g, const MixedTarget& t, double rtol, double eta
                 }
             }
             if (last) break;
-            waiting = chk ? g->checks : 0;
+            waiting = chk && g->slots ? g->checks : 0;
         }
         inner_total += it;
         const int b = cp ? 8 : 0;
@@ -1320,8 +1350,8 @@ pt_status transposed_sweeps(pt_grid* g, const double* kc, const double* mus, dou
         for (int64_t waiting = 0;;) {
             // (the sweeps up to the next check before this one is read, as
             // in solve_linear_core)
-            const int at_cp = cp;
-            const int64_t at_it = it;
+            int at_cp = cp;
+            int64_t at_it = it;
             bool chk = false;
             while (it < max_iter && !chk) {
                 ++it;
@@ -1348,6 +1378,11 @@ pt_status transposed_sweeps(pt_grid* g, const double* kc, const double* mus, dou
                 }
             }
             const bool last = it == at_it;
+            if (chk && !g->slots) {
+                waiting = g->checks;
+                at_cp = cp;
+                at_it = it;
+            }
             if (waiting) {
                 pt_norms nm;
                 bool stop = false;
@@ -1361,7 +1396,7 @@ pt_status transposed_sweeps(pt_grid* g, const double* kc, const double* mus, dou
                 }
             }
             if (last) break;
-            waiting = chk ? g->checks : 0;
+            waiting = chk && g->slots ? g->checks : 0;
         }
     }
     *lam_copy = cp;

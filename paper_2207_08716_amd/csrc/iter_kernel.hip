@@ -688,7 +688,8 @@ __global__ __launch_bounds__(RT) void k_reduce_max(const double* __restrict__ pa
 }
 
 // A check of a solve (see CheckRule).  The host waits for the number, which
-// is written after the rest, not for a copy and the stream.
+// is written after the rest, not for a copy and the stream; without a slot it
+// copies the norms, the domain flag and the gate, which follow each other.
 __global__ __launch_bounds__(RT) void k_check(const double* __restrict__ part, int64_t nb, double* __restrict__ out,
                                               const double* __restrict__ domain, double* __restrict__ gate, CheckRule r,
                                               double* __restrict__ slot, double number) {
@@ -723,10 +724,9 @@ __global__ __launch_bounds__(RT) void k_check(const double* __restrict__ part, i
         }
     }
     if (stop) gate[0] = 1.0;
-    for (int q = 0; q < NNORM; ++q) {
-        out[q] = n[q];
-        slot[q] = n[q];
-    }
+    for (int q = 0; q < NNORM; ++q) out[q] = n[q];
+    if (!slot) return;
+    for (int q = 0; q < NNORM; ++q) slot[q] = n[q];
     slot[NNORM] = flag;
     slot[NNORM + 1] = stop ? 1.0 : 0.0;
     __hip_atomic_store(slot + NNORM + 2, number, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);

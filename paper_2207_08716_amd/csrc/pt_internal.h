@@ -337,8 +337,8 @@ struct CheckRule {
 };
 // Doubles of a gate: closed (0 or 1), the least rho, checks since then.
 constexpr int GATE_DOUBLES = 3;
-// What a check leaves in host memory: the norms, the domain flag, whether
-// the gate is closed, and last the check's number.
+// What a check leaves in host memory (slot, if not null): the norms, the
+// domain flag, whether the gate is closed, and last the check's number.
 constexpr int SLOT_DOUBLES = NNORM + 3;
 hipError_t launch_check(const double* partials, int64_t nblocks, double* out8, const double* domain, double* gate,
                         const CheckRule& r, double* slot, double number, hipStream_t s);

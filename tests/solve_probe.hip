@@ -251,6 +251,29 @@ void mixed_nan() {
     say("queued", fake::queued(a.s));
 }
 
+// Host memory that a handle's first solves ask for; refuse: and do not get.
+void memory(bool refuse) {
+    fake::refuse_mallocs = refuse;
+    Handle a(8, 0x100), b(8, 0x200), c(8, 0x300);
+    int64_t it = 0, inner = 0;
+    int32_t outer = 0;
+    double rho = 0.0;
+    say("status_static", pt_solve_linear_static(a.g, 1e-12, 1000, &it, &rho));
+    say("iters_static", it);
+    say("rho_static", rho);
+    say("steps_static", a.steps());
+    say("queued_static", fake::queued(a.s));
+    say("mallocs_static", fake::mallocs);
+    say("status_linear", pt_solve_linear(b.g, 1e-12, 1000, &it, &rho));
+    say("iters_linear", it);
+    say("rho_linear", rho);
+    say("steps_linear", b.steps());
+    say("status_mixed", pt_solve_mixed(c.g, 1e-12, 1e-3, 1000, 10, &inner, &outer, &rho));
+    say("inner_mixed", inner);
+    say("outer_mixed", outer);
+    say("mallocs", fake::mallocs);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -259,6 +282,8 @@ int main(int argc, char** argv) {
     else if (what == "tail_static") tail(true);
     else if (what == "tail_transposed") tail_transposed();
     else if (what == "mixed_nan") mixed_nan();
+    else if (what == "memory") memory(false);
+    else if (what == "memory_refused") memory(true);
     else return 2;
     return 0;
 }

@@ -46,3 +46,17 @@ def test_a_transposed_solve_at_its_limit_leaves_nothing_queued(run):
 def test_a_mixed_solve_that_diverges_leaves_nothing_queued(run):
     r = run("mixed_nan")
     assert r["status"] == -3 and r["queued"] == 0
+
+
+def test_the_static_solve_allocates_nothing(run):
+    r = run("memory")
+    assert r["mallocs_static"] == 0 and r["mallocs"] == 2
+    assert r["status_static"] == r["status_linear"] == r["status_mixed"] == 0
+    # and it is the other solve: 2^-(sweeps - 1) <= 1e-12 first holds at a check after 45
+    assert r["iters_static"] == r["iters_linear"] == r["steps_static"] == r["steps_linear"] == 45
+    assert r["rho_static"] == r["rho_linear"] and r["queued_static"] == 0
+
+
+def test_a_solve_without_host_memory_is_the_same_solve(run):
+    r, full = run("memory_refused"), run("memory")
+    assert r.pop("mallocs") >= 2 and full.pop("mallocs") == 2 and r == full
