@@ -21,8 +21,9 @@
  *   pt_bind_adjoint_workspace; the run adjoint's tape is an argument).
  *   A handle's first solve, but for pt_solve_linear_static, allocates 176
  *   bytes of host memory that the device writes the checks' norms to (without
- *   them the same solve waits for the device at each check); pt_destroy frees
- *   them.
+ *   them the same solve waits for the device at each check); pt_destroy keeps
+ *   them for the process's next handle (64 blocks at most, the rest is freed,
+ *   which waits for the device).
  *   Bound pointers must stay valid while the handle uses them.
  * Layout.  Every field is an FP64 array in one common padded box layout:
  *   element (i, j, k) of any staggered field is at offset

@@ -391,20 +391,47 @@ pt_status read_norms(pt_grid* g, pt_norms* out) {
     return take_norms(g, host, out);
 }
 
+// Blocks of host memory of handles that are gone, for the next ones' checks:
+// freeing pinned memory waits for everything the device has to do, which
+// destroying a handle must not.  A handle's solves have drained their stream
+// when they return, so nothing writes to its block any more.
+constexpr int SPARE_SLOTS = 64;
+std::mutex spare_mutex;
+double* spare[SPARE_SLOTS];
+int spares = 0;
+
+double* take_slots() {
+    {
+        std::lock_guard<std::mutex> lock(spare_mutex);
+        if (spares > 0) return spare[--spares];
+    }
+    void* m = nullptr;
+    if (hipHostMalloc(&m, 2 * SLOT_DOUBLES * sizeof(double),
+                      hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess)
+        return static_cast<double*>(m);
+    (void)hipGetLastError();
+    return nullptr;
+}
+
+void give_slots(double* s) {
+    {
+        std::lock_guard<std::mutex> lock(spare_mutex);
+        if (spares < SPARE_SLOTS) {
+            spare[spares++] = s;
+            return;
+        }
+    }
+    (void)hipHostFree(s);
+}
+
 // Opens the gate of a solve; the host memory of the checks, one small block
 // per handle, comes with its first solve that may allocate.  Without it (the
 // static scratch in force, or no memory to be had) each check is read before
 // the next sweeps are launched.
 pt_status open_gate(pt_grid* g) {
     if (!g->slots && !g->nw) {
-        void* m = nullptr;
-        if (hipHostMalloc(&m, 2 * SLOT_DOUBLES * sizeof(double),
-                          hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess) {
-            g->slots = static_cast<double*>(m);
-            for (int q = 0; q < 2 * SLOT_DOUBLES; ++q) g->slots[q] = 0.0;
-        } else {
-            (void)hipGetLastError();
-        }
+        g->slots = take_slots();
+        if (g->slots) std::fill(g->slots, g->slots + 2 * SLOT_DOUBLES, 0.0);
     }
     const hipError_t e = launch_fill(gate(g), 0.0, 1, g->stream);
     return e == hipSuccess ? PT_OK : hip_fail(g, e, "gate");
@@ -539,7 +566,7 @@ pt_status pt_create(int32_t nx, int32_t ny, int32_t nz, int64_t row_pitch, const
 }
 
 pt_status pt_destroy(pt_grid* g) {
-    if (g && g->slots) (void)hipHostFree(g->slots);
+    if (g && g->slots) give_slots(g->slots);
     delete g;
     return PT_OK;
 }

@@ -274,6 +274,32 @@ void memory(bool refuse) {
     say("mallocs", fake::mallocs);
 }
 
+// Handles that come and go while another stream is busy: one after the
+// other, then many at once.
+void destroy() {
+    const hipStream_t busy = reinterpret_cast<hipStream_t>(0x900);
+    fake::put(busy, [] {});
+    int64_t it = 0;
+    double rho = 0.0;
+    bool solved = true;
+    for (int q = 0; q < 10; ++q) {
+        Handle a(8, 0x100);
+        solved = solved && pt_solve_linear(a.g, 1e-12, 1000, &it, &rho) == PT_OK && it == 45 && a.steps() == 45;
+        pt_destroy(a.g);
+    }
+    say("solved", solved);
+    say("waited", fake::queued(busy) == 0);
+    say("mallocs_in_turn", fake::mallocs);
+    std::vector<Handle> many;
+    for (int q = 0; q < 200; ++q) {
+        many.emplace_back(8, 0x100 + 16 * (uintptr_t)q);
+        solved = solved && pt_solve_linear(many.back().g, 1e-12, 1000, &it, &rho) == PT_OK && it == 45;
+    }
+    for (auto& h : many) pt_destroy(h.g);
+    say("solved_many", solved);
+    say("kept", fake::mallocs - fake::frees);
+}
+
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -284,6 +310,7 @@ int main(int argc, char** argv) {
     else if (what == "mixed_nan") mixed_nan();
     else if (what == "memory") memory(false);
     else if (what == "memory_refused") memory(true);
+    else if (what == "destroy") destroy();
     else return 2;
     return 0;
 }

@@ -53,3 +53,17 @@ def test_a_mixed_solve_that_diverges_has_left_its_stream():
     with pytest.raises(Exception, match="non-finite"):
         g.solve_mixed(1e-8, 1e-2, 1000, 5)
     assert g.stream.query()
+
+
+def test_destroying_a_handle_does_not_wait_for_another_stream():
+    with torch.cuda.stream(torch.cuda.Stream()):
+        a = _grid((21, 18, 15))
+    with torch.cuda.stream(torch.cuda.Stream()):
+        b = _grid((255, 255, 255))
+    a.solve_linear(1e-300, 40)
+    b.iterate(15)
+    torch.cuda.synchronize()
+    b.iterate(300)          # 0.2 s
+    a.close()
+    assert not b.stream.query()
+    torch.cuda.synchronize()

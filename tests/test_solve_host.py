@@ -60,3 +60,12 @@ def test_the_static_solve_allocates_nothing(run):
 def test_a_solve_without_host_memory_is_the_same_solve(run):
     r, full = run("memory_refused"), run("memory")
     assert r.pop("mallocs") >= 2 and full.pop("mallocs") == 2 and r == full
+
+
+def test_destroying_a_handle_waits_for_no_other_stream(run):
+    # freeing pinned memory waits for the device: the block goes to the next
+    # handle instead, up to a bound
+    r = run("destroy")
+    assert r["solved"] == 1 and r["solved_many"] == 1
+    assert r["waited"] == 0 and r["mallocs_in_turn"] == 1
+    assert r["kept"] <= 64
