@@ -110,12 +110,7 @@ struct CT {
           beta_n(T(c.beta_n)), rho_i_inv(T(c.rho_i_inv)), dtauv_c(T(c.dtauv_c)), dampx(T(c.dampx)),
           dampy(T(c.dampy)), dampz(T(c.dampz)), rhofg(T(c.rhofg)), rhosg(T(c.rhosg)), rhobg(T(c.rhobg)),
           hdx(T(0.5 * c.dxi)), hdy(T(0.5 * c.dyi)), hdz(T(0.5 * c.dzi)), bpt(T(c.beta_phi * c.dti)), dt(T(c.dt)),
-          gbg_half(T(c.gbg_half)) {
-        if (c.mech_off) {   // V, R and Pt stay as they are: no pseudo step, R' = R
-            dtaupt_c = dtauv_c = rho_i_inv = T(0);
-            dampx = dampy = dampz = T(1);
-        }
-    }
+          gbg_half(T(c.gbg_half)) {}
 };
 
 // Kernel arguments as one block, so that they can be read again from the
@@ -129,13 +124,20 @@ struct SweepArgs {
 
 // Damping memory of a sweep variant: the previous velocity iterate (in the
 // rx..rz inputs), the stored damped residual, or none (damping factor 0).
-constexpr int RM_VPREV = 0, RM_STORED = 1, RM_NONE = 2;
+// RM_FROZEN, mechanics off: V, R and Pt keep their values, whatever the forces
+// (a variant of its own: zero pseudo steps let a non-finite force in, and a
+// flag in the others made a multigrid stage at 127^3 1.6 % slower, a linear
+// solve at 40^3 0.5 %).
+constexpr int RM_VPREV = 0, RM_STORED = 1, RM_NONE = 2, RM_FROZEN = 3;
 
 // One face's damped velocity update (see the header): returns V', sets the
 // damped residual R' in r.  q: the stored R or V_prev.
 template <int RM, typename T, typename C>
 __device__ __forceinline__ T damped_update(const C& c, T v_c, T q, T f, T damp, T dtv, T& r) {
-    if constexpr (RM == RM_STORED) {
+    if constexpr (RM == RM_FROZEN) {
+        r = q;
+        return v_c;
+    } else if constexpr (RM == RM_STORED) {
         r = f * c.rho_i_inv + damp * q;
         return v_c + dtv * r;
     } else if constexpr (RM == RM_NONE) {
@@ -157,7 +159,7 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
     constexpr bool RESID = (MODE == MD_RESID);
     constexpr bool CORR = (MODE == MD_CORR);
     constexpr bool WNORM = NORMS || RESID;
-    constexpr bool RREAD = !RESID && RM != RM_NONE;
+    constexpr bool RREAD = !RESID && RM != RM_NONE && (RM != RM_FROZEN || RW);
     constexpr bool GATED = (MODE == MD_LINEAR || CORR) && RM != RM_NONE;   // the sweeps of solves
     constexpr int L_DTV = L_CORE, L_S = L_DTV + (RESID ? 0 : 2), L_TZZ = L_S + (UPD_LP ? 2 : 0), L_W = L_TZZ + (UPD_LP ? 1 : 0), NPL = L_W + (NORMS ? 1 : 0);
     constexpr int WH = W * H;
@@ -384,7 +386,7 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
                 rpt_k = pto + divv + c.bdt * (pt - c.alpha * pf_c) + (pt - pf_c) * chi;
             } else {
                 chi = quot(one, eta * s_c);
-                if constexpr (RESID)
+                if constexpr (RESID || RM == RM_FROZEN)
                     ptn = pt;
                 else
                     ptn = quot(pt - dtp * (divv - c.bdt * (pto + c.alpha * (pf_c - pfo)) - pf_c * chi),
@@ -505,7 +507,7 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
         // cells' (the one of the larger viscosity): one quotient per cell
         // where each face took its own, in two planes by parity, so that the
         // thesis sweeps spill no register (511^3 4.85 -> 4.76 ms)
-        if constexpr (!RESID) sh(L_DTV + bc, 0, 0) = quot(c.dtauv_c, mu_c);
+        if constexpr (!RESID && RM != RM_FROZEN) sh(L_DTV + bc, 0, 0) = quot(c.dtauv_c, mu_c);
         sh(L_TXX, 0, 0) = txx;
         sh(L_TYY, 0, 0) = tyy;
         sh(L_TXY, 0, 0) = txy;
@@ -786,12 +788,18 @@ hipError_t launch_sweep(const Geom& g, const Tiling& tl, const Coef& c, const Sw
 template <typename T, int MODE>
 hipError_t launch_mode(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<T>& p, int norms,
                        hipStream_t s) {
+    if constexpr (MODE != MD_CORR)
+        if (c.mech_off) {   // (R' = R is stored: it has moved to its other copy)
+            if (norms) return launch_sweep<T, MODE, true, RM_FROZEN, true>(g, t, c, p, s);
+            return launch_sweep<T, MODE, false, RM_FROZEN, true>(g, t, c, p, s);
+        }
     if (norms) {
         if (c.rform) return launch_sweep<T, MODE, true, RM_STORED, true>(g, t, c, p, s);
         return launch_sweep<T, MODE, true, RM_VPREV, true>(g, t, c, p, s);
     }
     if (c.rwrite) {
-        if (c.rform) return launch_sweep<T, MODE, false, RM_STORED, true>(g, t, c, p, s);
+        if constexpr (MODE != MD_THESIS)
+            if (c.rform) return launch_sweep<T, MODE, false, RM_STORED, true>(g, t, c, p, s);
         if constexpr (MODE == MD_CORR) return launch_sweep<T, MODE, false, RM_VPREV, true>(g, t, c, p, s);
         return hipErrorInvalidValue;
     }
@@ -828,7 +836,10 @@ hipError_t launch_check(const double* partials, int64_t nblocks, double* out8, c
 #if SWEEP_HAS(1)
 hipError_t launch_linear(const Geom& g, const Tiling& t, const Coef& c, const SweepPtrs<double>& p, int norms,
                          hipStream_t s) {
-    if (c.undamped) return launch_sweep<double, MD_LINEAR, false, RM_NONE, false>(g, t, c, p, s);
+    if (c.undamped) {
+        if (c.mech_off) return launch_sweep<double, MD_LINEAR, false, RM_FROZEN, false>(g, t, c, p, s);
+        return launch_sweep<double, MD_LINEAR, false, RM_NONE, false>(g, t, c, p, s);
+    }
     return launch_mode<double, MD_LINEAR>(g, t, c, p, norms, s);
 }
 #endif

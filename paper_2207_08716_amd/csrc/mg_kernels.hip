@@ -355,6 +355,8 @@ struct CoarseArgs {
     double *vx, *vy, *vz, *pt, *pf;
 };
 
+// FROZEN: mechanics off, V and Pt keep their zero whatever the forces.
+template <bool FROZEN>
 __global__ __launch_bounds__(1024) void k_mg_coarsest(CoarseArgs a) {
     extern __shared__ double lds[];
     const int X = a.nx + 2, XY = X * (a.ny + 2), N = XY * (a.nz + 2);   // a plane of the rimmed grid
@@ -427,8 +429,9 @@ __global__ __launch_bounds__(1024) void k_mg_coarsest(CoarseArgs a) {
             txy[me] = hxy; txz[me] = hxz; tyz[me] = hyz;
         }
         f -= tf * rpf;
-        p = ptn;
+        if constexpr (!FROZEN) p = ptn;
         __syncthreads();
+        if constexpr (FROZEN) continue;
         const double gx = (nx - sx[me - 1]) * a.dxi + (txy[me + X] - hxy) * a.dyi + (txz[me + XY] - hxz) * a.dzi + fox;
         const double gy = (txy[me + 1] - hxy) * a.dxi + (ny - sy[me - X]) * a.dyi + (tyz[me + XY] - hyz) * a.dzi + foy;
         const double gz = (txz[me + 1] - hxz) * a.dxi + (tyz[me + X] - hyz) * a.dyi + (nz - sz[me - XY]) * a.dzi + foz;
@@ -538,14 +541,14 @@ hipError_t launch_mg_coarsest(const Geom& g, const Coef& c, const SweepPtrs<doub
     a.dxi = c.dxi; a.dyi = c.dyi; a.dzi = c.dzi;
     a.bdt = c.beta_d * c.dti; a.alpha = c.alpha; a.ab = c.ab;
     a.gdts = c.gdts_inv; a.beta_n = c.beta_n; a.rho_i_inv = c.rho_i_inv;
-    // with the mechanics off V and Pt keep their zero
-    a.dtauv_c = c.mech_off ? 0.0 : c.dtauv_c; a.dtaupt_c = c.mech_off ? 0.0 : c.dtaupt_c; a.dtaupf_c = c.dtaupf_c;
+    a.dtauv_c = c.dtauv_c; a.dtaupt_c = c.dtaupt_c; a.dtaupf_c = c.dtaupf_c;
     a.dampx = c.dampx; a.dampy = c.dampy; a.dampz = c.dampz;
     a.lp = p.lp; a.kc = p.kc; a.eta = p.eta; a.mus = p.mus;
     a.fox = p.fox; a.foy = p.foy; a.foz = p.foz; a.pto = p.pto; a.pfo = p.pfo;
     a.vx = out[0]; a.vy = out[1]; a.vz = out[2]; a.pt = out[3]; a.pf = out[4];
     const int threads = (g.nx * g.ny * g.nz + 63) / 64 * 64;
-    hipLaunchKernelGGL(k_mg_coarsest, dim3(1), dim3(threads), coarsest_lds(g), s, a);
+    if (c.mech_off) hipLaunchKernelGGL(k_mg_coarsest<true>, dim3(1), dim3(threads), coarsest_lds(g), s, a);
+    else hipLaunchKernelGGL(k_mg_coarsest<false>, dim3(1), dim3(threads), coarsest_lds(g), s, a);
     return hipGetLastError();
 }
 
