@@ -425,7 +425,7 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
             // largest permeability of the cell and its face neighbours
             kz_n = max1(kc_c, kc_n);
             const T kl = max1(max1(max1(kw, ke), max1(ks, kn)), max1(kz_c, kz_n));
-            const T dtf = quot(c.dtaupf_c, kl);
+            const T dtf = quot_field(c.dtaupf_c, kl);
             if constexpr (CORR) {
                 pfn = quot(pf_c - dtf * (divq + pfo - c.bda * pt - pt * chi), one + dtf * (c.bdab + chi));
                 if (WNORM) rpf_k = pfo + divq + c.bdt * (c.ab * pf_c - c.alpha * pt) + (pf_c - pt) * chi;
@@ -507,7 +507,7 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
         // cells' (the one of the larger viscosity): one quotient per cell
         // where each face took its own, in two planes by parity, so that the
         // thesis sweeps spill no register (511^3 4.85 -> 4.76 ms)
-        if constexpr (!RESID && RM != RM_FROZEN) sh(L_DTV + bc, 0, 0) = quot(c.dtauv_c, mu_c);
+        if constexpr (!RESID && RM != RM_FROZEN) sh(L_DTV + bc, 0, 0) = quot_field(c.dtauv_c, mu_c);
         sh(L_TXX, 0, 0) = txx;
         sh(L_TYY, 0, 0) = tyy;
         sh(L_TXY, 0, 0) = txy;

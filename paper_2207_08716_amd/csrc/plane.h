@@ -47,9 +47,13 @@ __device__ __forceinline__ double inverse(double b) {
 }
 
 // a / b by an iteration on the reciprocal and a corrected quotient, without
-// the rescaling of the operands that only quotients and divisors near the
-// ends of the exponent range need; infinities, zeros and NaN come out as from
-// the division.
+// the rescaling of the operands that the division has.  As accurate as the division (one unit in the last
+// place, two where the dividend is so small that its residual is subnormal)
+// for divisors from 2^-1022 to 2^1022, in FP32 from 2^-126 to 2^126;
+// infinities, zeros and NaN come out as from the division.  Outside, the
+// reciprocal leaves the exponent range and the result is wrong.  In FP64 no
+// quantity of a run comes near the ends; in FP32 a field's value can (a
+// permeability is the cube of a porosity ratio): see quot_field.
 __device__ __forceinline__ double quot(double a, double b) {
     const double y = inverse(b);
     const double q = a * y;
@@ -68,6 +72,11 @@ __device__ __forceinline__ float quot(float a, float b) {
     const float q = a * y;
     return __builtin_amdgcn_div_fixupf(__builtin_fmaf(__builtin_fmaf(-b, q, a), y, q), b, a);
 }
+
+// A quotient by a value of a field: in FP32 the division (0.5 % of a mixed
+// solve at 95^3).
+__device__ __forceinline__ double quot_field(double a, double b) { return quot(a, b); }
+__device__ __forceinline__ float quot_field(float a, float b) { return a / b; }
 
 // A copy in a register of its own: the queue moves out of the registers a
 // plane was loaded into, which then take the loads after next.  (Left to
