@@ -34,7 +34,8 @@
  *   field's extent are never written, except by pt_reset_state, which fills
  *   whole buffers; the kernels may read them (every load stays inside the
  *   buffer) and ignore their values.  Base pointers must be 256-byte aligned;
- *   row_pitch >= nx + 1.
+ *   row_pitch >= nx + 1 (launches take up to 67 million: the rows of a block's
+ *   tile lie within 2 GiB).
  * State.  The nine iterated fields (PT_VX .. PT_RZ) are double-buffered
  *   (Jacobi iteration: no point reads a value written in the same sweep).
  *   Bind both copies (copy 0 and 1); pt_current() tells which copy holds the

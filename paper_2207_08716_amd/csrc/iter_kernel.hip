@@ -203,8 +203,8 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
     const u32 sz = (u32)sizeof(T);
     const int row0 = max(by * (H - 2) - 1, 0), rows = min(by * (H - 2) - 1 + H - 1, g.ny) - row0 + 1;
     const int64_t tile0 = (int64_t)row0 * g.P;
-    const u32 col = (u32)((j - row0) * (int)g.P + i);
-    const u32 o_near = (u32)((min(max(j, 0), g.ny - 1) - row0) * (int)g.P + min(max(i, 0), g.nx - 1)) * sz;
+    const u32 col = (u32)(j - row0) * (u32)g.P + (u32)i;
+    const u32 o_near = ((u32)(min(max(j, 0), g.ny - 1) - row0) * (u32)g.P + (u32)min(max(i, 0), g.nx - 1)) * sz;
     const u32 o_cell = cell ? col * sz : OFF_NONE;
     const u32 o_vx = ((i >= 0) && (i <= g.nx) && cj) ? col * sz : OFF_NONE;
     const u32 o_vy = (ci && (j >= 0) && (j <= g.ny)) ? col * sz : OFF_NONE;
@@ -214,8 +214,8 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H, NORMS && sizeof(T) == 8))
     const u32 o_sx = (outc && i >= 1) ? col * so : OFF_NONE;
     const u32 o_sy = (outc && j >= 1) ? col * so : OFF_NONE;
     const u32 o_sc = outc ? col * so : OFF_NONE;
-    const u32 tile_bytes = (u32)(rows * (int)g.P) * sz;
-    const u32 tile_store = (u32)(rows * (int)g.P) * so;
+    const u32 tile_bytes = (u32)rows * (u32)g.P * sz;
+    const u32 tile_store = (u32)rows * (u32)g.P * so;
 
     // The field pointers are read from the argument segment at every plane
     // step (scalar loads that hit the scalar cache): kept in registers they
@@ -740,7 +740,7 @@ namespace {
 
 template <typename T, int MODE, bool NORMS, int RM, bool RW, int W, int H, bool STREAM>
 hipError_t launch_tile(const Geom& g, const TileShape& t, const Coef& c, const SweepPtrs<T>& p, hipStream_t s) {
-    if (g.P > (int64_t)(0x7fffffff / (H * sizeof(T)))) return hipErrorInvalidValue;   // a tile's rows: below 2 GiB
+    if (!rows_fit(g, H, sizeof(T))) return hipErrorInvalidValue;
     SweepArgs<T> a{g, CT<T>(c), p};
     a.g.kz = t.kz;
     const dim3 grid((unsigned)sweep_blocks(g, t)), block(W * H);

@@ -234,19 +234,29 @@ inline int64_t sweep_blocks(const Geom& g, const TileShape& t) {
     return tiles_xy(g, t.w, t.h) * ((g.nz + t.kz - 1) / t.kz);
 }
 
-// The cheapest tile and chunk by the model above, over the n shapes given
-// and, for each, the chunks that fill 1 to 16 blocks per compute unit (no
-// more than 4096 blocks beyond the first).  held: waves of a shape's blocks
-// that a compute unit's registers hold; weight: a factor on a shape's cost.
+// Whether the rows that a tile of h rows holds of a plane (of the box's ny + 1
+// at most) lie within 2 GiB, which the kernels' 32-bit offsets reach.
+inline bool rows_fit(const Geom& g, int h, int elem_bytes) {
+    return g.P <= (int64_t)0x7fffffff / ((int64_t)std::min(h, g.ny + 1) * elem_bytes);
+}
+
+// The cheapest tile and chunk by the model above, over those of the n shapes
+// given whose rows fit and, for each, the chunks that fill 1 to 16 blocks per
+// compute unit (no more than 4096 blocks beyond the first).  held: waves of a
+// shape's blocks that a compute unit's registers hold; weight: a factor on a
+// shape's cost.  (Where no shape's rows fit, the last shape, whose launch is
+// refused.)
 template <typename Held, typename Weight>
-inline TileShape pick_tile(const Geom& g, const SweepCost& sc, const TileShape* shapes, int n, Held held,
+inline TileShape pick_tile(const Geom& g, const SweepCost& sc, const TileShape* shapes, int n, int elem_bytes, Held held,
                            Weight weight) {
     const int cus = g.cus > 0 ? g.cus : DEFAULT_CUS;
     const bool cached = (double)g.nx * g.ny * g.nz * sc.cell_bytes <= LAST_LEVEL_CACHE;
     const double full = cached ? sc.full_cached : sc.full_memory;
-    TileShape best{};
+    TileShape best = shapes[n - 1];
+    best.kz = std::min(g.nz, KZ_MAX);
     double best_cost = -1.0;
     for (int q = 0; q < n; ++q) {
+        if (!rows_fit(g, shapes[q].h, elem_bytes)) continue;
         TileShape t = shapes[q];
         t.stream = !cached;
         const int64_t tiles = tiles_xy(g, t.w, t.h);
@@ -284,10 +294,11 @@ inline TileShape pick_tile(const Geom& g, const SweepCost& sc, const TileShape* 
 inline TileShape sweep_shape(const Geom& g, SweepKind kind) {
     int n = 0;
     const TileShape* shapes = sweep_shapes(kind, n);
-    if (kind == SK_F32 && g.tall32) n = 1;
+    const int elem_bytes = kind == SK_F32 || kind == SK_NORM32 ? 4 : 8;
+    if (kind == SK_F32 && g.tall32 && rows_fit(g, BY_CORR32, elem_bytes)) n = 1;
     const int other = kind == SK_F32 ? (corr32_short(g) ? BY_CORR32 : BY_CORR32_SHORT) : 0;
     return pick_tile(
-        g, sweep_cost(kind), shapes, n,
+        g, sweep_cost(kind), shapes, n, elem_bytes,
         [&](const TileShape& t, bool) {
             return kind == SK_F32 ? 24 : kind == SK_NORM32 ? 16 : 4 * sweep_waves(t.w * t.h, kind == SK_NORM64);
         },

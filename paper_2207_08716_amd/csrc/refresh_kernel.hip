@@ -88,8 +88,8 @@ struct Place {
         kz1 = min(g.nz, kz0 + g.kz);
         const int row0 = max(by * (H - 2) - 1, 0), rows = min(by * (H - 2) + H - 2, g.ny) - row0 + 1;
         tile0 = (int64_t)row0 * g.P;
-        off = (u32)((j - row0) * (int)g.P + i) * 8u;
-        bytes = (u32)(rows * (int)g.P) * 8u;
+        off = ((u32)(j - row0) * (u32)g.P + (u32)i) * 8u;
+        bytes = (u32)rows * (u32)g.P * 8u;
     }
 };
 
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(W * H, sweep_waves(W * H)) void k_fo_tiled(RefreshA
 
 template <int W, int H, bool STREAM>
 hipError_t launch_tile(bool fo, const TileShape& t, const RefreshArgs& a, hipStream_t s) {
-    if (a.g.P > (int64_t)(0x7fffffff / (H * sizeof(double)))) return hipErrorInvalidValue;   // a tile's rows: below 2 GiB
+    if (!rows_fit(a.g, H, sizeof(double))) return hipErrorInvalidValue;
     const dim3 grid((unsigned)sweep_blocks(a.g, t)), block(W * H);
     if (fo)
         hipLaunchKernelGGL((k_fo_tiled<W, H, STREAM>), grid, block, 0, s, a);

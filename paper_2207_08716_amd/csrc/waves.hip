@@ -48,8 +48,10 @@ constexpr unsigned ONE_BLOCK_LDS = 80 * 1024;   // bytes, beside the kernel's ow
 inline TileShape waves_tile(const Geom& g) {
     const SweepCost cost{0.31, 0.089, 0.135, 0.195, 0.73, 88.0};
     const bool cached = (double)g.nx * g.ny * g.nz * cost.cell_bytes <= LAST_LEVEL_CACHE;
+    // (past the cache the two larger tiles, unless their rows are too wide)
+    const int n = cached || !rows_fit(g, WAVE_TILES[0].h, 8) ? 5 : 2;
     return pick_tile(
-        g, cost, WAVE_TILES, cached ? 5 : 2, [](const TileShape&, bool fits) { return fits ? 28 : 1; },
+        g, cost, WAVE_TILES, n, 8, [](const TileShape&, bool fits) { return fits ? 28 : 1; },
         [](const TileShape&, bool) { return 1.0; });
 }
 constexpr int RB = 256;  // threads of the reduction kernels
@@ -107,9 +109,9 @@ __global__ __launch_bounds__(W * H) void k_waves_sweep(WavesArgs args) {
     // Pf and k (no flux comes out through the walls), only tile cells the rest.
     const int row0 = max(by * (H - 2) - 1, 0), rows = min(by * (H - 2) + H - 2, g.ny) - row0 + 1;
     const int64_t tile0 = (int64_t)row0 * g.P;
-    const u32 o_near = (u32)((min(max(j, 0), g.ny - 1) - row0) * (int)g.P + min(max(i, 0), g.nx - 1)) * 8u;
+    const u32 o_near = ((u32)(min(max(j, 0), g.ny - 1) - row0) * (u32)g.P + (u32)min(max(i, 0), g.nx - 1)) * 8u;
     const u32 o_out = tile ? o_near : OFF_NONE;
-    const u32 bytes = (u32)(rows * (int)g.P) * 8u;
+    const u32 bytes = (u32)rows * (u32)g.P * 8u;
     const double dtau = *args.p.dtau;
 
     using KPtrs = const __attribute__((address_space(4))) WavesPtrs;
@@ -395,7 +397,7 @@ double* walt(pt_waves* w, int f) { return w->f[f][1 - w->cur[f]]; }
 
 template <bool NORMS, int W, int H, bool STREAM>
 hipError_t launch_waves_tile(pt_waves* w, const WavesPtrs& p) {
-    if (w->geom.P > 0x7fffffff / (H * 8)) return hipErrorInvalidValue;   // a tile's rows: below 2 GiB
+    if (!rows_fit(w->geom, H, sizeof(double))) return hipErrorInvalidValue;
     WavesArgs a{w->geom, w->coef, p};
     a.g.kz = w->tile.kz;
     hipLaunchKernelGGL((k_waves_sweep<NORMS, W, H, STREAM>), dim3((unsigned)w->blocks), dim3(W * H),
