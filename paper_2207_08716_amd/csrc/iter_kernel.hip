@@ -759,14 +759,14 @@ hipError_t launch_sweep(const Geom& g, const Tiling& tl, const Coef& c, const Sw
     const TileShape& t = tl.shape[kind];
     const int wh = t.w * 100 + t.h;
     // (the sweeps with norms and the residual sweep, whose results are read
-    // next, measured the same either way)
+    // next, measured the same either way; grids past the cache take the lower
+    // tiles only where their rows are too wide for these)
     if constexpr (!NORMS && MODE != MD_RESID)
         if (t.stream) {
             if constexpr (sizeof(T) == 4)
                 if (wh == 6614) return launch_tile<T, MODE, NORMS, RM, RW, 66, 14, true>(g, t, c, p, s);
             if (wh == 6610) return launch_tile<T, MODE, NORMS, RM, RW, 66, 10, true>(g, t, c, p, s);
             if (wh == 3414) return launch_tile<T, MODE, NORMS, RM, RW, 34, 14, true>(g, t, c, p, s);
-            if (wh == 3406) return launch_tile<T, MODE, NORMS, RM, RW, 34, 6, true>(g, t, c, p, s);
         }
     if constexpr (NORMS) {
         if (wh == 6607) return launch_tile<T, MODE, NORMS, RM, RW, 66, 7, false>(g, t, c, p, s);
