@@ -7,6 +7,8 @@ import pytest
 
 from paper_2207_08716_amd import inputs, schedules
 
+from test_gpu_parity import STATE, _compare, _pair
+
 pytestmark = pytest.mark.gpu
 
 FROZEN = ("vx", "vy", "vz", "rx", "ry", "rz", "pt")
@@ -73,3 +75,20 @@ def test_frozen_multigrid_cycles_stay_finite():
     for n in ("vx", "vy", "vz", "pt"):
         assert np.array_equal(a.get(n), before[n]), n
     assert np.array_equal(a.get("pf"), b.get("pf")) and np.isfinite(a.get("pf")).all()
+
+
+@pytest.mark.parametrize("shape", [(7, 9, 8), (33, 30, 21), (75, 61, 40), (47, 45, 49), (64, 57, 61), (110, 50, 75),
+                                   (108, 34, 364), (48, 123, 227)])
+@pytest.mark.parametrize("shear", [0.0, 0.7])
+def test_frozen_sweeps_match_the_oracle_on_every_tile(shape, shear):
+    nx, ny, nz = shape
+    cfg = dataclasses.replace(inputs.config_fp64_picard(8), nx=nx, ny=ny, nz=nz, name="frozen")
+    cfg.phys = cfg.phys.replace(lx=nx / 40, ly=ny / 40, lz=nz / 40, mech_off=True, shear_bg=shear)
+    g, o = _pair(cfg)
+    for x in (g, o):
+        x.begin_step(*([False] if x is g else []))
+        x.refresh()
+    for update, norms in ((True, False), (True, True), (True, False), (False, False), (False, True), (False, False)):
+        g.iteration(update, norms)
+        o.iteration(update, norms)
+    _compare(g, o, STATE)
