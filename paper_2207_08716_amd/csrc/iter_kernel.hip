@@ -45,9 +45,9 @@
 //     combined on the host, divisions without operand rescaling, one
 //     pseudo-step quotient per cell: 355 vector instructions per plane step of
 //     the linear sweep instead of 640.
-// Measured at 511^3 (before all of this -> now): thesis sweep 6.17 -> 4.77 ms
-// (5.7 TB/s of its 24 streams; a copy reaches 6.0), with norms 8.75 -> 6.49,
-// linear 5.68 -> 4.39, residual 6.47 -> 3.78, FP32 correction 2.67 -> 2.21; at
+// Measured at 511^3 (before all of this -> now): thesis sweep 6.18 -> 4.76 ms
+// (5.7 TB/s of its 24 streams; a copy reaches 6.0), with norms 8.69 -> 6.49,
+// linear 5.67 -> 4.37, residual 6.49 -> 3.78, FP32 correction 2.66 -> 2.22; at
 // 32^3, mostly by its tile (sweep_shape, pt_internal.h), thesis 27.1 -> 7.7 us.
 //
 // Damped velocity update of the FP64 sweeps (eq (19) with the script's

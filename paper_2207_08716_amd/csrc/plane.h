@@ -47,13 +47,13 @@ __device__ __forceinline__ double inverse(double b) {
 }
 
 // a / b by an iteration on the reciprocal and a corrected quotient, without
-// the rescaling of the operands that the division has.  As accurate as the division (one unit in the last
-// place, two where the dividend is so small that its residual is subnormal)
-// for divisors from 2^-1022 to 2^1022, in FP32 from 2^-126 to 2^126;
-// infinities, zeros and NaN come out as from the division.  Outside, the
-// reciprocal leaves the exponent range and the result is wrong.  In FP64 no
-// quantity of a run comes near the ends; in FP32 a field's value can (a
-// permeability is the cube of a porosity ratio): see quot_field.
+// the rescaling of the operands that the division has.  Within one unit in
+// the last place of the division (two where the dividend is so small that its
+// residual is subnormal) for divisors from 2^-1022 to 2^1022, in FP32 from
+// 2^-126 to 2^126; infinities, zeros and NaN come out as from the division.
+// Outside, the reciprocal leaves the exponent range and the result is wrong.
+// In FP64 no quantity of a run comes near the ends; in FP32 a field's value
+// can (a permeability goes with the cube of a porosity): see quot_field.
 __device__ __forceinline__ double quot(double a, double b) {
     const double y = inverse(b);
     const double q = a * y;

@@ -123,9 +123,8 @@ inline int64_t tiling_cost(const Geom& g, int bx, int by) {
     return c * by;
 }
 
-// Whether the FP32 correction sweep runs its shorter tiles on this grid
-// (measured: 10 rows 19 % faster at 127^3 and 7 % at 255^3, 14 rows 12 %
-// faster at 511^3; the cost model picks the same in all three).
+// Whether the FP32 correction sweep's 10-row tiling costs less rows than its
+// 14-row one (see sweep_shape).
 inline bool corr32_short(const Geom& g) {
     if (g.tall32) return false;
     return tiling_cost(g, BX, BY_CORR32_SHORT) < tiling_cost(g, BX, BY_CORR32);
@@ -205,8 +204,9 @@ enum SweepKind { SK_F64, SK_F32, SK_NORM64, SK_NORM32 };
 // 121 -> 97 at 173 x 131 x 97.
 // (Fitted before the loads were spread over the plane step; since then, on 14
 // grids of 16^3 to 150 x 128 x 101, the tile it picks was within 3 % of the
-// fastest of all, at 40^3 within 10 %, and the linear sweep takes 6.4 us at
-// 16^3, 7.0 at 32^3, 14.0 at 64^3, 31.4 at 95^3, 65.8 at 127^3.)
+// fastest of all, at 40^3 within 10 % (11.9 us on 66 x 10 threads, 11.1 on
+// 66 x 6), and the linear sweep takes 6.4 us at 16^3, 7.0 at 32^3, 14.0 at
+// 64^3, 31.4 at 95^3, 65.8 at 127^3.)
 struct SweepCost {
     double step, wave, full_cached, full_memory, lead;
     double cell_bytes;   // streamed per cell
@@ -290,7 +290,13 @@ inline TileShape pick_tile(const Geom& g, const SweepCost& sc, const TileShape* 
 // come from memory (rows of 256 bytes; 34 x 14 against 66 x 10 threads at
 // 180^3: 284 and 255 us, at 383^3: 2.32 and 2.15 ms, at equal model cost).  Of
 // the FP32 sweep's 64-column tiles, the 14-row ones are preferred where their
-// tiling costs less rows (corr32_short), and run alone if asked for.
+// tiling costs less rows (corr32_short: it decides where the model has both
+// nearly equal, as at 200^3, 168 us against 171 on 10 rows), and run alone if
+// asked for.  Measured, 14 and 10 rows, where the rule takes 14: 150^3 70 and
+// 74 us, 300^3 498 and 537, 383^3 1.02 and 1.09 ms, 511^3 2.42 and 2.55; where
+// it takes 10: 64^3 11.2 and 9.7 us, 255^3 300 and 272, 127^3 34 either way;
+// at 173 x 131 x 97 43.7 on the 34 x 14 it takes, 42.0 on 14 rows (per sweep,
+// the check after every 15th included).
 inline TileShape sweep_shape(const Geom& g, SweepKind kind) {
     int n = 0;
     const TileShape* shapes = sweep_shapes(kind, n);

@@ -24,7 +24,7 @@
 // 66 x 10 block's plane step) as much as by memory (3.6 us), the divergence
 // by memory on large grids, both by a step's latency on small ones.  Refresh
 // and divergence together, before (fixed tiles of 66 x 10 and 66 x 14 threads,
-// branches around the stores) and now: 511^3 8.0 and 7.1 ms, 255x255x510 2.24
+// branches around the stores) and now: 511^3 8.4 and 6.9 ms, 255x255x510 2.24
 // and 1.70 ms, 173x131x97 215 and 140 us, 127^3 155 and 117 us, 32^3 38 and
 // 14 us.
 #include "plane.h"

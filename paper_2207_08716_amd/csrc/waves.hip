@@ -33,16 +33,15 @@
 namespace ptk {
 namespace {
 
-// Tiles of the sweep and their cost (pick_tile; constants in us).
-// Tiles of the sweep (pick_tile, constants in us; rms error 14 % over 340
-// measured launches from 8 x 8 x 32 to 95 x 95 x 380, where the tile picked is
-// the fastest measured or within 1 % of it).  Where the fields outgrow the
+// Tiles of the sweep and their cost (pick_tile, constants in us; rms error 14 %
+// over 340 measured launches from 8 x 8 x 32 to 95 x 95 x 380, where the tile
+// picked is the fastest measured or within 1 % of it).  Where the fields outgrow the
 // last-level cache, one block at a time on each compute unit: two interleave
 // their planes' accesses in memory (255 x 255 x 1020 1118 -> 1080 us, 506 x
-// 506 x 2042 9.06 -> 8.97 ms; the request for LDS keeps the second one away).
+// 506 x 2042 1 % less; the request for LDS keeps the second one away).
 // Measured, one tile of 66 x 12 threads -> these: 31 x 31 x 124 10.7 -> 5.5 us,
 // 64 x 60 x 250 19.8 -> 15.7, 95 x 95 x 380 78 -> 60, 127 x 127 x 508 170 -> 137,
-// 255 x 255 x 1020 1451 -> 1080, 506 x 506 x 2042 9.22 -> 8.97 ms.
+// 255 x 255 x 1020 1451 -> 1080, 506 x 506 x 2042 9.34 -> 8.75 ms.
 constexpr TileShape WAVE_TILES[] = {{66, 10}, {34, 14}, {34, 10}, {34, 6}, {34, 4}};
 constexpr unsigned ONE_BLOCK_LDS = 80 * 1024;   // bytes, beside the kernel's own
 inline TileShape waves_tile(const Geom& g) {
